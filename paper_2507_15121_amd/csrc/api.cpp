@@ -237,7 +237,7 @@ amped_status upload_tables(amped_tensor_s* t, ModeDev& m, int d, const HostModeL
     m.zero_row = aux;
     m.sink = static_cast<float*>(aux) + 4;
     m.n_gaps = (int64_t)lay.gaps.size() / 2;
-    m.queue = static_cast<unsigned*>(queues) + (size_t)d * amped::kQueueSlots;
+    m.queue = static_cast<unsigned*>(queues) + (size_t)d * amped::kQueueWords;
     t->flags[d] = lay.flags;
     t->touched[d] = lay.touched;
 cleanup:
@@ -255,8 +255,8 @@ amped_status build_host_layout(amped_tensor_s* t, const int32_t* indices, const 
     void* queues = nullptr;
     void* aux = nullptr;
     void* p = nullptr;
-    HIP_OR_FAIL(t->alloc(&queues, (size_t)(order + 1) * amped::kQueueSlots * sizeof(unsigned)), "hipMalloc(queues)");
-    HIP_OR_FAIL(hipMemset(queues, 0, (size_t)(order + 1) * amped::kQueueSlots * sizeof(unsigned)), "hipMemset(queues)");
+    HIP_OR_FAIL(t->alloc(&queues, (size_t)(order + 1) * amped::kQueueWords * sizeof(unsigned)), "hipMalloc(queues)");
+    HIP_OR_FAIL(hipMemset(queues, 0, (size_t)(order + 1) * amped::kQueueWords * sizeof(unsigned)), "hipMemset(queues)");
     HIP_OR_FAIL(t->alloc(&aux, (size_t)(4 + kSinkFloats) * sizeof(float)), "hipMalloc(aux)");
     HIP_OR_FAIL(hipMemset(aux, 0, (size_t)(4 + kSinkFloats) * sizeof(float)), "hipMemset(aux)");
     for (int b = 0; b < 2; ++b) {
@@ -301,7 +301,7 @@ amped_status build_host_layout(amped_tensor_s* t, const int32_t* indices, const 
         return fail(AMPED_ERR_NOMEM, "host allocation failed");
     }
     t->loss_dev = t->mode[0];
-    t->loss_dev.queue = static_cast<unsigned*>(queues) + (size_t)order * amped::kQueueSlots;
+    t->loss_dev.queue = static_cast<unsigned*>(queues) + (size_t)order * amped::kQueueWords;
 cleanup:
     return st;
 }
@@ -508,9 +508,9 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
         HIP_OR_FAIL(t->alloc(&d_vals, (size_t)nnz * 4), "hipMalloc(values)");
         if (nnz) HIP_OR_FAIL(hipMemcpy(d_vals, values, (size_t)nnz * 4, hipMemcpyHostToDevice), "hipMemcpy(values)");
         if (!keep_perm) HIP_OR_FAIL(t->alloc(&d_tmp_perm, (size_t)nnz * 4), "hipMalloc(perm)");
-        HIP_OR_FAIL(t->alloc(&d_queues, (size_t)(order + 1) * amped::kQueueSlots * sizeof(unsigned)),
+        HIP_OR_FAIL(t->alloc(&d_queues, (size_t)(order + 1) * amped::kQueueWords * sizeof(unsigned)),
                     "hipMalloc(queues)");
-        HIP_OR_FAIL(hipMemset(d_queues, 0, (size_t)(order + 1) * amped::kQueueSlots * sizeof(unsigned)),
+        HIP_OR_FAIL(hipMemset(d_queues, 0, (size_t)(order + 1) * amped::kQueueWords * sizeof(unsigned)),
                     "hipMemset(queues)");
         // 16 zero bytes followed by the store sink
         HIP_OR_FAIL(t->alloc(&d_aux, (size_t)(4 + kSinkFloats) * sizeof(float)), "hipMalloc(aux)");
@@ -580,7 +580,7 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
             if (st != AMPED_OK) goto cleanup;
         }
         t->loss_dev = t->mode[0];
-        t->loss_dev.queue = static_cast<unsigned*>(d_queues) + (size_t)order * amped::kQueueSlots;
+        t->loss_dev.queue = static_cast<unsigned*>(d_queues) + (size_t)order * amped::kQueueWords;
     } catch (const std::bad_alloc&) {
         st = fail(AMPED_ERR_NOMEM, "host allocation failed");
         goto cleanup;

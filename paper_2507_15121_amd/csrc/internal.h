@@ -35,6 +35,10 @@ constexpr int kGapPiece = 2048;
 // Work-queue counters per layout: the chunks are split into at most this many
 // contiguous stripes, each with its own counter (one stripe per XCD).
 constexpr int kQueueSlots = 8;
+// Words between two counters: a cache line each, so that atomics on different
+// counters do not wait for each other.
+constexpr int kQueueStride = 32;
+constexpr int kQueueWords = kQueueSlots * kQueueStride;
 
 // ----------------------------------------------------------------- host layout
 struct HostModeLayout {
@@ -88,7 +92,7 @@ struct ModeDev {
     const int32_t* zero_rows = nullptr;            // [n_zero]
     const int32_t* gaps = nullptr;                 // [2 * n_gaps]
     int64_t nnz = 0, chunk = 0, n_chunks = 0, rows = 0, n_zero = 0, n_gaps = 0;
-    unsigned* queue = nullptr;                     // kQueueSlots device work-queue counters
+    unsigned* queue = nullptr;                     // kQueueSlots device work-queue counters, kQueueStride words apart
     const int32_t* hot = nullptr;                  // hot-row tables of this mode [kHotTableLen]
     const void* zero_row = nullptr;                // 16 zero bytes
     float* sink = nullptr;                         // kSinkFloats floats of write-only scratch

@@ -111,8 +111,9 @@ struct KParams {
     const float* own;
     float* out;
     double* loss;
-    unsigned* queue;  // n_stripes counters
+    unsigned* queue;  // n_stripes counters, kQueueStride words apart
     int n_stripes;    // contiguous chunk stripes, one counter each (1..kQueueSlots)
+    int stripe_len;   // chunks per stripe
     int64_t nnz, chunk, n_chunks, rows;
     int64_t ld;     // row stride of factors and output, in elements
     int col0;       // first column handled by this launch
@@ -328,43 +329,101 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Work queue.  The chunks are split into S contiguous stripes, each with its
-// own counter.  A wave starts on stripe `home` and moves on to the next stripe
-// when one runs dry, so with one stripe per XCD the consecutive chunks of a
-// stripe (neighbouring output rows; for a heavy row, neighbouring input
-// indices) are taken by one XCD's CUs while any chunk is left on its stripe,
-// and no CU idles while any chunk is left anywhere.  With S = 1 this is one
-// global counter.  A wave reads each counter at most once past the end of its
-// stripe, so a counter never exceeds the stripe's chunks plus the waves of the
-// grid (below 2^32: chunks < 2^31), and it is compared as unsigned.
+// Work distribution.  The chunks are split into S contiguous stripes, each with
+// its own counter.  A wave's first chunk is fixed by its place in the grid; the
+// next ones come from the counter of its home stripe (with one stripe per XCD
+// the consecutive chunks of a stripe, neighbouring output rows or, for a heavy
+// row, neighbouring input indices, are taken by one XCD's CUs while any chunk
+// is left on it), and when that runs dry from the stripe with most chunks left,
+// so no CU idles while any chunk is left anywhere.
+//
+// What bounds it: an atomic on one cache line takes 12 ns, one after the other,
+// whatever the wave.  So every counter has a line of its own, the first chunks
+// and a grid with a wave for every chunk need no atomic, and a wave looks at all
+// counters with one load (lane x reads stripe x) before it takes from another
+// stripe.  Counters side by side in one line, with every wave ending by a
+// failing atomic on each of the 8, took 2048 * 8 * 12 ns = 195 us at the end of
+// every launch, whatever its work: 228 us instead of 48 us for 25 chunks
+// (100k nonzeros, rank 16), 273 instead of 102 us for 5M nonzeros at rank 32,
+// 2.95 instead of 2.86 ms for 200M.  The next chunk is asked for before the
+// current one is worked on, so the atomic's latency is hidden.
+//
+// A counter grows only by its stripe's chunks and by at most one failing add per
+// wave of the grid (a stripe once seen empty is not asked again), so it stays
+// below 2^32 (chunks < 2^31).
 struct ChunkQueue {
     unsigned* q;
-    int64_t n_chunks;
-    int S, home, tried = 0;
-    int64_t b0 = 0, b1 = 0;   // current stripe's chunk range
+    unsigned n, len;      // chunks; chunks per stripe: stripe x holds [x * len, min((x + 1) * len, n))
+    unsigned S, home;     // stripes, this wave's stripe
+    unsigned per, rest;   // waves of the grid per stripe, and stripes with one block of waves more
+    unsigned waves;       // per block
+    bool more;            // the home stripe may have more chunks
+    unsigned asked;       // lane 0: the home counter's value
 
-    __device__ __forceinline__ ChunkQueue(unsigned* q_, int64_t n, int stripes, int home_)
-        : q(q_), n_chunks(n), S(stripes), home(home_)
+    __device__ __forceinline__ unsigned size(unsigned x) const { return min(n, (x + 1) * len) - min(n, x * len); }
+    // chunks of stripe x that are first chunks of its waves, outside the counter
+    __device__ __forceinline__ unsigned fixed(unsigned x) const { return per + (x < rest ? waves : 0u); }
+
+    // the wave's first chunk, or -1
+    __device__ __forceinline__ int start(const KParams& p, unsigned block, unsigned wave, unsigned waves_per_block)
     {
-        set_stripe();
-    }
-    __device__ __forceinline__ void set_stripe()
-    {
-        const int x = (home + tried) % S;
-        b0 = (int64_t)x * n_chunks / S;
-        b1 = (int64_t)(x + 1) * n_chunks / S;
-    }
-    // next chunk, or -1 when every stripe is exhausted (wave-uniform)
-    __device__ __forceinline__ int64_t pop(int lane)
-    {
-        while (tried < S) {
-            unsigned c = 0;
-            if (lane == 0) c = atomicAdd(q + (home + tried) % S, 1u);
-            c = (unsigned)__builtin_amdgcn_readfirstlane((int)c);
-            if ((int64_t)c < b1 - b0) return b0 + (int64_t)c;
-            if (++tried < S) set_stripe();
+        const unsigned blocks = gridDim.x;
+        q = p.queue;
+        n = (unsigned)p.n_chunks;
+        S = (unsigned)p.n_stripes;
+        len = (unsigned)p.stripe_len;
+        waves = waves_per_block;
+        home = block % S;
+        per = blocks / S * waves;
+        rest = blocks % S;
+        asked = 0;
+        more = n > blocks * waves;
+        if (!more) {   // a wave for every chunk: no counter (S = 0: none to look at)
+            S = 0;
+            const unsigned c = wave * blocks + block;   // spread over the CUs first
+            return c < n ? (int)c : -1;
         }
-        return -1;
+        const unsigned i = block / S * waves + wave;
+        return i < size(home) ? (int)(home * len + i) : take(0u);
+    }
+    // asks for the home stripe's next chunk; next() gets the answer
+    __device__ __forceinline__ void ask(int lane)
+    {
+        if (more && lane == 0) asked = atomicAdd(q + home * kQueueStride, 1u);
+    }
+    __device__ __forceinline__ int next()
+    {
+        if (more) {
+            const unsigned i = (unsigned)__builtin_amdgcn_readfirstlane((int)asked) + fixed(home);
+            if (i < size(home)) return (int)(home * len + i);
+        }
+        return S == 0 ? -1 : take(1u << home);
+    }
+    // a chunk of the stripe with most left, or -1 when none is left anywhere
+    // (dry: bits of stripes seen empty)
+    __device__ __forceinline__ int take(unsigned dry)
+    {
+        more = false;
+        const unsigned lane = threadIdx.x & 63;
+        for (;;) {
+            unsigned best = lane & 7;
+            if (lane < S && !((dry >> lane) & 1u)) {
+                const unsigned c = __hip_atomic_load(q + lane * kQueueStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
+                                   fixed(lane);
+                const unsigned sz = size(lane);
+                best |= c < sz ? min(sz - c, 0x0FFFFFFFu) << 3 : 0u;
+            }
+#pragma unroll
+            for (int m = 1; m < 8; m <<= 1) best = max(best, (unsigned)__shfl_xor((int)best, m, 64));
+            best = (unsigned)__builtin_amdgcn_readfirstlane((int)best);
+            if (best < 8) return -1;
+            const unsigned x = best & 7;
+            unsigned c = 0;
+            if (lane == 0) c = atomicAdd(q + x * kQueueStride, 1u);
+            c = (unsigned)__builtin_amdgcn_readfirstlane((int)c) + fixed(x);
+            if (c < size(x)) return (int)(x * len + c);
+            dry |= 1u << x;
+        }
     }
 };
 
@@ -505,11 +564,10 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
 #if AMPED_QUEUE_STATS
     unsigned long long st_chunks = 0, st_nnz = 0, st_first = 0;
 #endif
-    ChunkQueue cq(p.queue, p.n_chunks, p.n_stripes, (int)(blockIdx.x % (unsigned)p.n_stripes));
-    for (;;) {
-        const int64_t chunk = cq.pop(lane);
-        if (chunk < 0) break;
-        const int64_t cs = chunk * p.chunk;
+    ChunkQueue cq;
+    for (int chunk = cq.start(p, blockIdx.x, wv, kWaves); chunk >= 0; chunk = cq.next()) {
+        cq.ask(lane);
+        const int64_t cs = (int64_t)chunk * p.chunk;
         const int clen = (int)(min(cs + p.chunk, p.nnz) - cs);
 #if AMPED_QUEUE_STATS
         if (st_chunks == 0) st_first = (unsigned long long)wall_clock64();
@@ -868,13 +926,21 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
     }
 #endif
     if constexpr (LOSS) {
-        // wave sum in fp64, one atomic per wave.  The first log2(LPR) steps add
-        // equal values (every lane of a group holds the group's sum), so they
-        // are exact doublings undone by the final 1/LPR.
+        // wave sum in fp64.  The first log2(LPR) steps add equal values (every
+        // lane of a group holds the group's sum), so they are exact doublings
+        // undone by the final 1/LPR.  One atomic per block: atomics on one
+        // address take 12 ns each, one after the other.
 #pragma unroll
         for (int m = 1; m < 64; m <<= 1) lsum += __shfl_xor(lsum, m, 64);
         lsum *= 1.0 / LPR;
-        if (lane == 0 && lsum != 0.0) atomicAdd(p.loss, lsum);
+        __shared__ double s_loss[kWaves];
+        if (lane == 0) s_loss[wv] = lsum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double sum = 0.0;
+            for (int w = 0; w < kWaves; ++w) sum += s_loss[w];
+            if (sum != 0.0) atomicAdd(p.loss, sum);
+        }
     }
 }
 

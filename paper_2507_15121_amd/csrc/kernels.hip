@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(kBlock) init_kernel(float* out, int64_t ld, in
                                                       double* loss)
 {
     if (blockIdx.x == 0) {
-        if (queue && threadIdx.x < kQueueSlots) queue[threadIdx.x] = 0u;
+        if (queue && threadIdx.x < kQueueSlots) queue[threadIdx.x * kQueueStride] = 0u;
         if (loss && threadIdx.x == 0) *loss = 0.0;
     }
     if (!out) return;
@@ -196,6 +196,11 @@ Shape launch_shape(KernelFn fn, int block, int nin, int row_bytes, bool cache)
     return sh;
 }
 
+// Blocks of a launch: the persistent grid, or a block per chunk when there are
+// fewer chunks (one wave of each block then has work: the chunks spread over
+// the CUs).
+int launch_grid(const Shape& sh, const ModeDev& m) { return (int)std::min<int64_t>(sh.grid, m.n_chunks); }
+
 hipError_t launch_init(const ModeDev& m, float* out, int64_t ld, int col0, int ncols, double* loss,
                        hipStream_t st)
 {
@@ -226,6 +231,7 @@ KParams base_params(const ModeDev& m)
     k.val = m.val;
     k.queue = m.queue;
     k.n_stripes = queue_stripes();
+    k.stripe_len = (int)((m.n_chunks + k.n_stripes - 1) / k.n_stripes);
     k.nnz = m.nnz;
     k.chunk = m.chunk;
     k.n_chunks = m.n_chunks;
@@ -310,10 +316,11 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
         k.col0 = col0;
         k.ncols = ncols;
 #if AMPED_QUEUE_STATS
-        if ((e = qstats_attach(k, sh.grid, block, a.stream)) != hipSuccess) return e;
+        if ((e = qstats_attach(k, launch_grid(sh, m), block, a.stream)) != hipSuccess) return e;
 #endif
         void* args[] = {&k};
-        e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(sh.grid), dim3(block), args, sh.dyn, a.stream);
+        e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(launch_grid(sh, m)), dim3(block), args, sh.dyn,
+                            a.stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -364,10 +371,11 @@ hipError_t launch_cp_loss(const LossArgs& a)
     if (sh.grid <= 0) return hipErrorInvalidDevice;
     set_hot(k, sh.hot_k, a.in_hot, a.order - 1);
 #if AMPED_QUEUE_STATS
-    if ((e = qstats_attach(k, sh.grid, block, a.stream)) != hipSuccess) return e;
+    if ((e = qstats_attach(k, launch_grid(sh, m), block, a.stream)) != hipSuccess) return e;
 #endif
     void* args[] = {&k};
-    return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(sh.grid), dim3(block), args, sh.dyn, a.stream);
+    return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(launch_grid(sh, m)), dim3(block), args, sh.dyn,
+                           a.stream);
 }
 
 }  // namespace amped

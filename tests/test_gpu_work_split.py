@@ -1,0 +1,46 @@
+"""How the nonzeros are handed to the waves, at the edges of the split: every
+chunk exactly once whether the grid has a wave for each of them or takes them
+from the counters.  Integer inputs, whose sums are exact in fp32 in any order,
+so every result equals the oracle's bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import dev_factors, hip_mttkrp, log, oracle_mttkrp
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2507_15121_amd import api  # noqa: E402
+
+
+def int_problem(dims, nnz, rank, seed, heavy=0.2):
+    """nnz random coordinates (duplicates add), a share of them in one mode-0 row."""
+    rng = np.random.default_rng(seed)
+    idx = np.stack([rng.integers(0, d, nnz) for d in dims]).astype(np.int32)
+    idx[0, rng.random(nnz) < heavy] = dims[0] // 2
+    val = rng.integers(1, 4, nnz).astype(np.float32)
+    factors = [rng.integers(-2, 3, (d, rank)).astype(np.float32) for d in dims]
+    return idx, val, factors
+
+
+@pytest.mark.parametrize("chunks", [1, 7, 255, 256, 257, 2047, 2048, 2049, 4097, 30011])
+def test_every_chunk_once(chunks):
+    """Chunk counts around a grid of 256 blocks of 8 waves (and of 512 or 768 of 4)."""
+    dims, rank = (900, 400, 300), 32
+    idx, val, factors = int_problem(dims, chunks * 4 - 1, rank, chunks)
+    t = api.Tensor(idx, val, dims, chunk_nnz=4)
+    dfac = dev_factors(factors)
+    loss_ref, _ = oracle.cp_loss(idx, val, [f.astype(np.float64) for f in factors])
+    for d in range(3):
+        np.testing.assert_array_equal(hip_mttkrp(t, d, dfac), oracle_mttkrp(idx, val, dims, factors, d).astype(np.float32))
+        grad = torch.full((dims[d], rank), float("nan"), device="cuda")
+        loss, _ = api.cp_loss_grad(t, d, dfac, -2.0, out=grad)
+        np.testing.assert_array_equal(grad.cpu().numpy(), oracle.cp_grad(idx, val, dims, factors, d).astype(np.float32))
+        assert float(loss) == loss_ref
+    assert float(api.cp_loss(t, dfac)) == loss_ref
+    log("%d chunks: exact" % chunks)
+    t.close()

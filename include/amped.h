@@ -59,9 +59,12 @@ typedef enum {
 
 /* Creation options; pass NULL for the defaults. */
 typedef struct {
-    int64_t chunk_nnz;        /* CH: nonzeros per work-queue chunk, <= 2^28; 0 = 4096.  Part of
+    int64_t chunk_nnz;        /* CH: nonzeros per chunk, <= 2^28; 0 = 4096.  Part of
                                  the layout contract (chunk k holds positions
-                                 [k*CH, min((k+1)*CH, nnz)) of a mode's order).        */
+                                 [k*CH, min((k+1)*CH, nnz)) of a mode's order).  A given
+                                 CH is also what the kernels' waves take from the work
+                                 queue at a time; with 0 the library sizes those work
+                                 units by the nonzeros.                                */
     int64_t device_byte_cap;  /* 0 = no cap; otherwise creation fails with NOMEM,
                                  before touching the device, if the layouts would
                                  need more device bytes than this.                     */

@@ -69,6 +69,7 @@ struct amped_tensor_s {
     int order = 0;
     int64_t dims[kMaxOrder] = {};
     int64_t nnz = 0, chunk = 0, n_chunks = 0;
+    int64_t unit = 0;                       // nonzeros per work unit of the kernels
     int device = 0;
     bool keep_perm = false;
     int64_t device_bytes = 0;
@@ -230,8 +231,8 @@ amped_status upload_tables(amped_tensor_s* t, ModeDev& m, int d, const HostModeL
         m.gaps = static_cast<int32_t*>(p);
     }
     m.nnz = t->nnz;
-    m.chunk = t->chunk;
-    m.n_chunks = t->n_chunks;
+    m.chunk = t->unit;
+    m.n_chunks = (t->nnz + t->unit - 1) / t->unit;
     m.rows = t->dims[d];
     m.n_zero = (int64_t)lay.zero_rows.size();
     m.zero_row = aux;
@@ -273,7 +274,7 @@ amped_status build_host_layout(amped_tensor_s* t, const int32_t* indices, const 
         for (int d = 0; d < order; ++d) {
             HostModeLayout lay;
             amped::mode_order(t->dims, nnz, indices, lex, d, lay.perm);
-            amped::mode_tables(t->dims, nnz, indices, d, t->chunk, lay);
+            amped::mode_tables(t->dims, nnz, indices, d, t->chunk, lay, t->unit);
             auto& h = t->hmode[d];
             HIP_OR_FAIL(t->host_alloc(&p, padded), "hipHostMalloc(out_idx)");
             h.out_idx = static_cast<int32_t*>(p);
@@ -353,7 +354,7 @@ amped_status stream_shards(amped_tensor_s* t, int d, const ModeDev& base, hipStr
         if ((e = hipEventRecord(t->copied[b], t->copy_stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
         if ((e = hipStreamWaitEvent(s, t->copied[b], 0)) != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
         m.nnz = len;
-        m.n_chunks = (len + t->chunk - 1) / t->chunk;
+        m.n_chunks = (len + t->unit - 1) / t->unit;
         m.prev_key = start > 0 ? h.out_idx[start - 1] : -1;
         m.next_key = end < nnz ? h.out_idx[end] : -1;
         if (i > 0) {
@@ -462,6 +463,9 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
     t->nnz = nnz;
     t->chunk = chunk;
     t->n_chunks = (nnz + chunk - 1) / chunk;
+    t->unit = chunk;
+    if (!opts || opts->chunk_nnz == 0)
+        t->unit = host_layout ? amped::stream_work_unit(std::min(stage_len, nnz)) : amped::work_unit(nnz);
     t->device = dev;
     t->keep_perm = keep_perm;
     if (host_layout) {
@@ -575,7 +579,7 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
             HIP_OR_FAIL(amped::launch_permute32(p, d_vals, static_cast<int32_t*>(d_perm), nnz, stream), "permute");
             m.val = static_cast<float*>(p);
             HIP_OR_FAIL(hipStreamSynchronize(stream), "layout build");
-            amped::mode_tables_sorted(keys_h.data(), nnz, dims[d], chunk, lay);
+            amped::mode_tables_sorted(keys_h.data(), nnz, dims[d], chunk, lay, t->unit);
             st = upload_tables(t, m, d, lay, d_queues, d_aux);
             if (st != AMPED_OK) goto cleanup;
         }

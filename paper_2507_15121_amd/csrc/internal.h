@@ -15,6 +15,42 @@ constexpr int64_t kDefaultChunk = 4096;
 // Largest chunk: a chunk's metadata arrays stay below 2^30 bytes, so 32-bit
 // buffer offsets into them (with an out-of-range bias) never wrap.
 constexpr int64_t kMaxChunk = int64_t(1) << 28;
+// Nonzeros per work unit (what one wave takes from the queue) of a layout of nnz
+// nonzeros, when the caller leaves the chunk size to the library.  A unit costs
+// a wave about 11 us beside 6 us for each 256 nonzeros (rank 32), and a last
+// round of units that fills the 2048 waves of the grid only in part leaves the
+// rest idle: so up to 4 whole rounds of equal units, of at most 5120 nonzeros
+// (longer ones spread the waves' rows over more of the factors: at 50M nonzeros
+// one round of 24576 takes 2234 us for all modes, units of 4096 take 2148), and
+// above that units of 4096, whose last round is short.  Measured, all modes at
+// rank 32, units of 4096 against this rule: 100k nonzeros (rank 16) 145 -> 41
+// us, 1M 94 us (units of 512), 5M 309 -> 258 us, 10M 603 -> 482 us, 20M with
+// bfloat16 rank 64 1120 -> 1111 us.
+constexpr int64_t kGridWaves = 2048;
+constexpr int64_t kTileNnz = 256;      // a unit is whole tiles of the kernel
+constexpr int64_t kMaxRoundUnit = 5120;
+inline int64_t work_unit(int64_t nnz)
+{
+    const int64_t rounds = (nnz + kGridWaves * kMaxRoundUnit - 1) / (kGridWaves * kMaxRoundUnit);
+    if (rounds > 4) return kDefaultChunk;
+    const int64_t waves = kGridWaves * (rounds > 0 ? rounds : 1);
+    const int64_t tiles = (nnz + waves * kTileNnz - 1) / (waves * kTileNnz);
+    return kTileNnz * (tiles > 0 ? tiles : 1);
+}
+// The same for layouts that are streamed in shards of whole chunks of 4096: a
+// power of two, so that shards end at unit ends too.
+inline int64_t stream_work_unit(int64_t shard)
+{
+    int64_t u = kTileNnz;
+    while (u < kDefaultChunk && u * kGridWaves < shard) u *= 2;
+    return u;
+}
+// Least nonzeros of a launch that keeps the most-used factor rows in LDS.  Every
+// block copies them first, about 10 us; all modes at rank 32 without and with
+// the copy: 5M nonzeros 258 and 260 us, 10M 504 and 482, 20M 989 and 889, 200M
+// 9433 and 8718 (order 4, 10M: 815 and 831).
+constexpr int64_t kHotMinNnz = int64_t(8) << 20;
+
 // Hot-row tables: for every power of two K <= kHotMax, a direct-mapped table
 // of K slots; slot s names the row r with r % K == s that the most nonzeros
 // use in this mode (kHotEmpty if no row maps to s).  The tables of all K are
@@ -44,7 +80,7 @@ constexpr int kQueueWords = kQueueSlots * kQueueStride;
 struct HostModeLayout {
     std::vector<int32_t> perm;        // position -> input nonzero
     std::vector<uint8_t> flags;       // per chunk: bit0 head continues, bit1 tail continues
-    std::vector<int32_t> zero_rows;   // rows shared by two or more chunks, then untouched rows of short runs
+    std::vector<int32_t> zero_rows;   // rows shared by two or more work units, then untouched rows of short runs
     std::vector<int32_t> gaps;        // (start, length) pairs of long untouched-row runs
     std::vector<int32_t> hot;         // hot-row tables of this mode's rows [kHotTableLen]
     int64_t touched = 0;              // distinct output indices
@@ -58,13 +94,14 @@ std::vector<int32_t> lex_order(int order, const int64_t* dims, int64_t nnz, cons
 void mode_order(const int64_t* dims, int64_t nnz, const int32_t* idx, const std::vector<int32_t>& base,
                 int mode, std::vector<int32_t>& perm);
 
-// Chunk flags, zero-row list, long gaps, hot-row tables and touched count of a
-// mode order.
+// Chunk flags, zero-row list (of units of `unit` nonzeros; 0: of the chunks),
+// long gaps, hot-row tables and touched count of a mode order.
 void mode_tables(const int64_t* dims, int64_t nnz, const int32_t* idx, int mode, int64_t chunk,
-                 HostModeLayout& lay);
+                 HostModeLayout& lay, int64_t unit = 0);
 
 // The same tables from the mode's sorted output-index column keys[nnz].
-void mode_tables_sorted(const int32_t* keys, int64_t nnz, int64_t rows, int64_t chunk, HostModeLayout& lay);
+void mode_tables_sorted(const int32_t* keys, int64_t nnz, int64_t rows, int64_t chunk, HostModeLayout& lay,
+                        int64_t unit = 0);
 
 // True when the COO is already in lexicographic order of (i_0, ..., i_{N-1}).
 bool is_lexicographic(int order, int64_t nnz, const int32_t* idx);
@@ -91,7 +128,8 @@ struct ModeDev {
     const float* val = nullptr;                    // [nnz]
     const int32_t* zero_rows = nullptr;            // [n_zero]
     const int32_t* gaps = nullptr;                 // [2 * n_gaps]
-    int64_t nnz = 0, chunk = 0, n_chunks = 0, rows = 0, n_zero = 0, n_gaps = 0;
+    int64_t nnz = 0, rows = 0, n_zero = 0, n_gaps = 0;
+    int64_t chunk = 0, n_chunks = 0;               // nonzeros per work unit, work units
     unsigned* queue = nullptr;                     // kQueueSlots device work-queue counters, kQueueStride words apart
     const int32_t* hot = nullptr;                  // hot-row tables of this mode [kHotTableLen]
     const void* zero_row = nullptr;                // 16 zero bytes

@@ -526,15 +526,30 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
 #pragma unroll
                 for (int w = 0; w < NIN; ++w) {
                     for (int i = threadIdx.x; i < K; i += kMttkrpBlock) tag[w * K + i] = p.hot[w][i];
+                    // 4 pieces per thread at a time, their loads in flight together
                     constexpr int PR = RB / 16;   // 16-byte pieces per row
-                    for (int i = threadIdx.x; i < K * PR; i += kMttkrpBlock) {
-                        const int slot = i / PR, piece = i % PR;
-                        const int row = p.hot[w][slot];
-                        u32x4 v = {0u, 0u, 0u, 0u};
-                        if (row >= 0)
-                            v = *reinterpret_cast<const u32x4*>(static_cast<const char*>(p.fac[w]) +
-                                                                 (uint64_t)row * RB + piece * 16);
-                        *reinterpret_cast<u32x4*>(s_dyn + hrow + ((size_t)w * K + slot) * RB + piece * 16) = v;
+                    for (int i0 = threadIdx.x; i0 < K * PR; i0 += 4 * kMttkrpBlock) {
+                        int row[4];
+                        u32x4 v[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int i = i0 + u * kMttkrpBlock;
+                            row[u] = i < K * PR ? p.hot[w][i / PR] : kHotEmpty;
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int piece = (i0 + u * kMttkrpBlock) % PR;
+                            v[u] = u32x4{0u, 0u, 0u, 0u};
+                            if (row[u] >= 0)
+                                v[u] = *reinterpret_cast<const u32x4*>(static_cast<const char*>(p.fac[w]) +
+                                                                        (uint64_t)row[u] * RB + piece * 16);
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int i = i0 + u * kMttkrpBlock;
+                            if (i < K * PR)
+                                *reinterpret_cast<u32x4*>(s_dyn + hrow + ((size_t)w * K + i / PR) * RB + (i % PR) * 16) = v[u];
+                        }
                     }
                 }
             }

@@ -190,7 +190,7 @@ void push_gap(std::vector<int32_t>& gaps, int64_t start, int64_t len)
 // Chunk flags, zero-row list, long gaps, hot-row tables and touched count from
 // key(p), the output index at position p of the mode's order.
 template <typename Key>
-void tables_from_keys(int64_t nnz, int64_t rows, int64_t chunk, const Key& key, HostModeLayout& lay)
+void tables_from_keys(int64_t nnz, int64_t rows, int64_t chunk, int64_t unit, const Key& key, HostModeLayout& lay)
 {
     const int64_t n_chunks = (nnz + chunk - 1) / chunk;
     lay.flags.assign(n_chunks, 0);
@@ -203,11 +203,10 @@ void tables_from_keys(int64_t nnz, int64_t rows, int64_t chunk, const Key& key, 
         lay.flags[k] = f;
     }
     lay.zero_rows.clear();
-    for (int64_t k = 1; k < n_chunks; ++k)
-        if (lay.flags[k] & 1) {
-            const int32_t r = key(k * chunk);
-            if (lay.zero_rows.empty() || lay.zero_rows.back() != r) lay.zero_rows.push_back(r);
-        }
+    for (int64_t p = unit; p < nnz; p += unit) {
+        const int32_t r = key(p);
+        if (key(p - 1) == r && (lay.zero_rows.empty() || lay.zero_rows.back() != r)) lay.zero_rows.push_back(r);
+    }
     // distinct output indices; untouched rows as long runs or single rows
     int nt = omp_get_max_threads();
     if (nt < 1) nt = 1;
@@ -253,16 +252,17 @@ void tables_from_keys(int64_t nnz, int64_t rows, int64_t chunk, const Key& key, 
 }  // namespace
 
 void mode_tables(const int64_t* dims, int64_t nnz, const int32_t* idx, int mode, int64_t chunk,
-                 HostModeLayout& lay)
+                 HostModeLayout& lay, int64_t unit)
 {
     const int32_t* col = idx + (int64_t)mode * nnz;
     const int32_t* perm = lay.perm.data();
-    tables_from_keys(nnz, dims[mode], chunk, [&](int64_t p) { return col[perm[p]]; }, lay);
+    tables_from_keys(nnz, dims[mode], chunk, unit > 0 ? unit : chunk, [&](int64_t p) { return col[perm[p]]; }, lay);
 }
 
-void mode_tables_sorted(const int32_t* keys, int64_t nnz, int64_t rows, int64_t chunk, HostModeLayout& lay)
+void mode_tables_sorted(const int32_t* keys, int64_t nnz, int64_t rows, int64_t chunk, HostModeLayout& lay,
+                        int64_t unit)
 {
-    tables_from_keys(nnz, rows, chunk, [&](int64_t p) { return keys[p]; }, lay);
+    tables_from_keys(nnz, rows, chunk, unit > 0 ? unit : chunk, [&](int64_t p) { return keys[p]; }, lay);
 }
 
 bool is_lexicographic(int order, int64_t nnz, const int32_t* idx)

@@ -44,3 +44,36 @@ def test_every_chunk_once(chunks):
     assert float(api.cp_loss(t, dfac)) == loss_ref
     log("%d chunks: exact" % chunks)
     t.close()
+
+
+@pytest.mark.parametrize("nnz", [1, 255, 256, 257, 256 * 2048, 256 * 2048 + 1, 512 * 2048 + 1])
+@pytest.mark.parametrize("rank", [16, 32, 128])
+def test_library_sized_units(nnz, rank):
+    """Units that the library sizes, around whole tiles of 256 nonzeros and
+    whole rounds of 2048 waves; rows shared by many units and by none."""
+    dims = (40_000, 300, 200)
+    idx, val, factors = int_problem(dims, nnz, rank, nnz % 1000 + rank)
+    t = api.Tensor(idx, val, dims)
+    assert t.chunk_nnz == 4096   # the layout contract's chunks are as before
+    dfac = dev_factors(factors)
+    for d in (0, 2):
+        np.testing.assert_array_equal(hip_mttkrp(t, d, dfac), oracle_mttkrp(idx, val, dims, factors, d).astype(np.float32))
+    t.close()
+
+
+def test_rows_kept_in_lds():
+    """9M nonzeros: the launch copies the most-used rows to LDS first (a share
+    of the factors' rows, so that cached and other rows mix)."""
+    dims, rank = (3000, 2000, 900), 32
+    rng = np.random.default_rng(9)
+    nnz = 9_000_000
+    idx = np.stack([np.minimum((d * rng.random(nnz) ** 4).astype(np.int32), d - 1) for d in dims])
+    val = rng.integers(0, 2, nnz).astype(np.float32)
+    factors = [rng.integers(-1, 2, (d, rank)).astype(np.float32) for d in dims]
+    t = api.Tensor(idx, val, dims)
+    dfac = dev_factors(factors)
+    for d in range(3):
+        ref = oracle_mttkrp(idx, val, dims, factors, d)
+        assert np.abs(ref).max() < 2 ** 24
+        np.testing.assert_array_equal(hip_mttkrp(t, d, dfac), ref.astype(np.float32))
+    t.close()

@@ -46,10 +46,14 @@ inline int64_t stream_work_unit(int64_t shard)
     return u;
 }
 // Least nonzeros of a launch that keeps the most-used factor rows in LDS.  Every
-// block copies them first, about 10 us; all modes at rank 32 without and with
-// the copy: 5M nonzeros 258 and 260 us, 10M 504 and 482, 20M 989 and 889, 200M
-// 9433 and 8718 (order 4, 10M: 815 and 831).
-constexpr int64_t kHotMinNnz = int64_t(8) << 20;
+// block copies them first, about 10 us, and the instances with the copy hold 70
+// more registers; all modes at rank 32 without and with it: 5M nonzeros 235 and
+// 258 us, 10M 456 and 469, 20M 875 and 893, 50M 2175 and 2118, 200M 9146 and 8650
+// (order 4, 10M: 764 and 827; rank 64 with bfloat16 factors, 20M: 1027 and 1088).
+#ifndef AMPED_HOT_MIN_NNZ
+#define AMPED_HOT_MIN_NNZ (int64_t(32) << 20)
+#endif
+constexpr int64_t kHotMinNnz = AMPED_HOT_MIN_NNZ;
 
 // Hot-row tables: for every power of two K <= kHotMax, a direct-mapped table
 // of K slots; slot s names the row r with r % K == s that the most nonzeros

@@ -4,7 +4,7 @@
 namespace amped {
 namespace dev {
 
-KernelFn pick_grad(int nin, int lpr, bool scalar, bool buf) { return pick_any<float, 1>(nin, lpr, scalar, buf); }
+KernelFn pick_grad(int nin, Lanes v, bool buf) { return pick_any<float, 1>(nin, v, buf); }
 
 }  // namespace dev
 }  // namespace amped

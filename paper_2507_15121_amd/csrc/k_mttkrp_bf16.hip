@@ -4,9 +4,9 @@
 namespace amped {
 namespace dev {
 
-KernelFn pick_mttkrp_bf16(int nin, int lpr, bool scalar, bool buf)
+KernelFn pick_mttkrp_bf16(int nin, Lanes v, bool buf)
 {
-    return pick_any<uint16_t, 0>(nin, lpr, scalar, buf);
+    return pick_any<uint16_t, 0>(nin, v, buf);
 }
 
 }  // namespace dev

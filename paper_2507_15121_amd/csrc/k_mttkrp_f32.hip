@@ -4,7 +4,7 @@
 namespace amped {
 namespace dev {
 
-KernelFn pick_mttkrp_f32(int nin, int lpr, bool scalar, bool buf) { return pick_any<float, 0>(nin, lpr, scalar, buf); }
+KernelFn pick_mttkrp_f32(int nin, Lanes v, bool buf) { return pick_any<float, 0>(nin, v, buf); }
 
 }  // namespace dev
 }  // namespace amped

@@ -38,21 +38,19 @@ namespace dev {
 
 constexpr int kBlock = 256;  // init and permute kernels
 // MTTKRP kernel blocks: the waves of a block share only the hot-row cache,
-// so MTTKRP (which uses it) runs 512-thread blocks, one per CU beside a large
-// cache, and the residual and loss forms (whose extra own-row registers leave
-// them short of waves otherwise) 256-thread blocks without it.
+// so the MTTKRP instances that have it run 512-thread blocks, one per CU beside
+// a large cache, and the others (the residual and loss forms, whose extra
+// own-row registers leave them short of waves otherwise, and MTTKRP without the
+// cache) 256-thread blocks.
 #ifndef AMPED_BLOCK
 #define AMPED_BLOCK 512
 #endif
 #ifndef AMPED_BLOCK_OWN
 #define AMPED_BLOCK_OWN 256
 #endif
-__host__ __device__ constexpr int mttkrp_block(int kind) { return kind == 0 ? AMPED_BLOCK : AMPED_BLOCK_OWN; }
-// The residual and loss forms keep hot rows in LDS too (else MTTKRP only).
-#ifndef AMPED_HOT_OWN
-#define AMPED_HOT_OWN 0
-#endif
-__host__ __device__ constexpr bool hot_cache_kind(int kind) { return kind == 0 || AMPED_HOT_OWN != 0; }
+__host__ __device__ constexpr int mttkrp_block(bool cache) { return cache ? AMPED_BLOCK : AMPED_BLOCK_OWN; }
+// Instances with the hot-row cache: MTTKRP of the exact ranks.
+__host__ __device__ constexpr bool has_hot_cache(int kind, bool exact) { return kind == 0 && exact; }
 // Compile-time knobs, off by default (both measured slower): non-temporal
 // output-row stores, and the cache-policy bits of factor-row gathers.
 #ifndef AMPED_OUT_NT
@@ -86,7 +84,7 @@ constexpr int kMaxIn = kMaxOrder - 1;
 #define AMPED_UMAX_NIN 2   // most input modes that still get AMPED_UMAX
 #endif
 #ifndef AMPED_MIN_WAVES
-#define AMPED_MIN_WAVES 0
+#define AMPED_MIN_WAVES 2   // an instance that takes more than 256 registers runs one wave per SIMD
 #endif
 // Spread each tile's metadata loads over its batch pairs (see the tile loop).
 #ifndef AMPED_META_SPREAD
@@ -102,6 +100,7 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 struct KParams {
     const int32_t* out_idx;
@@ -158,6 +157,18 @@ template <int N, typename F>
 __device__ __forceinline__ void static_for(F&& f)
 {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// One product or sum rounded by itself (never contracted into an fma).
+__device__ __forceinline__ float mul_rounded(float a, float b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
+__device__ __forceinline__ float add_rounded(float a, float b)
+{
+#pragma clang fp contract(off)
+    return a + b;
 }
 
 template <int LPR>
@@ -272,9 +283,11 @@ __device__ __forceinline__ void store_vec(float* p, const float (&v)[RPL])
     if constexpr (RPL % 4 == 0) {
 #pragma unroll
         for (int i = 0; i < RPL; i += 4) {
-            const f32x4 x = {v[i], v[i + 1], v[i + 2], v[i + 3]};
-            if constexpr (AMPED_OUT_NT != 0) __builtin_nontemporal_store(x, reinterpret_cast<f32x4*>(p + i));
-            else *reinterpret_cast<f32x4*>(p + i) = x;
+            // rows of ranks that are no multiple of 4 are only 4-byte aligned,
+            // which 16-byte global accesses of gfx950 take
+            const f32x4_a4 x = {v[i], v[i + 1], v[i + 2], v[i + 3]};
+            if constexpr (AMPED_OUT_NT != 0) __builtin_nontemporal_store(x, reinterpret_cast<f32x4_a4*>(p + i));
+            else *reinterpret_cast<f32x4_a4*>(p + i) = x;
         }
     } else {
 #pragma unroll
@@ -440,10 +453,19 @@ struct ChunkQueue {
 // value and the row index -1, whose gather returns zeros (past the end of the
 // buffer resource, or redirected to a zero row on the 64-bit path).  Padding
 // therefore adds exact zeros to the open row and never starts a new one.
-template <int NIN, int LPR, int RPL, typename T, int KIND, bool BUF>
-__global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_kernel(const KParams p)
+//
+// EXACT: the launch's columns are LPR * RPL (or, on the column-tile path, RPL is
+// 1).  Otherwise they are any number up to that, from RPL on: lane s reads RPL
+// columns from min(s * RPL, columns - RPL), so the lanes of a group still cover
+// the row with one load each, the last ones overlapping; all loads stay inside
+// the row, a column held twice gets the same value twice, and sums over the
+// columns leave the second one out.
+template <int NIN, int LPR, int RPL, typename T, int KIND, bool BUF, bool EXACT>
+__global__ void __launch_bounds__(mttkrp_block(has_hot_cache(KIND, EXACT))) AMPED_OCCUPANCY
+mttkrp_kernel(const KParams p)
 {
-    constexpr int kMttkrpBlock = mttkrp_block(KIND);
+    constexpr bool HOT = has_hot_cache(KIND, EXACT) && RPL > 1;
+    constexpr int kMttkrpBlock = mttkrp_block(has_hot_cache(KIND, EXACT));
     constexpr int kWaves = kMttkrpBlock / 64;
     constexpr int G = 64 / LPR;
     constexpr int RT = LPR * RPL;
@@ -468,6 +490,7 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
     static_assert(NB % 2 == 0, "batches per tile must be even");
     static_assert(TS % 4 == 0 && (U == 1 || U == 2 || U % 4 == 0), "ring rows must be vector aligned");
     static_assert(!BUF || VEC, "buffer addressing is for the vector path");
+    static_assert(EXACT || (VEC && BUF), "other ranks take the vector path with buffer addressing");
 
     __shared__ int s_key[kWaves][2 * G];
     __shared__ int s_ext[kWaves][2 * G];
@@ -479,8 +502,9 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
     const int g = lane / LPR;
     const int s = lane % LPR;
     const bool lane_on = VEC || (s * RPL < p.ncols);
-    const int c = p.col0 + (lane_on ? s * RPL : 0);
-    const int64_t ld = VEC ? (int64_t)RT : p.ld;
+    const int c = p.col0 + (EXACT ? (lane_on ? s * RPL : 0) : min(s * RPL, p.ncols - RPL));
+    const int64_t ld = VEC && EXACT ? (int64_t)RT : p.ld;
+    const int over = EXACT ? 0 : p.col0 + s * RPL - c;   // leading columns that an earlier lane holds
     const uint64_t rb = (uint64_t)ld * sizeof(T);
     const uint64_t rb_own = (uint64_t)ld * sizeof(float);
     const float oscale = GRAD ? p.scale : 1.0f;
@@ -507,12 +531,12 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
     // entries that name a cached row are rewritten to -2 - slot when parked.
     extern __shared__ __align__(16) char s_dyn[];
     constexpr int RB = RT * (int)sizeof(T);  // row bytes on the vector path
-    const int K = (VEC && hot_cache_kind(KIND)) ? p.hot_k : 0;
+    const int K = HOT ? p.hot_k : 0;
     const int* const htag = reinterpret_cast<const int*>(s_dyn + hot_tag_offset());
     const uint32_t hrow = (uint32_t)hot_row_offset(NIN, K);  // byte offset of the cached rows
-    {
+    if constexpr (HOT) {
         if (threadIdx.x < 4) reinterpret_cast<int*>(s_dyn)[threadIdx.x] = 0;
-        if constexpr (VEC && hot_cache_kind(KIND)) {
+        {
             if (K > 0) {
                 int* tag = reinterpret_cast<int*>(s_dyn + hot_tag_offset());
 #pragma unroll
@@ -550,12 +574,15 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
     }
     // one factor-row gather: row >= 0 from memory, -1 (padding) zeros, <= -2
     // cache slot -2 - row from LDS (its memory read then returns zeros: past
-    // the buffer's end, or the zero row on the 64-bit path)
+    // the buffer's end, or the zero row on the 64-bit path).  Without EXACT the
+    // ring holds byte offsets (row * row bytes, multiplied once when parked).
+    const int pad = EXACT ? -1 : -(int)rb;
     auto gather = [&](int w, int ix) -> typename RowT::Raw {
         typename RowT::Raw r;
-        if constexpr (BUF) r = RowT::load_buf(rsrc[w], (uint32_t)max(ix, -1) * (uint32_t)rb + cb);
+        if constexpr (!EXACT) r = RowT::load_buf(rsrc[w], (uint32_t)ix + cb);
+        else if constexpr (BUF) r = RowT::load_buf(rsrc[w], (uint32_t)max(ix, -1) * (uint32_t)rb + cb);
         else r = RowT::load_ptr(ix < 0 ? zrow : lbase[w] + (uint64_t)(uint32_t)ix * rb);
-        if constexpr (VEC && hot_cache_kind(KIND)) {
+        if constexpr (HOT) {
             constexpr uint32_t LB = RPL * sizeof(T);   // bytes per lane
             const uint32_t la = ix <= -2 ? hrow + (uint32_t)(w * K + (-2 - ix)) * RB + (uint32_t)s * LB : 0u;
             r = RowT::merge_lds(r, s_dyn + la);
@@ -695,13 +722,17 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
                 const int rel = t * TS + kq * 4 * LPR + 4 * s;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const bool pad = rel + e >= len;
-                    vm[kq][0][e] = pad ? last_key : vm[kq][0][e];
+                    const bool past = rel + e >= len;
+                    vm[kq][0][e] = past ? last_key : vm[kq][0][e];
 #pragma unroll
-                    for (int w = 0; w < NIN; ++w) vm[kq][1 + w][e] = pad ? -1 : vm[kq][1 + w][e];
-                    vm[kq][NF - 1][e] = pad ? 0 : vm[kq][NF - 1][e];
+                    for (int w = 0; w < NIN; ++w) {
+                        int ix = vm[kq][1 + w][e];
+                        if constexpr (!EXACT) ix = (int)((uint32_t)ix * (uint32_t)rb);
+                        vm[kq][1 + w][e] = past ? pad : ix;
+                    }
+                    vm[kq][NF - 1][e] = past ? 0 : vm[kq][NF - 1][e];
                 }
-                if constexpr (VEC && hot_cache_kind(KIND)) {
+                if constexpr (HOT) {
                     if (K > 0) {
                         // rows held in the LDS cache become -2 - slot (tags
                         // are rows or -2, so padding -1 never matches)
@@ -751,7 +782,7 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
                     // is skipped altogether (a wave-uniform branch, so the
                     // address unit does no work for it)
                     const bool same = j0 + ju > 0 && kk[ju] == (ju == 0 ? kprev : kk[ju > 0 ? ju - 1 : 0]);
-                    const bool need = !(ix[0][ju] == -1 || same);   // -1: padding
+                    const bool need = !(ix[0][ju] == pad || same);
                     if (__builtin_amdgcn_ballot_w64(need) != 0) own[ju] = gather_own(need ? kk[ju] : -1);
                     else own[ju] = typename OwnRow::Raw{};
                 }
@@ -803,8 +834,21 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
                     for (int i = 0; i < RPL; ++i) cur_own[i] = fresh ? ow[i] : cur_own[i];
                     own_key = key[ju];
                     float part = 0.f;
+                    if constexpr (EXACT) {
 #pragma unroll
-                    for (int i = 0; i < RPL; ++i) part = fmaf(prod[i], cur_own[i], part);
+                        for (int i = 0; i < RPL; ++i) part = fmaf(prod[i], cur_own[i], part);
+                    } else {
+                        // the columns' tree of the column-tile path: rounded
+                        // products, neighbours added first
+                        float term[RPL];
+#pragma unroll
+                        for (int i = 0; i < RPL; ++i) term[i] = i < over ? 0.f : mul_rounded(prod[i], cur_own[i]);
+#pragma unroll
+                        for (int m = 1; m < RPL; m <<= 1)
+#pragma unroll
+                            for (int i = 0; i < RPL; i += 2 * m) term[i] = add_rounded(term[i], term[i + m]);
+                        part = term[0];
+                    }
                     if constexpr (!VEC) part = lane_on ? part : 0.f;
                     coef = val - group_sum<LPR>(part);
                 }
@@ -908,19 +952,35 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
             // slots' keys sit in lane registers
             constexpr int CL = (RT + 63) / 64;
             constexpr bool FULL = RT >= 64;
+            static_assert(EXACT || VEC, "");
             const int kq = lane < 2 * G ? s_key[wv][lane] : -1;
             const int eq = lane < 2 * G ? s_ext[wv][lane] : 0;
-            const bool col_on = (FULL || lane < RT) && (VEC || lane < p.ncols);
-            const int col = FULL || lane < RT ? lane : 0;
+            // where column `lane + 64 i` sits in a slot (the last lanes' columns
+            // overlap), and whether the launch has it
+            bool col_on[CL];
+            int at[CL];
+#pragma unroll
+            for (int i = 0; i < CL; ++i) {
+                const int cc = lane + 64 * i;
+                if constexpr (EXACT) {
+                    col_on[i] = (FULL || cc < RT) && (VEC || cc < p.ncols);
+                    at[i] = FULL || cc < RT ? cc : 0;
+                } else {
+                    const int full = (p.ncols / RPL) * RPL;   // columns that only their own lane holds
+                    col_on[i] = cc < p.ncols;
+                    at[i] = !col_on[i] ? 0 : cc < full ? cc : cc + full + RPL - p.ncols;
+                }
+            }
             int cur = -1, cur_ext = 0;
             float cacc[CL];
 #pragma unroll
             for (int i = 0; i < CL; ++i) cacc[i] = 0.f;
             auto emit = [&]() {
-                if (cur < 0 || !col_on) return;
-                float* o = p.out + (int64_t)cur * ld + p.col0 + col;
+                if (cur < 0) return;
+                float* o = p.out + (int64_t)cur * ld + p.col0 + lane;
 #pragma unroll
                 for (int i = 0; i < CL; ++i) {
+                    if (!col_on[i]) continue;
                     const float v = cacc[i] * oscale;
                     if (cur_ext) atomicAdd(o + 64 * i, v);
                     else o[64 * i] = v;
@@ -929,17 +989,17 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
             for (uint64_t left = __builtin_amdgcn_ballot_w64(kq >= 0); left != 0; left &= left - 1) {
                 const int qq = __builtin_ctzll(left);
                 const int k = __builtin_amdgcn_readlane(kq, qq), e = __builtin_amdgcn_readlane(eq, qq);
-                const float* src = &s_acc[wv][qq][col];
+                const float* src = s_acc[wv][qq];
                 if (k != cur) {
                     emit();
                     cur = k;
                     cur_ext = e;
 #pragma unroll
-                    for (int i = 0; i < CL; ++i) cacc[i] = src[64 * i];
+                    for (int i = 0; i < CL; ++i) cacc[i] = src[at[i]];
                 } else {
                     cur_ext |= e;
 #pragma unroll
-                    for (int i = 0; i < CL; ++i) cacc[i] += src[64 * i];
+                    for (int i = 0; i < CL; ++i) cacc[i] += src[at[i]];
                 }
             }
             emit();
@@ -976,76 +1036,99 @@ __global__ void __launch_bounds__(mttkrp_block(KIND)) AMPED_OCCUPANCY mttkrp_ker
 
 using KernelFn = void (*)(const KParams);
 
-// Vector instances: fp32 ranks 16/32/64/128 and bf16 ranks 32/64/128 for up
-// to 4 input modes; every other case takes the scalar column-tile path.
+// Vector instances exist for up to 4 input modes; every other case takes the
+// column-tile path.
 constexpr int kMaxVecNin = 4;
 
-// Kernel pickers, one translation unit each (compiled in parallel).
-KernelFn pick_mttkrp_f32(int nin, int lpr, bool scalar, bool buf);
-KernelFn pick_mttkrp_bf16(int nin, int lpr, bool scalar, bool buf);
-KernelFn pick_grad(int nin, int lpr, bool scalar, bool buf);
-KernelFn pick_loss(int nin, int lpr, bool scalar, bool buf);
-KernelFn pick_grad_loss(int nin, int lpr, bool scalar, bool buf);
+// How the columns of a launch are spread over a lane group: lpr lanes of rpl
+// columns (lpr = 0: the column-tile path), exactly or with overlap.
+struct Lanes {
+    int lpr = 0, rpl = 1;
+    bool exact = true;
+};
 
-// The instance each picker returns: lpr counts 16-byte lanes per row (the
-// vector path), scalar selects the column-tile path.  bfloat16 rows of up to
-// 64 bytes (rank <= 32) use 8 bytes per lane, so a wave still covers 8 rows
-// per gather at rank 32 (16-byte lanes would make 16 narrow groups), except
-// 64-byte rows with three or more gathered factors (below).
-#ifndef AMPED_BF16_NARROW
-#define AMPED_BF16_NARROW 1
-#endif
-template <int NIN, typename T, int KIND, bool BUF>
-KernelFn pick_vec(int lpr)
+// Kernel pickers, one translation unit each (compiled in parallel).
+KernelFn pick_mttkrp_f32(int nin, Lanes v, bool buf);
+KernelFn pick_mttkrp_bf16(int nin, Lanes v, bool buf);
+KernelFn pick_grad(int nin, Lanes v, bool buf);
+KernelFn pick_loss(int nin, Lanes v, bool buf);
+KernelFn pick_grad_loss(int nin, Lanes v, bool buf);
+
+template <int NIN, int LPR, int RPL, typename T, int KIND>
+KernelFn pick_buf(bool exact, bool buf)
 {
-    constexpr int RPL = 16 / sizeof(T);
-    constexpr bool narrow = AMPED_BF16_NARROW && std::is_same<T, uint16_t>::value;
+    // 2 lanes and 64 lanes, and bfloat16 with 32, have no exact instance: their
+    // ranks take the other one, which the residual forms have up to rank 64
+    constexpr bool kExact = LPR >= 4 && LPR <= (sizeof(T) == 4 ? 32 : 16);
+    constexpr bool kAny = KIND == 0 || LPR <= 16;
+    if constexpr (kExact) {
+        if (exact) return buf ? mttkrp_kernel<NIN, LPR, RPL, T, KIND, true, true>
+                              : mttkrp_kernel<NIN, LPR, RPL, T, KIND, false, true>;
+    }
+    if constexpr (kAny) {
+        if (buf) return mttkrp_kernel<NIN, LPR, RPL, T, KIND, true, false>;
+    }
+    return nullptr;
+}
+
+template <int NIN, typename T, int KIND>
+KernelFn pick_vec(Lanes v, bool buf)
+{
     if constexpr (NIN > kMaxVecNin) {
         return nullptr;
     } else {
-        if constexpr (narrow) {
-            // with three or more gathered factors, 64-byte rows take 16-byte
-            // lanes again (16 rows per gather instruction): the order-4
-            // tensors measured faster so, in every mode, the order-3 ones
-            // slower
-            if (lpr == 2 || (lpr == 4 && NIN <= 2)) {
-                switch (lpr) {
-                case 2: return mttkrp_kernel<NIN, 4, 4, T, KIND, BUF>;
-                case 4: return mttkrp_kernel<NIN, 8, 4, T, KIND, BUF>;
-                default: return nullptr;
-                }
+        if (v.rpl == 4) {
+            switch (v.lpr) {
+            case 2: return pick_buf<NIN, 2, 4, T, KIND>(v.exact, buf);
+            case 4: return pick_buf<NIN, 4, 4, T, KIND>(v.exact, buf);
+            case 8:
+                if constexpr (std::is_same<T, float>::value || NIN <= 2)
+                    return pick_buf<NIN, 8, 4, T, KIND>(v.exact, buf);
+                break;
+            case 16:
+                if constexpr (std::is_same<T, float>::value) return pick_buf<NIN, 16, 4, T, KIND>(v.exact, buf);
+                break;
+            case 32:
+                if constexpr (std::is_same<T, float>::value) return pick_buf<NIN, 32, 4, T, KIND>(v.exact, buf);
+                break;
+            case 64:
+                if constexpr (std::is_same<T, float>::value) return pick_buf<NIN, 64, 4, T, KIND>(v.exact, buf);
+                break;
+            default: break;
+            }
+        } else if constexpr (std::is_same<T, uint16_t>::value) {
+            switch (v.lpr) {
+            case 4:
+                if constexpr (NIN > 2) return pick_buf<NIN, 4, 8, T, KIND>(v.exact, buf);
+                break;
+            case 8: return pick_buf<NIN, 8, 8, T, KIND>(v.exact, buf);
+            case 16: return pick_buf<NIN, 16, 8, T, KIND>(v.exact, buf);
+            case 32: return pick_buf<NIN, 32, 8, T, KIND>(v.exact, buf);
+            default: break;
             }
         }
-        switch (lpr) {
-        case 4: return mttkrp_kernel<NIN, 4, RPL, T, KIND, BUF>;
-        case 8: return mttkrp_kernel<NIN, 8, RPL, T, KIND, BUF>;
-        case 16: return mttkrp_kernel<NIN, 16, RPL, T, KIND, BUF>;
-        case 32:
-            if constexpr (std::is_same<T, float>::value) return mttkrp_kernel<NIN, 32, RPL, T, KIND, BUF>;
-            else return nullptr;
-        default: return nullptr;
-        }
+        return nullptr;
     }
 }
 
 template <int NIN, typename T, int KIND>
-KernelFn pick_nin(int lpr, bool scalar, bool buf)
+KernelFn pick_nin(Lanes v, bool buf)
 {
-    if (scalar) return mttkrp_kernel<NIN, 64, 1, T, KIND, false>;
-    return buf ? pick_vec<NIN, T, KIND, true>(lpr) : pick_vec<NIN, T, KIND, false>(lpr);
+    if (v.lpr == 0) return mttkrp_kernel<NIN, 64, 1, T, KIND, false, true>;
+    return pick_vec<NIN, T, KIND>(v, buf);
 }
 
 template <typename T, int KIND>
-KernelFn pick_any(int nin, int lpr, bool scalar, bool buf)
+KernelFn pick_any(int nin, Lanes v, bool buf)
 {
     switch (nin) {
-    case 1: return pick_nin<1, T, KIND>(lpr, scalar, buf);
-    case 2: return pick_nin<2, T, KIND>(lpr, scalar, buf);
-    case 3: return pick_nin<3, T, KIND>(lpr, scalar, buf);
-    case 4: return pick_nin<4, T, KIND>(lpr, scalar, buf);
-    case 5: return pick_nin<5, T, KIND>(lpr, scalar, buf);
-    case 6: return pick_nin<6, T, KIND>(lpr, scalar, buf);
-    case 7: return pick_nin<7, T, KIND>(lpr, scalar, buf);
+    case 1: return pick_nin<1, T, KIND>(v, buf);
+    case 2: return pick_nin<2, T, KIND>(v, buf);
+    case 3: return pick_nin<3, T, KIND>(v, buf);
+    case 4: return pick_nin<4, T, KIND>(v, buf);
+    case 5: return pick_nin<5, T, KIND>(v, buf);
+    case 6: return pick_nin<6, T, KIND>(v, buf);
+    case 7: return pick_nin<7, T, KIND>(v, buf);
     default: return nullptr;
     }
 }

@@ -86,15 +86,32 @@ bool fits_buffer(int64_t rows, int rank, int elem_bytes)
     return (uint64_t)(rows + 1) * (uint64_t)rank * (uint64_t)elem_bytes <= (1ull << 32);
 }
 
-// Vector path: one 16-byte load per lane covers the row (rank * size / 16
-// lanes).  Returns 0 when the rank needs the scalar column-tile path.
-int vector_lpr(int rank, int elem_bytes)
+// How a launch spreads `cols` columns over a lane group.  One load per lane
+// covers the row, so the loads of a nonzero take cols * size / 16 lanes of the
+// address unit's time instead of a whole wave's (the column-tile path walks one
+// nonzero per wave step: 597 us for all modes of 3M nonzeros at rank 20, against
+// 167 us here; their gradients 1513 and 186 us).  fp32 rows: 4 columns (16 bytes) per lane.
+//  bfloat16 rows of up to 32 columns: 4 columns (8 bytes), so that a wave still
+// covers 8 rows per gather at rank 32, except above 16 columns with three or more
+// gathered factors, where 16-byte lanes (16 rows per gather instruction) measured
+// faster, in every mode of the order-4 tensors, and slower on the order-3 ones;
+// wider ones 8 columns.  Rows start on 4 bytes, so odd bfloat16 ranks take the
+// column-tile path, as do fewer columns than a lane reads.
+Lanes choose_lanes(int cols, FactorType ft, int nin)
 {
-    if ((rank * elem_bytes) % 16) return 0;
-    const int lpr = rank * elem_bytes / 16;
-    if (lpr < 2 || lpr > 64 || (lpr & (lpr - 1))) return 0;
-    return lpr;
+    Lanes v;
+    const bool f32 = ft == FactorType::F32;
+    v.rpl = f32 || cols <= 16 || (cols <= 32 && nin <= 2) ? 4 : 8;
+    if (cols < v.rpl || (!f32 && cols % 2)) return Lanes{};
+    const int need = (cols + v.rpl - 1) / v.rpl;
+    v.lpr = v.rpl == 4 ? 2 : 4;
+    while (v.lpr < need) v.lpr *= 2;
+    v.exact = cols == v.lpr * v.rpl && v.lpr >= 4 && v.lpr <= (f32 ? 32 : 16);
+    return v;
 }
+
+// Most columns of one launch on the vector path.
+constexpr int kMaxVecCols = 256;
 
 // Launch shape of an MTTKRP-kernel instance on the current device: the
 // hot-row cache slots K (largest power of two whose LDS, with the kernel's
@@ -251,11 +268,11 @@ __global__ void __launch_bounds__(kBlock) permute_kernel(uint32_t* dst, const ui
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride) dst[p] = src[perm[p]];
 }
 
-KernelFn pick_mttkrp(int nin, FactorType ft, Kind kind, int lpr, bool scalar, bool buf)
+KernelFn pick_mttkrp(int nin, FactorType ft, Kind kind, Lanes v, bool buf)
 {
-    if (kind == Kind::ResidualGrad) return ft == FactorType::F32 ? pick_grad(nin, lpr, scalar, buf) : nullptr;
-    if (kind == Kind::ResidualGradLoss) return ft == FactorType::F32 ? pick_grad_loss(nin, lpr, scalar, buf) : nullptr;
-    return ft == FactorType::F32 ? pick_mttkrp_f32(nin, lpr, scalar, buf) : pick_mttkrp_bf16(nin, lpr, scalar, buf);
+    if (kind == Kind::ResidualGrad) return ft == FactorType::F32 ? pick_grad(nin, v, buf) : nullptr;
+    if (kind == Kind::ResidualGradLoss) return ft == FactorType::F32 ? pick_grad_loss(nin, v, buf) : nullptr;
+    return ft == FactorType::F32 ? pick_mttkrp_f32(nin, v, buf) : pick_mttkrp_bf16(nin, v, buf);
 }
 
 }  // namespace dev
@@ -275,7 +292,6 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
 {
     const ModeDev& m = *a.m;
     const int eb = (a.ftype == FactorType::F32) ? 4 : 2;
-    const int lpr = vector_lpr(a.rank, eb);
     // buffer addressing when every factor the kernel reads fits in 32-bit
     // offsets with one row to spare
     bool buf = AMPED_BUFFER_LOADS != 0;
@@ -283,12 +299,24 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
         if (!fits_buffer(a.in_rows[w], a.rank, eb)) buf = false;
     const bool grad = a.kind != Kind::Mttkrp;   // the residual forms read the output mode's factor
     if (grad && !fits_buffer(m.rows, a.rank, 4)) buf = false;
-    KernelFn fn = lpr ? pick_mttkrp(a.nin, a.ftype, a.kind, lpr, false, buf) : nullptr;
+    // ranks above one launch's columns: equal launches, of whole 16-byte pieces
+    const int parts = (a.rank + kMaxVecCols - 1) / kMaxVecCols;
+    int tile = parts == 1 ? a.rank : ((a.rank + parts - 1) / parts + 3) & ~3;
+    Lanes v = choose_lanes(tile, a.ftype, a.nin);
+    if (tile != a.rank) v.exact = false;
+    // An exact rank's instance with the hot-row cache is used where the cache
+    // is; the residual forms (no cache) always take the exact one.
+    if (!grad && buf && m.nnz < kHotMinNnz) v.exact = false;
+    KernelFn fn = v.lpr ? pick_mttkrp(a.nin, a.ftype, a.kind, v, buf) : nullptr;
     const bool scalar = (fn == nullptr);
     // the fused residual form needs the whole row in one launch (rank <= 64
     // on the scalar path)
     if (scalar && grad && a.rank > 64) return hipErrorNotSupported;
-    if (scalar) fn = pick_mttkrp(a.nin, a.ftype, a.kind, 64, true, false);
+    if (scalar) {
+        v = Lanes{};
+        tile = std::min(64, a.rank);
+        fn = pick_mttkrp(a.nin, a.ftype, a.kind, v, false);
+    }
     if (!fn) return hipErrorNotSupported;
     KParams k = base_params(m);
     for (int w = 0; w < a.nin; ++w) {
@@ -301,11 +329,11 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
     k.loss = a.kind == Kind::ResidualGradLoss ? a.loss : nullptr;
     k.ld = a.rank;
     k.scale = a.scale;
-    const int block = mttkrp_block(a.kind == Kind::Mttkrp ? 0 : 1);
-    const Shape sh = launch_shape(fn, block, a.nin, a.rank * eb, !scalar && m.nnz >= kHotMinNnz && hot_cache_kind(a.kind == Kind::Mttkrp ? 0 : 1));
+    const bool cache = !grad && v.exact;
+    const int block = mttkrp_block(cache);
+    const Shape sh = launch_shape(fn, block, a.nin, v.lpr * v.rpl * eb, cache && !scalar && m.nnz >= kHotMinNnz);
     if (sh.grid <= 0) return hipErrorInvalidDevice;
     set_hot(k, sh.hot_k, a.in_hot, a.nin);
-    const int tile = scalar ? 64 : a.rank;
     for (int col0 = 0; col0 < a.rank; col0 += tile) {
         const int ncols = std::min(tile, a.rank - col0);
         // the loss (one launch: the residual forms never tile columns) is reset
@@ -343,14 +371,14 @@ hipError_t queue_stats_copy(unsigned long long* host, int64_t max_records, int64
 hipError_t launch_cp_loss(const LossArgs& a)
 {
     const ModeDev& m = *a.m;
-    const int lpr = vector_lpr(a.rank, 4);
     bool buf = AMPED_BUFFER_LOADS != 0 && fits_buffer(m.rows, a.rank, 4);
     for (int w = 0; w < a.order - 1; ++w)
         if (!fits_buffer(a.in_rows[w], a.rank, 4)) buf = false;
-    KernelFn fn = lpr ? pick_loss(a.order - 1, lpr, false, buf) : nullptr;
+    const Lanes v = choose_lanes(a.rank, FactorType::F32, a.order - 1);
+    KernelFn fn = v.lpr ? pick_loss(a.order - 1, v, buf) : nullptr;
     const bool scalar = (fn == nullptr);
     if (scalar && a.rank > 64) return hipErrorNotSupported;
-    if (scalar) fn = pick_loss(a.order - 1, 64, true, false);
+    if (scalar) fn = pick_loss(a.order - 1, Lanes{}, false);
     if (!fn) return hipErrorNotSupported;
     KParams k = base_params(m);
     for (int w = 0; w < a.order - 1; ++w) {
@@ -366,8 +394,8 @@ hipError_t launch_cp_loss(const LossArgs& a)
     hipError_t e = launch_init(m, nullptr, 0, 0, 0, a.accumulate ? nullptr : a.loss, a.stream);
     if (e != hipSuccess) return e;
     if (m.n_chunks == 0) return hipSuccess;
-    const int block = mttkrp_block(2);
-    const Shape sh = launch_shape(fn, block, a.order - 1, a.rank * 4, !scalar && m.nnz >= kHotMinNnz && hot_cache_kind(2));
+    const int block = mttkrp_block(false);
+    const Shape sh = launch_shape(fn, block, a.order - 1, a.rank * 4, false);
     if (sh.grid <= 0) return hipErrorInvalidDevice;
     set_hot(k, sh.hot_k, a.in_hot, a.order - 1);
 #if AMPED_QUEUE_STATS

@@ -62,18 +62,74 @@ def test_library_sized_units(nnz, rank):
 
 
 def test_rows_kept_in_lds():
-    """9M nonzeros: the launch copies the most-used rows to LDS first (a share
-    of the factors' rows, so that cached and other rows mix)."""
-    dims, rank = (3000, 2000, 900), 32
+    """Enough nonzeros (2^25 and a few) that the launch copies the most-used rows
+    to LDS first; they mix with other rows."""
+    dims, rank = (3000, 2000, 900), 16
     rng = np.random.default_rng(9)
-    nnz = 9_000_000
-    idx = np.stack([np.minimum((d * rng.random(nnz) ** 4).astype(np.int32), d - 1) for d in dims])
+    nnz = (1 << 25) + 77
+    idx = np.stack([np.minimum((d * rng.random(nnz, dtype=np.float32) ** 4).astype(np.int32), d - 1) for d in dims])
     val = rng.integers(0, 2, nnz).astype(np.float32)
     factors = [rng.integers(-1, 2, (d, rank)).astype(np.float32) for d in dims]
     t = api.Tensor(idx, val, dims)
+    dfac, bfac = dev_factors(factors), dev_factors(factors, torch.bfloat16)
+    ref = oracle_mttkrp(idx, val, dims, factors, 1)
+    assert np.abs(ref).max() < 2 ** 24
+    np.testing.assert_array_equal(hip_mttkrp(t, 1, dfac), ref.astype(np.float32))
+    np.testing.assert_array_equal(hip_mttkrp(t, 1, bfac, bf16=True), ref.astype(np.float32))
+    t.close()
+
+
+@pytest.mark.parametrize("order", [2, 3, 4, 5])
+@pytest.mark.parametrize("rank", [1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 12, 15, 17, 20, 25, 31, 33, 48, 63, 65, 100, 127, 129, 200, 255, 256,
+                                  257, 300, 513])
+def test_any_rank(rank, order):
+    """Ranks around every lane count of a row and every lane width: the last
+    lanes' columns overlap, the last launch of a wide rank is narrower.  fp32 and
+    bfloat16 factors (small integers are exact in both), and the residual forms
+    where they are taken (ranks up to 64)."""
+    rng = np.random.default_rng(rank * 10 + order)
+    dims = (37, 30, 23, 11, 9)[:order]
+    nnz = 3000 if rank <= 64 else 700
+    idx = np.stack([rng.integers(0, d, nnz) for d in dims]).astype(np.int32)
+    idx[0, idx[0] == 5] = 6          # an untouched row
+    val = rng.integers(1, 4, nnz).astype(np.float32)
+    factors = [rng.integers(-1, 2, (d, rank)).astype(np.float32) for d in dims]
+    t = api.Tensor(idx, val, dims)
     dfac = dev_factors(factors)
-    for d in range(3):
+    bfac = dev_factors(factors, torch.bfloat16)
+    for d in range(order):
         ref = oracle_mttkrp(idx, val, dims, factors, d)
         assert np.abs(ref).max() < 2 ** 24
         np.testing.assert_array_equal(hip_mttkrp(t, d, dfac), ref.astype(np.float32))
+        np.testing.assert_array_equal(hip_mttkrp(t, d, bfac, bf16=True), ref.astype(np.float32))
+        if rank <= 64:
+            grad = torch.full((dims[d], rank), float("nan"), device="cuda")
+            loss, _ = api.cp_loss_grad(t, d, dfac, -2.0, out=grad)
+            gref = oracle.cp_grad(idx, val, dims, factors, d)
+            assert np.abs(gref).max() < 2 ** 24
+            np.testing.assert_array_equal(grad.cpu().numpy(), gref.astype(np.float32))
+            assert float(loss) == oracle.cp_loss(idx, val, [f.astype(np.float64) for f in factors])[0]
+    if rank <= 64:
+        assert float(api.cp_loss(t, dfac)) == oracle.cp_loss(idx, val, [f.astype(np.float64) for f in factors])[0]
+    t.close()
+
+
+def test_infinities_stay_in_their_columns():
+    """A rank whose last lanes overlap: an infinite factor value changes the
+    columns and residuals that hold it and no other (a column that two lanes
+    hold enters a sum once)."""
+    dims, rank, nnz = (20, 15, 10), 22, 400
+    rng = np.random.default_rng(22)
+    idx = np.stack([rng.integers(0, d, nnz) for d in dims]).astype(np.int32)
+    val = rng.random(nnz).astype(np.float32) + 0.5
+    factors = [rng.random((d, rank)).astype(np.float32) + 0.5 for d in dims]
+    factors[1][3, 19] = np.inf
+    t = api.Tensor(idx, val, dims)
+    dfac = dev_factors(factors)
+    with np.errstate(invalid="ignore"):
+        ref = oracle_mttkrp(idx, val, dims, factors, 0)
+    got = hip_mttkrp(t, 0, dfac)
+    np.testing.assert_array_equal(np.isinf(got), np.isinf(ref))
+    assert not np.isnan(got).any()
+    assert np.isinf(float(api.cp_loss(t, dfac)))   # the squared residual of a hit entry, not NaN
     t.close()

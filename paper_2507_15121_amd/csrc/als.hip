@@ -30,6 +30,8 @@
 #include <algorithm>
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
+#include <utility>
 
 #include "internal.h"
 
@@ -40,14 +42,16 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kGramMaxPairs = 4;   // 32x32 output tiles per wave (4 x 16 accumulators)
 
-// x[t] for a run-time t < T, without indexing a register array
-template <int T>
-__device__ __forceinline__ float pick(const float (&x)[T], int t)
+// f(j) for j = 0 .. N - 1 as compile-time constants
+template <typename F, int... Is>
+__device__ __forceinline__ void for_pairs_impl(F&& f, std::integer_sequence<int, Is...>)
 {
-    float r = x[0];
-#pragma unroll
-    for (int j = 1; j < T; ++j) r = (t == j) ? x[j] : r;
-    return r;
+    (f(std::integral_constant<int, Is>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void for_pairs(F&& f)
+{
+    for_pairs_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 // Upper-triangle tile pair p of T x T tiles (G is symmetric): row-major over
@@ -71,28 +75,42 @@ __host__ __device__ constexpr int tri_tn(int T, int p)
     return tm + p;
 }
 
+// The Gram matrices of one launch: matrix m's slabs are blocks [begin, next
+// matrix's begin) of gram_partial, its partials are stored there too.
+constexpr int kGramMany = kMaxOrder;
+struct GramSet {
+    const float* A[kGramMany];
+    int64_t rows[kGramMany], slab_rows[kGramMany];
+    int64_t begin[kGramMany + 1];
+    double* G[kGramMany];
+    int n;
+};
+
 // T = number of 32-column tiles (R <= 32 T).  Grid (slabs, tile groups);
 // four waves per block each take a quarter of the slab's rows and keep up to
 // kGramMaxPairs 32x32 tiles in MFMA accumulators, with kGramBatch row pairs of
 // loads in flight before their MFMAs.  The four waves' tiles are then summed
 // through LDS in wave order (deterministic) into the slab's partial.
 constexpr int kGramBatch = 8;
-template <int T>
-__global__ void __launch_bounds__(256) gram_partial(const float* A, int64_t rows, int R, int64_t slab_rows,
-                                                    float* partial)
+template <int T, int GROUP>
+__device__ __forceinline__ void gram_slab(const GramSet& set, int R, float* partial,
+                                          float (&s_t)[4][T * (T + 1) / 2 < kGramMaxPairs ? T * (T + 1) / 2 : kGramMaxPairs][32 * 32])
 {
+    int mat = 0;
+    while (mat + 1 < set.n && (int64_t)blockIdx.x >= set.begin[mat + 1]) ++mat;
+    const float* const A = set.A[mat];
+    const int64_t rows = set.rows[mat], slab_rows = set.slab_rows[mat];
     constexpr int NP = T * (T + 1) / 2;                               // upper-triangle tiles
-    constexpr int NPB = NP < kGramMaxPairs ? NP : kGramMaxPairs;   // tiles per block
+    constexpr int P0 = GROUP * kGramMaxPairs;                         // this group's tiles: P0 .. P0 + NPB
+    constexpr int NPB = NP - P0 < kGramMaxPairs ? NP - P0 : kGramMaxPairs;
+    constexpr int T0 = tri_tm(T, P0);                                 // first column tile that they need
     constexpr int B = T <= 2 ? kGramBatch : kGramBatch / 2;          // row pairs per load batch
-    __shared__ float s_t[4][NPB][32 * 32];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t b0 = (int64_t)blockIdx.x * slab_rows;
-    const int64_t b1 = std::min<int64_t>(b0 + slab_rows, rows);
+    const int64_t b0 = ((int64_t)blockIdx.x - set.begin[mat]) * slab_rows;
+    const int64_t b1 = std::max(b0, std::min<int64_t>(b0 + slab_rows, rows));
     const int64_t q = ((slab_rows + 3) / 4 + 1) & ~(int64_t)1;   // even rows per wave, 4 q >= slab_rows
     const int64_t r0 = std::min<int64_t>(b0 + wave * q, b1);
     const int64_t r1 = std::min<int64_t>(r0 + q, b1);
-    const int p0 = blockIdx.y * kGramMaxPairs;
-    const int np = std::min(kGramMaxPairs, NP - p0);
     f32x16 acc[NPB];
 #pragma unroll
     for (int j = 0; j < NPB; ++j)
@@ -108,7 +126,7 @@ __global__ void __launch_bounds__(256) gram_partial(const float* A, int64_t rows
             const int64_t row = i + 2 * u + kk;
             const bool rv = row < r1;
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
+            for (int t = T0; t < T; ++t) {
                 const int c = t * 32 + col;
                 x[u][t] = (rv && c < R) ? A[row * R + c] : 0.f;
             }
@@ -117,14 +135,10 @@ __global__ void __launch_bounds__(256) gram_partial(const float* A, int64_t rows
     auto fma_batch = [&](const float (&x)[B][T]) {
 #pragma unroll
         for (int u = 0; u < B; ++u)
-#pragma unroll
-            for (int j = 0; j < NPB; ++j) {
-                if (j < np) {
-                    const int p = p0 + j;
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(pick<T>(x[u], tri_tm(T, p)),
-                                                                  pick<T>(x[u], tri_tn(T, p)), acc[j], 0, 0, 0);
-                }
-            }
+            for_pairs<NPB>([&](auto j) {
+                constexpr int p = P0 + decltype(j)::value;
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u][tri_tm(T, p)], x[u][tri_tn(T, p)], acc[j], 0, 0, 0);
+            });
     };
     float xa[B][T], xb[B][T];
     if (r0 < r1) load(xa, r0);
@@ -137,52 +151,73 @@ __global__ void __launch_bounds__(256) gram_partial(const float* A, int64_t rows
     // lane l holds output column l%32; value v sits in row 8(v/4) + 4(l/32) + v%4
 #pragma unroll
     for (int j = 0; j < NPB; ++j) {
-        if (j >= np) continue;
 #pragma unroll
         for (int v = 0; v < 16; ++v) s_t[wave][j][(8 * (v >> 2) + 4 * kk + (v & 3)) * 32 + col] = acc[j][v];
     }
     __syncthreads();
     float* out = partial + (int64_t)blockIdx.x * R * R;
-    for (int e = threadIdx.x; e < np * 1024; e += 256) {
-        const int j = e >> 10, m = (e >> 5) & 31, n = e & 31;
-        const float sum = ((s_t[0][j][e & 1023] + s_t[1][j][e & 1023]) + s_t[2][j][e & 1023]) + s_t[3][j][e & 1023];
-        const int p = p0 + j;
-        const int r = tri_tm(T, p) * 32 + m, c = tri_tn(T, p) * 32 + n;
-        if (r < R && c < R) {
-            out[r * R + c] = sum;
-            out[c * R + r] = sum;   // the mirrored tile (the same entry on the diagonal tiles)
+    for_pairs<NPB>([&](auto jj) {
+        constexpr int j = decltype(jj)::value, p = P0 + j;
+        for (int e = threadIdx.x; e < 1024; e += 256) {
+            const int m = e >> 5, n = e & 31;
+            const float sum = ((s_t[0][j][e] + s_t[1][j][e]) + s_t[2][j][e]) + s_t[3][j][e];
+            const int r = tri_tm(T, p) * 32 + m, c = tri_tn(T, p) * 32 + n;
+            if (r < R && c < R) {
+                out[r * R + c] = sum;
+                out[c * R + r] = sum;   // the mirrored tile (the same entry on the diagonal tiles)
+            }
         }
+    });
+}
+
+// The tile groups of a slab differ in blockIdx.y: each has code of its own, so
+// that the tiles of a matrix instruction are fixed registers (chosen at run time,
+// 50,000 rows of rank 100 took 1570 us, now KKK us).
+template <int T>
+__global__ void __launch_bounds__(256) gram_partial(GramSet set, int R, float* partial)
+{
+    constexpr int NP = T * (T + 1) / 2;
+    __shared__ float s_t[4][NP < kGramMaxPairs ? NP : kGramMaxPairs][32 * 32];
+    if (blockIdx.y == 0) gram_slab<T, 0>(set, R, partial, s_t);
+    if constexpr (NP > kGramMaxPairs) {
+        if (blockIdx.y == 1) gram_slab<T, 1>(set, R, partial, s_t);
+    }
+    if constexpr (NP > 2 * kGramMaxPairs) {
+        if (blockIdx.y == 2) gram_slab<T, 2>(set, R, partial, s_t);
     }
 }
 
-// G[e] = sum over slabs of partial[slab][e] in fp64.  A block takes 32
-// consecutive entries; its 8 slab lanes add every 8th slab, then the 8 sums
-// are added in lane order (deterministic).
-__global__ void __launch_bounds__(256) gram_reduce(const float* partial, int64_t nslab, int R, double* G)
+// G[m][e] = sum over matrix m's slabs of partial[slab][e] in fp64.  A block takes
+// 32 consecutive entries of one matrix; its 32 slab lanes add every 32nd slab,
+// then the 32 sums are added in lane order (deterministic).
+__global__ void __launch_bounds__(1024) gram_reduce(GramSet set, int R, const float* partial)
 {
-    __shared__ double s[8][32];
+    __shared__ double s[32][33];
     const int e32 = threadIdx.x & 31, sl = threadIdx.x >> 5;
     const int e = blockIdx.x * 32 + e32;
     const int RR = R * R;
+    const int m = blockIdx.y;
+    const int64_t nslab = set.begin[m + 1] - set.begin[m];
+    const float* src = partial + set.begin[m] * RR;
     double acc = 0.0;
     if (e < RR) {
         // 8 loads in flight, added in slab order
         int64_t k = sl;
-        for (; k + 56 < nslab; k += 64) {
+        for (; k + 224 < nslab; k += 256) {
             float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = partial[(k + 8 * u) * RR + e];
+            for (int u = 0; u < 8; ++u) v[u] = src[(k + 32 * u) * RR + e];
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc += (double)v[u];
         }
-        for (; k < nslab; k += 8) acc += (double)partial[k * RR + e];
+        for (; k < nslab; k += 32) acc += (double)src[k * RR + e];
     }
     s[sl][e32] = acc;
     __syncthreads();
     if (sl == 0 && e < RR) {
         double t = 0.0;
-        for (int j = 0; j < 8; ++j) t += s[j][e32];
-        G[e] = t;
+        for (int j = 0; j < 32; ++j) t += s[j][e32];
+        set.G[m][e] = t;
     }
 }
 
@@ -194,138 +229,221 @@ __global__ void __launch_bounds__(256) gram_reduce(const float* partial, int64_t
 // fp32 error of M itself (about 1e-6 relative).
 constexpr double kSolveFp32MaxCond = 1e4;
 
-// R x R fp64 algebra of one mode update, one block of 256 threads.  Works
-// in 4 R x R doubles: LDS when they fit (dynamic, in_lds), else the global
-// scratch.  G: [N][R][R] (G[d] is replaced).
-__global__ void __launch_bounds__(256) als_small(double* G, const double* S, int N, int d, int R, double* scratch,
-                                                 double* W, int* wide, double* lambda, int last,
-                                                 const double* xnorm2, double* fit, int in_lds)
+// R x R fp64 algebra of one mode update, one block: V, V^{-1}, P = V^{-1} S
+// V^{-1}, lambda, the new G[d], W and after the last mode the fit.
+// G: [N][R][R] (G[d] is replaced); T: R x R doubles of scratch.
+//
+// Thread (ti, tj) of a TI x TI grid holds the entries (ti + TI a, tj + TI b),
+// a, b < RA, of the RP x RP matrix (RP = TI RA >= R, padded by the identity) in
+// registers, through the elimination and both products; LDS carries what other
+// threads need.  What bounds it is the chain of R pivots, so a pivot is one LDS
+// round trip and one barrier (row k, column k in two buffers), and up to rank 32
+// the block is a single wave, which needs no barrier at all.  With the matrices
+// in LDS, or above rank 64 in global memory, and three barriers per pivot it took
+// 62 us at rank 32 and 7 ms at rank 100; now KKK us and LLL us.
+template <int RA, int TI>
+__global__ void __launch_bounds__(TI * TI) als_small(double* G, const double* S, int N, int d, int R, double* T,
+                                                     double* W, int* wide, double* lambda, int last,
+                                                     const double* xnorm2, double* fit)
 {
-    extern __shared__ __align__(16) double s_small[];
-    if (in_lds) scratch = s_small;
-    const int tid = threadIdx.x;
+    constexpr int RP = RA * TI, NT = TI * TI, LD = RP + 1;
+    constexpr bool ST = RP <= 64;                           // S, then T, in LDS too
+    extern __shared__ __align__(16) double s_inv[];        // V^{-1}, row stride LD; then (ST) S and T
+    double* const s_st = s_inv + RP * LD;
+    __shared__ double s_row[2][RP], s_col[2][RP];
+    __shared__ double s_lam[RP], s_tr[RP], s_red[NT / 64];
+    double(*const s_part)[RP] = reinterpret_cast<double(*)[RP]>(s_inv);   // TI x RP, until s_inv is filled
+    const int tid = threadIdx.x, ti = tid / TI, tj = tid % TI;
     const int RR = R * R;
-    double* V = scratch;
-    double* L = scratch + RR;
-    double* Vi = scratch + 2 * RR;
-    double* T = scratch + 3 * RR;
-    for (int e = tid; e < RR; e += 256) {
-        double v = 1.0;
-        for (int w = 0; w < N; ++w)
-            if (w != d) v *= G[(int64_t)w * RR + e];
-        V[e] = v;
-        L[e] = 0.0;
+    if constexpr (ST) {
+        for (int e = tid; e < RR; e += NT) s_st[e / R * LD + e % R] = S[e];
     }
-    __syncthreads();
-    // V^{-1} by Gauss-Jordan elimination without pivoting (V is symmetric
-    // positive semi-definite): L holds the reduced V, Vi starts as I.  A pivot
-    // that is not positive (V singular, e.g. a zero factor column) is replaced
-    // by a tiny one, so that row and column of V^{-1} stay apart from the rest.
-    double vmax = 0.0;
-    for (int k = 0; k < R; ++k) vmax = fmax(vmax, fabs(V[k * R + k]));
+    auto row_of = [&](int x) { return ti + TI * x; };
+    auto col_of = [&](int x) { return tj + TI * x; };
+
+    // largest value over the block's threads
+    auto block_max = [&](double x) {
+        for (int m = 1; m < 64; m <<= 1) x = fmax(x, __shfl_xor(x, m, 64));
+        if ((tid & 63) == 0) s_red[tid >> 6] = x;
+        __syncthreads();
+        x = s_red[0];
+        for (int w = 1; w < NT / 64; ++w) x = fmax(x, s_red[w]);
+        __syncthreads();
+        return x;
+    };
+    // largest column sum of |x| over the R x R part
+    auto norm1 = [&](const double (&x)[RA][RA]) {
+#pragma unroll
+        for (int j = 0; j < RA; ++j) {
+            double sum = 0.0;
+#pragma unroll
+            for (int i = 0; i < RA; ++i) sum += row_of(i) < R ? fabs(x[i][j]) : 0.0;
+            s_part[ti][col_of(j)] = sum;
+        }
+        __syncthreads();
+        double most = 0.0;
+        for (int c = tid; c < R; c += NT) {
+            double sum = 0.0;
+            for (int i = 0; i < TI; ++i) sum += s_part[i][c];
+            most = sum > most || !(sum == sum) ? sum : most;   // a NaN stays
+        }
+        __syncthreads();
+        const bool bad = __syncthreads_or(most == most ? 0 : 1) != 0;
+        most = block_max(bad ? 0.0 : most);
+        return bad ? __longlong_as_double(0x7ff8000000000000LL) : most;
+    };
+
+    double v[RA][RA], diag = 0.0;
+#pragma unroll
+    for (int i = 0; i < RA; ++i)
+#pragma unroll
+        for (int j = 0; j < RA; ++j) {
+            const int r = row_of(i), c = col_of(j);
+            double x = r == c ? 1.0 : 0.0;
+            if (r < R && c < R) {
+                x = 1.0;
+                for (int w = 0; w < N; ++w)
+                    if (w != d) x *= G[(int64_t)w * RR + r * R + c];
+                if (r == c) diag = fmax(diag, fabs(x));
+            }
+            v[i][j] = x;
+        }
+    const double vmax = block_max(diag);
+    const double vnorm = norm1(v);
+
+    // V^{-1} in place by Gauss-Jordan elimination without pivoting (V is
+    // symmetric positive semi-definite).  A pivot that is not positive (V
+    // singular, e.g. a zero factor column) is replaced by a tiny one, so that row
+    // and column of V^{-1} stay apart from the rest.
     const double tiny = (vmax > 0.0 ? vmax : 1.0) * 1e-30;
-    __shared__ double fcol[128];
-    for (int e = tid; e < RR; e += 256) {
-        L[e] = V[e];
-        Vi[e] = (e / R == e % R) ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    for (int k = 0; k < R; ++k) {
-        // pivot row k scaled by 1/pivot; the column-k multipliers saved first
-        const double pv = L[k * R + k];
-        const double inv = 1.0 / (pv > tiny ? pv : tiny);
-        for (int i = tid; i < R; i += 256) fcol[i] = L[i * R + k];
-        __syncthreads();
-        for (int j = tid; j < R; j += 256) {
-            L[k * R + j] *= inv;
-            Vi[k * R + j] *= inv;
+#pragma unroll
+    for (int ka = 0; ka < RA; ++ka) {
+        for (int kt = 0; kt < TI; ++kt) {
+            const int k = ka * TI + kt;
+            if (k >= R) break;
+            double* row = s_row[k & 1];
+            double* col = s_col[k & 1];
+            if (ti == kt) {
+#pragma unroll
+                for (int j = 0; j < RA; ++j) row[col_of(j)] = v[ka][j];
+            }
+            if (tj == kt) {
+#pragma unroll
+                for (int i = 0; i < RA; ++i) col[row_of(i)] = v[i][ka];
+            }
+            __syncthreads();
+            const double pv = row[k];
+            const double inv = 1.0 / (pv > tiny ? pv : tiny);
+            double rk[RA], ck[RA];
+#pragma unroll
+            for (int j = 0; j < RA; ++j) rk[j] = (j == ka && tj == kt ? 1.0 : row[col_of(j)]) * inv;
+#pragma unroll
+            for (int i = 0; i < RA; ++i) ck[i] = col[row_of(i)];
+#pragma unroll
+            for (int i = 0; i < RA; ++i)
+#pragma unroll
+                for (int j = 0; j < RA; ++j) {
+                    const double base = j == ka && tj == kt ? 0.0 : v[i][j];
+                    v[i][j] = i == ka && ti == kt ? rk[j] : base - ck[i] * rk[j];
+                }
         }
-        __syncthreads();
-        for (int e = tid; e < RR; e += 256) {
-            const int i = e / R, j = e % R;
-            if (i == k) continue;
-            const double f = fcol[i];
-            L[e] -= f * L[k * R + j];
-            Vi[e] -= f * Vi[k * R + j];
-        }
-        __syncthreads();
     }
     // The 1-norm condition number kappa = ||V||_1 ||V^{-1}||_1 picks the
     // precision of the update's product M W (als_solve): fp32 sums while kappa
     // <= kSolveFp32MaxCond, fp64 sums above (or when kappa is not finite).
-    if (tid < 64) {
-        double a = 0.0, b = 0.0;
-        for (int j = tid; j < R; j += 64) {
-            double sa = 0.0, sb = 0.0;
-            for (int i = 0; i < R; ++i) {
-                sa += fabs(V[i * R + j]);
-                sb += fabs(Vi[i * R + j]);
+    const double kappa = vnorm * norm1(v);
+    if (tid == 0) *wide = (kappa <= kSolveFp32MaxCond) ? 0 : 1;   // NaN: fp64
+#pragma unroll
+    for (int i = 0; i < RA; ++i)
+#pragma unroll
+        for (int j = 0; j < RA; ++j) s_inv[row_of(i) * LD + col_of(j)] = v[i][j];
+    __syncthreads();
+    // T = S V^{-1} (S is symmetric: column r of it is read as row r), then
+    // P = V^{-1} T (V^{-1} is symmetric)
+    double p[RA][RA];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < RA; ++i)
+#pragma unroll
+            for (int j = 0; j < RA; ++j) p[i][j] = 0.0;
+    };
+    clear();
+#pragma unroll 4
+    for (int k = 0; k < R; ++k) {
+        double x[RA], y[RA];
+#pragma unroll
+        for (int i = 0; i < RA; ++i) x[i] = ST ? s_st[k * LD + row_of(i)] : S[k * R + min(row_of(i), R - 1)];
+#pragma unroll
+        for (int j = 0; j < RA; ++j) y[j] = s_inv[k * LD + col_of(j)];
+#pragma unroll
+        for (int i = 0; i < RA; ++i)
+#pragma unroll
+            for (int j = 0; j < RA; ++j) p[i][j] = fma(x[i], y[j], p[i][j]);
+    }
+    if constexpr (ST) __syncthreads();   // S read by all
+#pragma unroll
+    for (int i = 0; i < RA; ++i)
+#pragma unroll
+        for (int j = 0; j < RA; ++j) {
+            const int r = row_of(i), c = col_of(j);
+            if constexpr (ST) s_st[r * LD + c] = p[i][j];
+            else if (r < R && c < R) T[r * R + c] = p[i][j];
+            if (r == c) s_tr[r] = p[i][j];
+        }
+    __syncthreads();
+    clear();
+#pragma unroll 4
+    for (int k = 0; k < R; ++k) {
+        double x[RA], y[RA];
+#pragma unroll
+        for (int i = 0; i < RA; ++i) x[i] = s_inv[k * LD + row_of(i)];
+#pragma unroll
+        for (int j = 0; j < RA; ++j) y[j] = ST ? s_st[k * LD + col_of(j)] : T[k * R + min(col_of(j), R - 1)];
+#pragma unroll
+        for (int i = 0; i < RA; ++i)
+#pragma unroll
+            for (int j = 0; j < RA; ++j) p[i][j] = fma(x[i], y[j], p[i][j]);
+    }
+    // lambda = sqrt(diag P)
+#pragma unroll
+    for (int i = 0; i < RA; ++i)
+#pragma unroll
+        for (int j = 0; j < RA; ++j)
+            if (row_of(i) == col_of(j)) s_lam[row_of(i)] = p[i][j] > 0.0 ? sqrt(p[i][j]) : 0.0;
+    __syncthreads();
+    for (int r = tid; r < R; r += NT) lambda[r] = s_lam[r];
+    double xh = 0.0;
+#pragma unroll
+    for (int i = 0; i < RA; ++i)
+#pragma unroll
+        for (int j = 0; j < RA; ++j) {
+            const int r = row_of(i), c = col_of(j);
+            if (r >= R || c >= R) continue;
+            const double lr = s_lam[r], lc = s_lam[c];
+            const double g = (lr > 0.0 && lc > 0.0) ? p[i][j] / (lr * lc) : 0.0;
+            G[(int64_t)d * RR + r * R + c] = g;
+            W[r * R + c] = lc > 0.0 ? v[i][j] / lc : 0.0;
+            if (last) {
+                double h = g;
+                for (int w = 0; w < N; ++w)
+                    if (w != d) h *= G[(int64_t)w * RR + r * R + c];
+                xh += lr * lc * h;
             }
-            a = fmax(a, sa);
-            b = fmax(b, sb);
         }
-        for (int m = 1; m < 64; m <<= 1) {
-            a = fmax(a, __shfl_xor(a, m, 64));
-            b = fmax(b, __shfl_xor(b, m, 64));
-        }
-        const double kappa = a * b;
-        if (tid == 0) *wide = (kappa <= kSolveFp32MaxCond) ? 0 : 1;   // NaN: fp64
-    }
-    __syncthreads();
-    // S into V's slot (V is no longer needed), then T = S V^{-1}
-    for (int e = tid; e < RR; e += 256) V[e] = S[e];
-    __syncthreads();
-    for (int e = tid; e < RR; e += 256) {
-        const int i = e / R, j = e % R;
-        double s = 0.0;
-        for (int k = 0; k < R; ++k) s += V[i * R + k] * Vi[k * R + j];
-        T[e] = s;
-    }
-    __syncthreads();
-    // P = V^{-1} T (V^{-1} is symmetric) into V; lambda = sqrt(diag P)
-    for (int e = tid; e < RR; e += 256) {
-        const int i = e / R, j = e % R;
-        double s = 0.0;
-        for (int k = 0; k < R; ++k) s += Vi[k * R + i] * T[k * R + j];
-        V[e] = s;
-    }
-    __syncthreads();
-    for (int r = tid; r < R; r += 256) {
-        const double p = V[r * R + r];
-        lambda[r] = p > 0.0 ? sqrt(p) : 0.0;
-    }
-    __syncthreads();
-    for (int e = tid; e < RR; e += 256) {
-        const int i = e / R, j = e % R;
-        const double li = lambda[i], lj = lambda[j];
-        G[(int64_t)d * RR + e] = (li > 0.0 && lj > 0.0) ? V[e] / (li * lj) : 0.0;
-        W[e] = lj > 0.0 ? Vi[e] / lj : 0.0;
-    }
-    __syncthreads();
     if (last) {
         // <X, Xhat> = sum_r lambda_r (S W)_rr = trace(S V^{-1}) over columns
-        // with lambda_r > 0; ||Xhat||^2 = lambda^T (Hadamard of all G) lambda.
-        // Per-thread sums over a fixed slice, then a fixed-order block sum.
-        __shared__ double part[256];
-        double xh = 0.0;
-        for (int e = tid; e < RR; e += 256) {
-            const int i = e / R, j = e % R;
-            double h = 1.0;
-            for (int w = 0; w < N; ++w) h *= G[(int64_t)w * RR + e];
-            xh += lambda[i] * lambda[j] * h;
-        }
-        part[tid] = xh;
+        // with lambda_r > 0; ||Xhat||^2 = lambda^T (Hadamard of all G) lambda,
+        // its per-thread sums added in a fixed order.
+        for (int m = 1; m < 64; m <<= 1) xh += __shfl_xor(xh, m, 64);
+        if ((tid & 63) == 0) s_red[tid >> 6] = xh;
         __syncthreads();
-        for (int off = 128; off > 0; off >>= 1) {
-            if (tid < off) part[tid] += part[tid + off];
-            __syncthreads();
-        }
         if (tid == 0) {
-            double inner = 0.0;
+            double model = 0.0, inner = 0.0;
+            for (int w = 0; w < NT / 64; ++w) model += s_red[w];
             for (int r = 0; r < R; ++r)
-                if (lambda[r] > 0.0) inner += T[r * R + r];
+                if (s_lam[r] > 0.0) inner += s_tr[r];
             const double x2 = *xnorm2;
-            const double res = x2 - 2.0 * inner + part[0];
+            const double res = x2 - 2.0 * inner + model;
             *fit = x2 > 0.0 ? 1.0 - sqrt(res > 0.0 ? res : 0.0) / sqrt(x2) : 0.0;
         }
     }
@@ -481,24 +599,65 @@ int64_t gram_slabs(int64_t rows)
     return std::max<int64_t>(1, std::min<int64_t>(n, 2048));
 }
 
+int64_t als_gram_slabs(int64_t rows, int R)
+{
+    // The sweep's Gram matrices need not have amped_gram's bits, and slabs of 8192
+    // rows leave most CUs idle: 80 us for 100k rows of rank 32 on 13 blocks, 86 us
+    // for 500k on 62.  So from 256 rows on (64 per wave), up to a few blocks per
+    // CU; wide ranks have several tile groups per slab and larger partials.
+    int64_t n = std::min<int64_t>((rows + 255) / 256, R <= 64 ? 1024 : 512);
+    if (n > 256) n = (n + 255) / 256 * 256;
+    return std::max<int64_t>(gram_slabs(rows), n);
+}
+
+static hipError_t launch_gram_set(GramSet& set, const int64_t* nslab, int R, float* partial, hipStream_t st)
+{
+    if (R < 1 || R > 128 || set.n < 1 || set.n > kGramMany) return hipErrorInvalidValue;
+    set.begin[0] = 0;
+    for (int m = 0; m < set.n; ++m) {
+        set.begin[m + 1] = set.begin[m] + nslab[m];
+        set.slab_rows[m] = (set.rows[m] + nslab[m] - 1) / nslab[m];
+        set.slab_rows[m] += set.slab_rows[m] & 1;
+    }
+    const int T = (R + 31) / 32;
+    const int groups = (T * (T + 1) / 2 + kGramMaxPairs - 1) / kGramMaxPairs;
+    dim3 grid((unsigned)set.begin[set.n], (unsigned)groups);
+    switch (T) {
+    case 1: hipLaunchKernelGGL(gram_partial<1>, grid, dim3(256), 0, st, set, R, partial); break;
+    case 2: hipLaunchKernelGGL(gram_partial<2>, grid, dim3(256), 0, st, set, R, partial); break;
+    case 3: hipLaunchKernelGGL(gram_partial<3>, grid, dim3(256), 0, st, set, R, partial); break;
+    default: hipLaunchKernelGGL(gram_partial<4>, grid, dim3(256), 0, st, set, R, partial); break;
+    }
+    hipLaunchKernelGGL(gram_reduce, dim3((R * R + 31) / 32, set.n), dim3(1024), 0, st, set, R, partial);
+    return hipGetLastError();
+}
+
 hipError_t launch_gram(const float* A, int64_t rows, int R, float* partial, double* G, hipStream_t st,
                        int64_t nslab)
 {
-    if (R < 1 || R > 128) return hipErrorInvalidValue;
+    GramSet set{};
+    set.n = 1;
+    set.A[0] = A;
+    set.rows[0] = rows;
+    set.G[0] = G;
     if (nslab <= 0) nslab = gram_slabs(rows);
-    int64_t slab_rows = (rows + nslab - 1) / nslab;
-    slab_rows += slab_rows & 1;
-    const int T = (R + 31) / 32;
-    const int groups = (T * (T + 1) / 2 + kGramMaxPairs - 1) / kGramMaxPairs;
-    dim3 grid((unsigned)nslab, (unsigned)groups);
-    switch (T) {
-    case 1: hipLaunchKernelGGL(gram_partial<1>, grid, dim3(256), 0, st, A, rows, R, slab_rows, partial); break;
-    case 2: hipLaunchKernelGGL(gram_partial<2>, grid, dim3(256), 0, st, A, rows, R, slab_rows, partial); break;
-    case 3: hipLaunchKernelGGL(gram_partial<3>, grid, dim3(256), 0, st, A, rows, R, slab_rows, partial); break;
-    default: hipLaunchKernelGGL(gram_partial<4>, grid, dim3(256), 0, st, A, rows, R, slab_rows, partial); break;
+    return launch_gram_set(set, &nslab, R, partial, st);
+}
+
+hipError_t launch_als_grams(const float* const* A, const int64_t* rows, int n, int R, float* partial, double* G,
+                            hipStream_t st)
+{
+    GramSet set{};
+    int64_t nslab[kGramMany] = {};
+    if (n > kGramMany) return hipErrorInvalidValue;
+    set.n = n;
+    for (int m = 0; m < n; ++m) {
+        set.A[m] = A[m];
+        set.rows[m] = rows[m];
+        set.G[m] = G + (int64_t)m * R * R;
+        nslab[m] = als_gram_slabs(rows[m], R);
     }
-    hipLaunchKernelGGL(gram_reduce, dim3((R * R + 31) / 32), dim3(256), 0, st, partial, nslab, R, G);
-    return hipGetLastError();
+    return launch_gram_set(set, nslab, R, partial, st);
 }
 
 // ------------------------------------------------ Gram without allocation
@@ -552,10 +711,19 @@ hipError_t launch_gram_noalloc(const float* A, int64_t rows, int R, double* G, h
 hipError_t launch_als_small(double* G, const double* S, int N, int d, int R, double* scratch, double* W, int* wide,
                             double* lambda, bool last, const double* xnorm2, double* fit, hipStream_t st)
 {
-    const size_t bytes = (size_t)4 * R * R * sizeof(double);
-    const bool in_lds = bytes <= (size_t)128 * 1024;
-    hipLaunchKernelGGL(als_small, dim3(1), dim3(256), in_lds ? bytes : 0, st, G, S, N, d, R, scratch, W, wide,
-                       lambda, last ? 1 : 0, xnorm2, fit, in_lds ? 1 : 0);
+    auto launch = [&](auto kernel, int rp, int threads) {
+        const size_t lds = (size_t)rp * (rp + 1) * sizeof(double) * (rp <= 64 ? 2 : 1);
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), lds, st, G, S, N, d, R, scratch, W, wide, lambda,
+                           last ? 1 : 0, xnorm2, fit);
+    };
+    // one to four entries per thread while the block has them: fewer waves have
+    // cheaper barriers but more arithmetic per pivot (rank 32: one wave of 16
+    // entries per thread 46 us, four of 4 entries KKK us); 16 above rank 96
+    if (R <= 16) launch(als_small<1, 16>, 16, 256);
+    else if (R <= 32) launch(als_small<2, 16>, 32, 256);
+    else if (R <= 64) launch(als_small<2, 32>, 64, 1024);
+    else if (R <= 96) launch(als_small<3, 32>, 96, 1024);
+    else launch(als_small<4, 32>, 128, 1024);
     return hipGetLastError();
 }
 

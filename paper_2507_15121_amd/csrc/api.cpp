@@ -100,7 +100,7 @@ struct amped_tensor_s {
         double* G = nullptr;       // [N][R][R] Gram matrices
         double* S = nullptr;       // R x R, M^T M
         float* partial = nullptr;  // Gram partials
-        double* scratch = nullptr; // 4 R x R
+        double* scratch = nullptr; // R x R
         double* W = nullptr;       // R x R, V^{-1} D^{-1}
         int* wide = nullptr;       // set by als_small: the product M W sums in fp64
         double* xnorm2 = nullptr;  // ||X||^2 (computed once)
@@ -845,8 +845,11 @@ amped_status amped_cp_als_sweep(amped_tensor_t t, int rank, float* const* factor
         w = amped_tensor_s::AlsWork{};
         w.xnorm2 = keep_x;
         w.have_xnorm2 = keep_have;
-        int64_t maxrows = 0;
-        for (int d = 0; d < N; ++d) maxrows = std::max(maxrows, t->dims[d]);
+        int64_t maxrows = 0, slabs = 0;
+        for (int d = 0; d < N; ++d) {
+            maxrows = std::max(maxrows, t->dims[d]);
+            slabs += amped::als_gram_slabs(t->dims[d], rank);   // all factors' Gram matrices in one launch
+        }
         void* p = nullptr;
         if ((e = t->alloc(&p, (size_t)maxrows * rank * sizeof(float))) != hipSuccess) return hip_fail(e, "als workspace");
         w.M = static_cast<float*>(p);
@@ -854,10 +857,10 @@ amped_status amped_cp_als_sweep(amped_tensor_t t, int rank, float* const* factor
         w.G = static_cast<double*>(p);
         if ((e = t->alloc(&p, RR * sizeof(double))) != hipSuccess) return hip_fail(e, "als workspace");
         w.S = static_cast<double*>(p);
-        if ((e = t->alloc(&p, (size_t)amped::gram_slabs(maxrows) * RR * sizeof(float))) != hipSuccess)
+        if ((e = t->alloc(&p, (size_t)slabs * RR * sizeof(float))) != hipSuccess)
             return hip_fail(e, "als workspace");
         w.partial = static_cast<float*>(p);
-        if ((e = t->alloc(&p, 4 * RR * sizeof(double))) != hipSuccess) return hip_fail(e, "als workspace");
+        if ((e = t->alloc(&p, RR * sizeof(double))) != hipSuccess) return hip_fail(e, "als workspace");
         w.scratch = static_cast<double*>(p);
         if ((e = t->alloc(&p, RR * sizeof(double))) != hipSuccess) return hip_fail(e, "als workspace");
         w.W = static_cast<double*>(p);
@@ -899,15 +902,14 @@ amped_status amped_cp_als_sweep(amped_tensor_t t, int rank, float* const* factor
     }
     w.have_grams = false;   // stays false if the sweep stops part-way
     if (!reuse) {
-        for (int m = 0; m < N; ++m)
-            if ((e = amped::launch_gram(factors[m], t->dims[m], rank, w.partial, w.G + m * RR, s)) != hipSuccess)
-                return hip_fail(e, "gram");
+        if ((e = amped::launch_als_grams(factors, t->dims, N, rank, w.partial, w.G, s)) != hipSuccess)
+            return hip_fail(e, "gram");
     }
     for (int d = 0; d < N; ++d) {
         st = run_mttkrp(t, d, rank, reinterpret_cast<const void* const*>(factors), w.M, stream,
                         amped::FactorType::F32, amped::Kind::Mttkrp, 1.0f);
         if (st != AMPED_OK) return st;
-        if ((e = amped::launch_gram(w.M, t->dims[d], rank, w.partial, w.S, s)) != hipSuccess)
+        if ((e = amped::launch_als_grams(&w.M, &t->dims[d], 1, rank, w.partial, w.S, s)) != hipSuccess)
             return hip_fail(e, "gram");
         if ((e = amped::launch_als_small(w.G, w.S, N, d, rank, w.scratch, w.W, w.wide, lambda, d == N - 1,
                                          w.xnorm2, fit, s)) != hipSuccess)

@@ -200,12 +200,17 @@ hipError_t queue_stats_copy(unsigned long long* host, int64_t max_records, int64
 int64_t gram_slabs(int64_t rows);
 hipError_t launch_gram(const float* A, int64_t rows, int R, float* partial, double* G, hipStream_t st,
                        int64_t nslab = 0);
-// The same with the partial sums in the library's fixed device array (no
+// The sweep's Gram matrices: G[m] = A[m]^T A[m] for n matrices in one launch, via
+// (sum of als_gram_slabs(rows[m], R)) x R x R fp32 partials.
+int64_t als_gram_slabs(int64_t rows, int R);
+hipError_t launch_als_grams(const float* const* A, const int64_t* rows, int n, int R, float* partial, double* G,
+                            hipStream_t st);
+// launch_gram with the partial sums in the library's fixed device array (no
 // allocation): at most gram_noalloc_slabs(rows, R) <= gram_slabs(rows) slabs,
 // so that they fit its 32 MiB.
 int64_t gram_noalloc_slabs(int64_t rows, int R);
 hipError_t launch_gram_noalloc(const float* A, int64_t rows, int R, double* G, hipStream_t st);
-// The R x R algebra of the mode-d update (scratch: 4 R x R doubles); G is
+// The R x R algebra of the mode-d update (scratch: R x R doubles); G is
 // [N][R][R] and G[d] is replaced by the Gram matrix of the new factor.
 hipError_t launch_als_small(double* G, const double* S, int N, int d, int R, double* scratch, double* W, int* wide,
                             double* lambda, bool last, const double* xnorm2, double* fit, hipStream_t st);

@@ -18,7 +18,7 @@
 //    supplying A[row0 + l/32][tile*32 + l%32] as both operands (the K index of
 //    the product is the row).  Per-slab fp32 partials are summed in fp64 by
 //    gram_reduce, in slab order (deterministic).
-//  * als_small: one block, fp64: V, V^{-1} (Gauss-Jordan), P, lambda,
+//  * als_small: one block, fp64 in registers: V, V^{-1} (Gauss-Jordan), P, lambda,
 //    the new G_d, W and, after the last mode, the fit.
 //  * als_solve: A_d = M W, a persistent grid over tiles of rows (256 at
 //    R <= 32) staged through LDS beside W; the next tile's rows are loaded
@@ -172,7 +172,7 @@ __device__ __forceinline__ void gram_slab(const GramSet& set, int R, float* part
 
 // The tile groups of a slab differ in blockIdx.y: each has code of its own, so
 // that the tiles of a matrix instruction are fixed registers (chosen at run time,
-// 50,000 rows of rank 100 took 1570 us, now KKK us).
+// 50,000 rows of rank 100 took 1570 us in amped_gram's slabs, now 316 us).
 template <int T>
 __global__ void __launch_bounds__(256) gram_partial(GramSet set, int R, float* partial)
 {
@@ -237,10 +237,10 @@ constexpr double kSolveFp32MaxCond = 1e4;
 // a, b < RA, of the RP x RP matrix (RP = TI RA >= R, padded by the identity) in
 // registers, through the elimination and both products; LDS carries what other
 // threads need.  What bounds it is the chain of R pivots, so a pivot is one LDS
-// round trip and one barrier (row k, column k in two buffers), and up to rank 32
-// the block is a single wave, which needs no barrier at all.  With the matrices
-// in LDS, or above rank 64 in global memory, and three barriers per pivot it took
-// 62 us at rank 32 and 7 ms at rank 100; now KKK us and LLL us.
+// round trip and one barrier (row k, column k in two buffers), on as many threads
+// as leave each one to four entries (16 above rank 96).  With the matrices in
+// LDS, or above rank 64 in global memory, and three barriers per pivot it took 62
+// us at rank 32 and about 5 ms at rank 100; now 19 us and 171 us (57 us at 64).
 template <int RA, int TI>
 __global__ void __launch_bounds__(TI * TI) als_small(double* G, const double* S, int N, int d, int R, double* T,
                                                      double* W, int* wide, double* lambda, int last,
@@ -603,7 +603,7 @@ int64_t als_gram_slabs(int64_t rows, int R)
 {
     // The sweep's Gram matrices need not have amped_gram's bits, and slabs of 8192
     // rows leave most CUs idle: 80 us for 100k rows of rank 32 on 13 blocks, 86 us
-    // for 500k on 62.  So from 256 rows on (64 per wave), up to a few blocks per
+    // for 500k on 62 (8 and 19 us here).  So from 256 rows on (64 per wave), up to a few blocks per
     // CU; wide ranks have several tile groups per slab and larger partials.
     int64_t n = std::min<int64_t>((rows + 255) / 256, R <= 64 ? 1024 : 512);
     if (n > 256) n = (n + 255) / 256 * 256;
@@ -718,7 +718,7 @@ hipError_t launch_als_small(double* G, const double* S, int N, int d, int R, dou
     };
     // one to four entries per thread while the block has them: fewer waves have
     // cheaper barriers but more arithmetic per pivot (rank 32: one wave of 16
-    // entries per thread 46 us, four of 4 entries KKK us); 16 above rank 96
+    // entries per thread 46 us, four waves of 4 entries 19 us); 16 above rank 96
     if (R <= 16) launch(als_small<1, 16>, 16, 256);
     else if (R <= 32) launch(als_small<2, 16>, 32, 256);
     else if (R <= 64) launch(als_small<2, 32>, 64, 1024);

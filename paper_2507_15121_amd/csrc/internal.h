@@ -109,15 +109,43 @@ void mode_tables_sorted(const int32_t* keys, int64_t nnz, int64_t rows, int64_t 
 
 // True when the COO is already in lexicographic order of (i_0, ..., i_{N-1}).
 bool is_lexicographic(int order, int64_t nnz, const int32_t* idx);
+// The same of its first len entries only, one after the other.
+bool is_lexicographic_prefix(int order, int64_t nnz, const int32_t* idx, int64_t len);
 
 // Device layout build: a stable LSD radix sort of n (key, value) pairs by the
-// low key_bits bits of the keys, 8 bits per pass, ping-ponging between
-// (keys, vals) and (keys_alt, vals_alt); *result_in_alt says where the sorted
-// pairs are.  scratch holds sort_scratch_words(n) 32-bit words.
+// low key_bits bits of the keys, 8 bits per pass (sort_passes(key_bits) passes,
+// at least one must be needed).  The first pass reads (keys, vals) and writes
+// (kbuf[first], vbuf[first]), the next ones alternate between the two buffer
+// pairs; vals NULL: the positions.  keys or vals may be a buffer of the pair that
+// is not written first.  scratch holds sort_scratch_words(n) 32-bit words.
 int64_t sort_scratch_words(int64_t n);
-hipError_t launch_stable_sort_pairs(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt,
-                                    uint32_t* scratch, int64_t n, int key_bits, bool* result_in_alt,
-                                    hipStream_t st);
+int sort_passes(int key_bits);
+hipError_t launch_stable_sort(const uint32_t* keys, const int32_t* vals, uint32_t* const* kbuf, int32_t* const* vbuf,
+                              int first, uint32_t* scratch, int64_t n, int key_bits, hipStream_t st);
+// *bad = min(*bad, least position whose index is outside [0, dim)).
+hipError_t launch_check_range(const int32_t* col, int64_t dim, int64_t n, unsigned long long* bad, hipStream_t st);
+// *unsorted = 1 when the coordinates are not in lexicographic order.
+hipError_t launch_check_sorted(int order, const int32_t* const* cols, int64_t n, unsigned* unsorted, hipStream_t st);
+// A nonzero's record: order indices and the value, record_words(order) words of
+// whole 16 bytes.  pack: columns (order index columns, then the values) to
+// records; gather: record perm[p] to place p of the columns (NULL: not wanted).
+inline int64_t record_words(int order) { return (order + 4) / 4 * 4; }
+hipError_t launch_pack_records(int order, const void* const* cols, void* rec, int64_t n, hipStream_t st);
+hipError_t launch_gather_records(int order, const void* rec, const int32_t* perm, void* const* cols, int64_t n,
+                                 hipStream_t st);
+// Row lists of a mode from its sorted keys, in two steps: the entries' totals
+// (counts: 4 * row_list_blocks(n) words, 16-byte aligned, kept for the second
+// step), then the lists themselves (zero: shared + lone rows; gaps: pairs).
+struct RowTotals {
+    int64_t shared, lone, gaps, touched;
+};
+int row_list_blocks(int64_t n);
+hipError_t launch_count_rows(const int32_t* keys, int64_t n, int64_t rows, int64_t unit, uint32_t* counts,
+                             RowTotals* totals, hipStream_t st);
+hipError_t launch_fill_rows(const int32_t* keys, int64_t n, int64_t rows, int64_t unit, const uint32_t* counts,
+                            int64_t n_shared, int32_t* zero, int32_t* gaps, hipStream_t st);
+// Hot-row tables (kHotTableLen entries) from sorted keys; best: kHotMax zeros.
+hipError_t launch_hot_tables(const int32_t* keys, int64_t n, unsigned long long* best, int32_t* hot, hipStream_t st);
 // a[i] = i for i < n.
 hipError_t launch_iota(int32_t* a, int64_t n, hipStream_t st);
 

@@ -280,6 +280,17 @@ bool is_lexicographic(int order, int64_t nnz, const int32_t* idx)
     return unsorted == 0;
 }
 
+bool is_lexicographic_prefix(int order, int64_t nnz, const int32_t* idx, int64_t len)
+{
+    for (int64_t k = 1; k < len; ++k)
+        for (int w = 0; w < order; ++w) {
+            const int32_t a = idx[(int64_t)w * nnz + k - 1], b = idx[(int64_t)w * nnz + k];
+            if (a > b) return false;
+            if (a < b) break;
+        }
+    return true;
+}
+
 void gather_i32(const int32_t* src, const int32_t* perm, int64_t p0, int64_t p1, int32_t* dst)
 {
 #pragma omp parallel for schedule(static)

@@ -70,6 +70,7 @@ struct amped_tensor_s {
     int64_t dims[kMaxOrder] = {};
     int64_t nnz = 0, chunk = 0, n_chunks = 0;
     int64_t unit = 0;                       // nonzeros per work unit of the kernels
+    bool own_units = false;                 // sized by the library
     int device = 0;
     bool keep_perm = false;
     int64_t device_bytes = 0;
@@ -239,7 +240,7 @@ amped_status upload_tables(amped_tensor_s* t, ModeDev& m, int d, const HostModeL
         m.gaps = static_cast<int32_t*>(p);
     }
     m.nnz = t->nnz;
-    m.chunk = t->unit;
+    m.chunk = m.residual_chunk = t->unit;
     m.n_chunks = (t->nnz + t->unit - 1) / t->unit;
     m.rows = t->dims[d];
     m.n_zero = (int64_t)lay.zero_rows.size();
@@ -436,6 +437,7 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
             m.nnz = nnz;
             m.chunk = t->unit;
             m.n_chunks = (nnz + t->unit - 1) / t->unit;
+            m.residual_chunk = t->unit * (t->own_units ? amped::residual_units(nnz, t->unit) : 1);
             m.rows = dims[d];
             m.zero_row = aux;
             m.sink = aux + 4;
@@ -808,7 +810,8 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
     t->chunk = chunk;
     t->n_chunks = (nnz + chunk - 1) / chunk;
     t->unit = chunk;
-    if (!opts || opts->chunk_nnz == 0)
+    t->own_units = !opts || opts->chunk_nnz == 0;
+    if (t->own_units)
         t->unit = host_layout ? amped::stream_work_unit(std::min(stage_len, nnz)) : amped::work_unit(nnz);
     t->device = dev;
     t->keep_perm = keep_perm;

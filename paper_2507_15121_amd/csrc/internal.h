@@ -17,25 +17,34 @@ constexpr int64_t kDefaultChunk = 4096;
 constexpr int64_t kMaxChunk = int64_t(1) << 28;
 // Nonzeros per work unit (what one wave takes from the queue) of a layout of nnz
 // nonzeros, when the caller leaves the chunk size to the library.  A unit costs
-// a wave about 11 us beside 6 us for each 256 nonzeros (rank 32), and a last
-// round of units that fills the 2048 waves of the grid only in part leaves the
-// rest idle: so up to 4 whole rounds of equal units, of at most 5120 nonzeros
-// (longer ones spread the waves' rows over more of the factors: at 50M nonzeros
-// one round of 24576 takes 2234 us for all modes, units of 4096 take 2148), and
-// above that units of 4096, whose last round is short.  Measured, all modes at
-// rank 32, units of 4096 against this rule: 100k nonzeros (rank 16) 145 -> 41
-// us, 1M 94 us (units of 512), 5M 309 -> 258 us, 10M 603 -> 482 us, 20M with
-// bfloat16 rank 64 1120 -> 1111 us.
+// a wave about 3 us beside 6 us for each 256 nonzeros (rank 32).  Up to 5.2M
+// nonzeros each of the 2048 waves of the grid gets one unit of whole tiles: fewer
+// or more of them leave waves idle at the end.  Above that waves that meet fewer
+// cache hits take longer, and small units off the queue even that out; from 32M
+// on more of a heavy row's neighbours share a unit of 2048.  All modes at rank 32,
+// units of 4096, one unit per wave, 1024 and 2048: 1M nonzeros 95, 63, 73 us and
+// more; 2M 103 us (one per wave), 128 us (512); 5M 309, 233, 248 us; 10M 600, 446,
+// 428, 450 us (order 4: 740, 703, 740 us with the last three); 20M 868 us (5120),
+// 809, 830; rank 64 with bfloat16 factors 1002, 934, 955; 50M 2090, -, 2071, 2045;
+// 200M 8694, -, 8756, 8626.
 constexpr int64_t kGridWaves = 2048;
 constexpr int64_t kTileNnz = 256;      // a unit is whole tiles of the kernel
-constexpr int64_t kMaxRoundUnit = 5120;
+constexpr int64_t kMaxRoundUnit = 2560;
 inline int64_t work_unit(int64_t nnz)
 {
-    const int64_t rounds = (nnz + kGridWaves * kMaxRoundUnit - 1) / (kGridWaves * kMaxRoundUnit);
-    if (rounds > 4) return kDefaultChunk;
-    const int64_t waves = kGridWaves * (rounds > 0 ? rounds : 1);
-    const int64_t tiles = (nnz + waves * kTileNnz - 1) / (waves * kTileNnz);
+    if (nnz > kGridWaves * kMaxRoundUnit) return nnz < (int64_t(32) << 20) ? 1024 : 2048;
+    const int64_t tiles = (nnz + kGridWaves * kTileNnz - 1) / (kGridWaves * kTileNnz);
     return kTileNnz * (tiles > 0 ? tiles : 1);
+}
+// Units that a wave of the residual and loss forms takes at a time: a unit costs
+// them more (their own rows start anew).  All gradients at rank 32 with 1, 2 and
+// this many units of 1024: 10M nonzeros 509, 502, 485 us (one chunk per wave), 20M
+// 965, 950, 950 us.
+inline int64_t residual_units(int64_t nnz, int64_t unit)
+{
+    if (nnz <= kGridWaves * kMaxRoundUnit || nnz >= (int64_t(32) << 20)) return 1;
+    if (nnz <= kGridWaves * 5120) return (nnz + kGridWaves * unit - 1) / (kGridWaves * unit);
+    return 2;
 }
 // The same for layouts that are streamed in shards of whole chunks of 4096: a
 // power of two, so that shards end at unit ends too.
@@ -162,6 +171,7 @@ struct ModeDev {
     const int32_t* gaps = nullptr;                 // [2 * n_gaps]
     int64_t nnz = 0, rows = 0, n_zero = 0, n_gaps = 0;
     int64_t chunk = 0, n_chunks = 0;               // nonzeros per work unit, work units
+    int64_t residual_chunk = 0;                    // the same for the residual and loss forms (whole units)
     unsigned* queue = nullptr;                     // kQueueSlots device work-queue counters, kQueueStride words apart
     const int32_t* hot = nullptr;                  // hot-row tables of this mode [kHotTableLen]
     const void* zero_row = nullptr;                // 16 zero bytes

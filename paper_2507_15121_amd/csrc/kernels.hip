@@ -216,7 +216,7 @@ Shape launch_shape(KernelFn fn, int block, int nin, int row_bytes, bool cache)
 // Blocks of a launch: the persistent grid, or a block per chunk when there are
 // fewer chunks (one wave of each block then has work: the chunks spread over
 // the CUs).
-int launch_grid(const Shape& sh, const ModeDev& m) { return (int)std::min<int64_t>(sh.grid, m.n_chunks); }
+int launch_grid(const Shape& sh, const KParams& k) { return (int)std::min<int64_t>(sh.grid, k.n_chunks); }
 
 hipError_t launch_init(const ModeDev& m, float* out, int64_t ld, int col0, int ncols, double* loss,
                        hipStream_t st)
@@ -240,7 +240,9 @@ void set_hot(KParams& k, int hot_k, const int32_t* const* in_hot, int nin)
     for (int w = 0; w < nin; ++w) k.hot[w] = hot_k ? in_hot[w] + (hot_k - 1) : nullptr;
 }
 
-KParams base_params(const ModeDev& m)
+// Rows that cross the edge of a chunk of several units cross a unit's edge, so
+// they are in the zero-row list.
+KParams base_params(const ModeDev& m, int64_t chunk)
 {
     KParams k{};
     k.out_idx = m.out_idx;
@@ -248,10 +250,10 @@ KParams base_params(const ModeDev& m)
     k.val = m.val;
     k.queue = m.queue;
     k.n_stripes = queue_stripes();
-    k.stripe_len = (int)((m.n_chunks + k.n_stripes - 1) / k.n_stripes);
+    k.chunk = chunk;
+    k.n_chunks = (m.nnz + chunk - 1) / chunk;
+    k.stripe_len = (int)((k.n_chunks + k.n_stripes - 1) / k.n_stripes);
     k.nnz = m.nnz;
-    k.chunk = m.chunk;
-    k.n_chunks = m.n_chunks;
     k.rows = m.rows;
     k.zero_row = m.zero_row;
     k.sink = m.sink;
@@ -318,7 +320,7 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
         fn = pick_mttkrp(a.nin, a.ftype, a.kind, v, false);
     }
     if (!fn) return hipErrorNotSupported;
-    KParams k = base_params(m);
+    KParams k = base_params(m, grad ? m.residual_chunk : m.chunk);
     for (int w = 0; w < a.nin; ++w) {
         k.fac[w] = a.in_factors[w];
         k.fbytes[w] = buf ? (uint32_t)((uint64_t)a.in_rows[w] * a.rank * eb) : 0u;
@@ -344,10 +346,10 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
         k.col0 = col0;
         k.ncols = ncols;
 #if AMPED_QUEUE_STATS
-        if ((e = qstats_attach(k, launch_grid(sh, m), block, a.stream)) != hipSuccess) return e;
+        if ((e = qstats_attach(k, launch_grid(sh, k), block, a.stream)) != hipSuccess) return e;
 #endif
         void* args[] = {&k};
-        e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(launch_grid(sh, m)), dim3(block), args, sh.dyn,
+        e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(launch_grid(sh, k)), dim3(block), args, sh.dyn,
                             a.stream);
         if (e != hipSuccess) return e;
     }
@@ -380,7 +382,7 @@ hipError_t launch_cp_loss(const LossArgs& a)
     if (scalar && a.rank > 64) return hipErrorNotSupported;
     if (scalar) fn = pick_loss(a.order - 1, Lanes{}, false);
     if (!fn) return hipErrorNotSupported;
-    KParams k = base_params(m);
+    KParams k = base_params(m, m.residual_chunk);
     for (int w = 0; w < a.order - 1; ++w) {
         k.fac[w] = a.in_factors[w];
         k.fbytes[w] = buf ? (uint32_t)((uint64_t)a.in_rows[w] * a.rank * 4) : 0u;
@@ -399,10 +401,10 @@ hipError_t launch_cp_loss(const LossArgs& a)
     if (sh.grid <= 0) return hipErrorInvalidDevice;
     set_hot(k, sh.hot_k, a.in_hot, a.order - 1);
 #if AMPED_QUEUE_STATS
-    if ((e = qstats_attach(k, launch_grid(sh, m), block, a.stream)) != hipSuccess) return e;
+    if ((e = qstats_attach(k, launch_grid(sh, k), block, a.stream)) != hipSuccess) return e;
 #endif
     void* args[] = {&k};
-    return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(launch_grid(sh, m)), dim3(block), args, sh.dyn,
+    return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(launch_grid(sh, k)), dim3(block), args, sh.dyn,
                            a.stream);
 }
 

@@ -160,9 +160,47 @@ hipError_t launch_iota(int32_t* a, int64_t n, hipStream_t st);
 
 // Gather idx[w][perm[p]] for p in [p0, p1) into dst.
 void gather_i32(const int32_t* src, const int32_t* perm, int64_t p0, int64_t p1, int32_t* dst);
-void gather_f32(const float* src, const int32_t* perm, int64_t p0, int64_t p1, float* dst);
+
+// A mode's layout packed for the host link: blocks of kPackBlock nonzeros, each
+//   8 words   the block's first output index, the bits b of the others above it
+//   8 b       words: output indices minus the first, b bits each
+//   8 bits[j] words: input indices j, bits[j] each (as its mode needs)
+//   256       words: the values
+// every column's entries one after the other, lowest bits first.  A block is never
+// longer than its plain arrays.  offset[k] is where block k starts, in 8 words.
+constexpr int kPackBlock = 256;
+struct PackedMode {
+    int nin = 0;
+    int bits[kMaxOrder - 1] = {};
+    int mode = 0, in_mode[kMaxOrder - 1] = {};
+    std::vector<uint32_t> offset;          // [blocks + 1]
+    uint32_t* data = nullptr;
+    uint32_t* dev_offset = nullptr;        // offset on the device
+
+    int64_t blocks() const { return offset.empty() ? 0 : (int64_t)offset.size() - 1; }
+    int64_t bytes(int64_t block) const { return offset.empty() ? 0 : (int64_t)offset[block] * 32; }
+    void plan(int order, const int64_t* dims, int64_t nnz, const int32_t* idx, int mode, const int32_t* perm);
+    void fill(int64_t nnz, const int32_t* idx, const float* val, const int32_t* perm);
+    int32_t out_index(int64_t p) const;
+    int32_t in_index(int j, int64_t p) const;
+    // out_idx [nnz], in_idx [nin][nnz], val [nnz], each nullable
+    void unpack(int64_t nnz, int32_t* out_idx, int32_t* in_idx, float* val) const;
+};
 
 // -------------------------------------------------------------- device layout
+// Packed blocks [first, first + blocks) (offset: the mode's, on the device; packed
+// holds them from block `first` on) to plain arrays: to[0] output indices, then
+// the input indices, then the values.
+struct UnpackArgs {
+    int order = 0;
+    int bits[kMaxOrder - 1] = {};
+    const uint32_t* packed = nullptr;
+    const uint32_t* offset = nullptr;
+    int64_t first = 0, blocks = 0;
+    int32_t* to[kMaxOrder + 1] = {};
+};
+hipError_t launch_unpack(const UnpackArgs& u, hipStream_t st);
+
 struct ModeDev {
     const int32_t* out_idx = nullptr;              // [nnz]
     const int32_t* in_idx[kMaxOrder - 1] = {};     // other modes ascending, each [nnz]

@@ -297,10 +297,124 @@ void gather_i32(const int32_t* src, const int32_t* perm, int64_t p0, int64_t p1,
     for (int64_t p = p0; p < p1; ++p) dst[p - p0] = src[perm[p]];
 }
 
-void gather_f32(const float* src, const int32_t* perm, int64_t p0, int64_t p1, float* dst)
+// ------------------------------------------------------------- packed layouts
+namespace {
+
+// Bits [at * b, (at + 1) * b) of a column (b <= 32; the word after the column's
+// last one is never needed).
+uint32_t get_bits(const uint32_t* col, int64_t at, int b)
+{
+    if (b == 0) return 0;
+    const int64_t bit = at * b;
+    const int sh = (int)(bit & 31);
+    uint64_t w = col[bit >> 5];
+    if (sh + b > 32) w |= (uint64_t)col[(bit >> 5) + 1] << 32;
+    return (uint32_t)(w >> sh) & (uint32_t)(((uint64_t)1 << b) - 1);
+}
+
+// kPackBlock entries of b bits each to 8 b words.
+template <typename Get>
+void put_bits(uint32_t* col, int b, const Get& get)
+{
+    uint64_t acc = 0;
+    int have = 0;
+    for (int k = 0; k < kPackBlock && b > 0; ++k) {
+        acc |= (uint64_t)get(k) << have;
+        have += b;
+        if (have >= 32) {
+            *col++ = (uint32_t)acc;
+            acc >>= 32;
+            have -= 32;
+        }
+    }
+}
+
+}  // namespace
+
+void PackedMode::plan(int order, const int64_t* dims, int64_t nnz, const int32_t* idx, int m, const int32_t* perm)
+{
+    mode = m;
+    nin = 0;
+    int words = 8 + kPackBlock;
+    for (int w = 0; w < order; ++w)
+        if (w != m) {
+            in_mode[nin] = w;
+            bits[nin] = bits_for((uint64_t)(dims[w] - 1));
+            words += 8 * bits[nin++];
+        }
+    const int64_t n = (nnz + kPackBlock - 1) / kPackBlock;
+    offset.assign((size_t)n + 1, 0);
+    const int32_t* key = idx + (int64_t)m * nnz;
+#pragma omp parallel for schedule(static)
+    for (int64_t b = 0; b < n; ++b) {
+        const int64_t last = std::min((b + 1) * kPackBlock, nnz) - 1;
+        const int kb = bits_for((uint64_t)(key[perm[last]] - key[perm[b * kPackBlock]]));
+        offset[b + 1] = (uint32_t)(words / 8 + kb);
+    }
+    for (int64_t b = 0; b < n; ++b) offset[b + 1] += offset[b];
+}
+
+void PackedMode::fill(int64_t nnz, const int32_t* idx, const float* val, const int32_t* perm)
+{
+    const int32_t* key = idx + (int64_t)mode * nnz;
+#pragma omp parallel for schedule(static)
+    for (int64_t b = 0; b < blocks(); ++b) {
+        const int64_t p0 = b * kPackBlock;
+        const int n = (int)std::min<int64_t>(kPackBlock, nnz - p0);
+        const int32_t* at = perm + p0;
+        uint32_t* w = data + (int64_t)offset[b] * 8;
+        const int32_t base = key[at[0]];
+        const int kb = bits_for((uint64_t)(key[at[n - 1]] - base));
+        std::memset(w, 0, 32);
+        w[0] = (uint32_t)base;
+        w[1] = (uint32_t)kb;
+        w += 8;
+        put_bits(w, kb, [&](int k) { return k < n ? (uint32_t)(key[at[k]] - base) : 0u; });
+        w += 8 * kb;
+        for (int j = 0; j < nin; ++j) {
+            const int32_t* col = idx + (int64_t)in_mode[j] * nnz;
+            put_bits(w, bits[j], [&](int k) { return k < n ? (uint32_t)col[at[k]] : 0u; });
+            w += 8 * bits[j];
+        }
+        for (int k = 0; k < kPackBlock; ++k) {
+            const float x = k < n ? val[at[k]] : 0.f;
+            std::memcpy(w + k, &x, 4);
+        }
+    }
+}
+
+int32_t PackedMode::out_index(int64_t p) const
+{
+    const uint32_t* w = data + (int64_t)offset[p / kPackBlock] * 8;
+    return (int32_t)(w[0] + get_bits(w + 8, p % kPackBlock, (int)w[1]));
+}
+
+int32_t PackedMode::in_index(int j, int64_t p) const
+{
+    const uint32_t* w = data + (int64_t)offset[p / kPackBlock] * 8;
+    int64_t at = 8 + 8 * (int64_t)w[1];
+    for (int i = 0; i < j; ++i) at += 8 * bits[i];
+    return (int32_t)get_bits(w + at, p % kPackBlock, bits[j]);
+}
+
+void PackedMode::unpack(int64_t nnz, int32_t* out_idx, int32_t* in_idx, float* val) const
 {
 #pragma omp parallel for schedule(static)
-    for (int64_t p = p0; p < p1; ++p) dst[p - p0] = src[perm[p]];
+    for (int64_t b = 0; b < blocks(); ++b) {
+        const int64_t p0 = b * kPackBlock;
+        const int n = (int)std::min<int64_t>(kPackBlock, nnz - p0);
+        const uint32_t* w = data + (int64_t)offset[b] * 8;
+        const int32_t base = (int32_t)w[0];
+        const int kb = (int)w[1];
+        w += 8;
+        for (int k = 0; k < n && out_idx; ++k) out_idx[p0 + k] = base + (int32_t)get_bits(w, k, kb);
+        w += 8 * kb;
+        for (int j = 0; j < nin; ++j) {
+            for (int k = 0; k < n && in_idx; ++k) in_idx[(int64_t)j * nnz + p0 + k] = (int32_t)get_bits(w, k, bits[j]);
+            w += 8 * bits[j];
+        }
+        if (val) std::memcpy(val + p0, w, (size_t)n * 4);
+    }
 }
 
 }  // namespace amped

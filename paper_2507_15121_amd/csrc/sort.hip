@@ -560,6 +560,46 @@ hipError_t gather_any(const Split& s, bool pack, void* rec, const int32_t* perm,
 
 }  // namespace
 
+// ------------------------------------------------------------ packed layouts
+namespace {
+
+// A wave per block of 256 nonzeros; lane l unpacks its entries 4 l .. 4 l + 3 of
+// every column, from a 64-bit window each (the word after a column's last one is
+// the next column's or a value's), and stores them with one 16-byte store.
+__global__ void __launch_bounds__(256) unpack_kernel(UnpackArgs u)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (k >= u.blocks) return;
+    const uint32_t* w = u.packed + (int64_t)(u.offset[u.first + k] - u.offset[u.first]) * 8;
+    const uint32_t base = w[0], kb = w[1];
+    w += 8;
+    auto column = [&](uint32_t b, uint32_t add, int32_t* to) {
+        int v[4];
+        const uint32_t mask = b ? 0xFFFFFFFFu >> (32 - b) : 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t bit = (4 * lane + j) * b;
+            const uint64_t x = (uint64_t)w[(bit >> 5) + 1] << 32 | w[bit >> 5];
+            v[j] = (int)(((uint32_t)(x >> (bit & 31)) & mask) + add);
+        }
+        *reinterpret_cast<int4*>(to + k * kPackBlock + 4 * lane) = make_int4(v[0], v[1], v[2], v[3]);
+        w += 8 * b;
+    };
+    column(kb, base, u.to[0]);
+    for (int j = 0; j < u.order - 1; ++j) column((uint32_t)u.bits[j], 0u, u.to[1 + j]);
+    *reinterpret_cast<int4*>(u.to[u.order] + k * kPackBlock + 4 * lane) = *reinterpret_cast<const int4*>(w + 4 * lane);
+}
+
+}  // namespace
+
+hipError_t launch_unpack(const UnpackArgs& u, hipStream_t st)
+{
+    if (u.blocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(unpack_kernel, dim3((unsigned)((u.blocks + 3) / 4)), dim3(256), 0, st, u);
+    return hipGetLastError();
+}
+
 hipError_t launch_check_range(const int32_t* col, int64_t dim, int64_t n, unsigned long long* bad, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;

@@ -178,9 +178,12 @@ def _torch():
 
 
 def _stream_ptr(stream):
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    # the current device's current stream without a Stream object around it
+    # (0.5 instead of 3 us, a quarter of a small call)
+    C = _torch()._C
+    return ctypes.c_void_p(C._cuda_getCurrentRawStream(C._cuda_getDevice()))
 
 
 def _ptr_array(t: Tensor, factors: Sequence, dtype, skip: Optional[int]):

@@ -31,7 +31,7 @@ QSTATS_LIB = os.path.join(HERE, "libamped_qstats.so")
 # row-gather ceiling of the GPU (a program, not part of the library)
 CEILING_BIN = os.path.join(HERE, "gather_ceiling")
 
-HIP_SOURCES = ["kernels.hip", "k_mttkrp_f32.hip", "k_mttkrp_bf16.hip", "k_grad.hip", "k_grad_loss.hip", "k_loss.hip",
+HIP_SOURCES = ["kernels.hip", "k_mttkrp_f32.hip", "k_mttkrp_bf16.hip", "k_grad.hip", "k_grad_loss.hip", "k_loss.hip", "k_small.hip",
                "sort.hip", "als.hip"]
 HOST_SOURCES = ["api.cpp", "layout.cpp"]
 

@@ -414,6 +414,7 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
     struct Status {
         amped::RowTotals totals[kMaxOrder];
         unsigned long long bad[kMaxOrder];
+        int32_t small[kMaxOrder][2];   // split rows, most units of one
         unsigned unsorted, pad;
     } status;
     const size_t n = (size_t)nnz;
@@ -424,8 +425,14 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
     const size_t keep_bytes = Arena::step(words * 4) + Arena::step(aux_floats * 4) +
                               (nnz ? (size_t)order * (order + 1) * Arena::step(padded * 4) : 0) +
                               (t->keep_perm ? (size_t)order * Arena::step(n * 4) : 0);
+    // the units of the one-launch MTTKRP
+    const bool small = t->own_units && nnz > 0 && nnz <= amped::kSmallNnz;
+    const int small_len = amped::small_unit(nnz);
+    const size_t units = small ? (n + small_len - 1) / small_len : 0;
+    const size_t small_bytes = small ? (size_t)order * (2 * Arena::step((units + 1) * 4) + Arena::step(units * 8) +
+                                                        Arena::step(units * 4)) : 0;
     Arena ka, ta;
-    HIP_OR_FAIL(t->alloc(&keep, keep_bytes), "hipMalloc(layouts)");
+    HIP_OR_FAIL(t->alloc(&keep, keep_bytes + small_bytes), "hipMalloc(layouts)");
     ka.base = static_cast<char*>(keep);
     {
         unsigned* queues = ka.take<unsigned>(words);
@@ -588,6 +595,18 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
             }
             HIP_OR_FAIL(amped::launch_count_rows(t->mode[d].out_idx, nnz, dims[d], t->unit, counts[d],
                                                  &d_status->totals[d], stream), "row counts");
+            if (small) {
+                int32_t* cut = ka.take<int32_t>(units + 1);
+                int32_t* left = ka.take<int32_t>(units + 1);
+                int32_t* split = ka.take<int32_t>(2 * units);
+                unsigned* arrived = ka.take<unsigned>(units);
+                HIP_OR_FAIL(amped::launch_small_units(t->mode[d].out_idx, nnz, small_len, (int)units, cut, left, split,
+                                                      arrived, d_status->small[d], stream), "small units");
+                t->mode[d].small.cut = cut;
+                t->mode[d].small.left = left;
+                t->mode[d].small.split = split;
+                t->mode[d].small.arrived = arrived;
+            }
         }
         HIP_OR_FAIL(hipMemcpyAsync(&status, d_status, sizeof(status), hipMemcpyDeviceToHost, stream), "status");
         HIP_OR_FAIL(hipStreamSynchronize(stream), "layout build");
@@ -599,10 +618,17 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
 
         // the row lists, and the hot-row tables where launches use them
         const bool hot = nnz >= amped::kHotMinNnz;
+        // the shares of rows that span units, where the mode takes the one launch
+        auto one_launch = [&](int d) {
+            return small && status.small[d][1] <= (nnz <= amped::kSmallSplitNnz ? amped::kSmallSpan : 0);
+        };
+        auto share_bytes = [&](int d) {
+            return one_launch(d) && status.small[d][0] > 0 ? Arena::step(units * 2 * amped::kSmallCols * 4) : 0;
+        };
         size_t list_bytes = 0;
         for (int d = 0; d < order; ++d)
             list_bytes += Arena::step((size_t)(status.totals[d].shared + status.totals[d].lone) * 4) +
-                          Arena::step((size_t)status.totals[d].gaps * 8) +
+                          Arena::step((size_t)status.totals[d].gaps * 8) + share_bytes(d) +
                           (hot ? Arena::step(amped::kHotTableLen * 4) : 0);
         HIP_OR_FAIL(t->alloc(&p, list_bytes), "hipMalloc(row lists)");
         Arena la;
@@ -617,6 +643,12 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
             m.n_zero = tot.shared + tot.lone;
             m.n_gaps = tot.gaps;
             t->touched[d] = tot.touched;
+            if (one_launch(d)) {
+                m.small.n_units = (int)units;
+                m.small.zrows = zero + tot.shared;
+                m.small.n_zero = tot.lone;
+                if (status.small[d][0] > 0) m.small.share = la.take<float>(units * 2 * amped::kSmallCols);
+            }
             if (m.n_zero + m.n_gaps > 0)
                 HIP_OR_FAIL(amped::launch_fill_rows(m.out_idx, nnz, dims[d], t->unit, counts[d], tot.shared, zero, gaps,
                                                     stream), "row lists");

@@ -64,6 +64,25 @@ inline int64_t stream_work_unit(int64_t shard)
 #endif
 constexpr int64_t kHotMinNnz = AMPED_HOT_MIN_NNZ;
 
+// Tensors whose MTTKRP is one launch of one wave per unit (small_kernel).  The
+// unit's nominal length leaves at most 2048 units; a row of up to kSmallRow
+// nonzeros lies in one unit, longer ones span units, and their shares' round trip
+// takes 2 us or more: up to 2^17 nonzeros a mode takes the one launch unless a row
+// spans more than kSmallSpan units, up to 2^18 only if no row spans any.  Kernels
+// of a mode without and with the one launch: 2000 nonzeros at rank 16 9.3 and 6.0
+// us, 100k 9.1 and 6.6 us (uniform), 20k with heavy rows 9.3 and 9.2 us (and 2.5
+// us less in the call); 250k with every row split 10.2 and 9.0 us at rank 16, but
+// 19 and 22 us at 128; 500k 15.5 and 15.5 us at rank 32, 10.6 and 14.6 us split.
+#ifndef AMPED_SMALL_NNZ
+#define AMPED_SMALL_NNZ (int64_t(1) << 18)
+#endif
+constexpr int64_t kSmallNnz = AMPED_SMALL_NNZ;
+constexpr int64_t kSmallSplitNnz = int64_t(1) << 17;
+constexpr int kSmallRow = 192;
+constexpr int kSmallSpan = 64;
+constexpr int kSmallCols = 256;        // columns of a launch
+inline int small_unit(int64_t nnz) { return nnz <= (1 << 17) ? 64 : 128; }
+
 // Hot-row tables: for every power of two K <= kHotMax, a direct-mapped table
 // of K slots; slot s names the row r with r % K == s that the most nonzeros
 // use in this mode (kHotEmpty if no row maps to s).  The tables of all K are
@@ -153,6 +172,11 @@ hipError_t launch_count_rows(const int32_t* keys, int64_t n, int64_t rows, int64
                              RowTotals* totals, hipStream_t st);
 hipError_t launch_fill_rows(const int32_t* keys, int64_t n, int64_t rows, int64_t unit, const uint32_t* counts,
                             int64_t n_shared, int32_t* zero, int32_t* gaps, hipStream_t st);
+// The units of small_kernel from sorted keys: cut and left [units + 1], split and
+// arrived (zeroed) for at most `units` split rows; info[0] = split rows, info[1] =
+// most units of one.
+hipError_t launch_small_units(const int32_t* keys, int64_t n, int unit, int units, int32_t* cut, int32_t* left,
+                              int32_t* split, unsigned* arrived, int32_t* info, hipStream_t st);
 // Hot-row tables (kHotTableLen entries) from sorted keys; best: kHotMax zeros.
 hipError_t launch_hot_tables(const int32_t* keys, int64_t n, unsigned long long* best, int32_t* hot, hipStream_t st);
 // a[i] = i for i < n.
@@ -214,6 +238,17 @@ struct ModeDev {
     const int32_t* hot = nullptr;                  // hot-row tables of this mode [kHotTableLen]
     const void* zero_row = nullptr;                // 16 zero bytes
     float* sink = nullptr;                         // kSinkFloats floats of write-only scratch
+    // MTTKRP in one launch (n_units = 0: not for this mode)
+    struct Small {
+        int n_units = 0;
+        const int32_t* cut = nullptr;      // [n_units + 1] positions
+        const int32_t* left = nullptr;     // [n_units + 1] the split row that a cut lies in, or -1
+        const int32_t* split = nullptr;    // pairs: a split row's first unit, its number of units
+        unsigned* arrived = nullptr;       // per split row, 0 between launches
+        float* share = nullptr;            // [n_units][2][kSmallCols], when any row is split
+        const int32_t* zrows = nullptr;    // the untouched rows of the zero-row list
+        int64_t n_zero = 0;
+    } small;
     // A shard of a longer layout (whole chunks of it): the output indices just
     // before and after the shard, -1 at the layout's ends.  Rows that cross a
     // shard edge cross a chunk edge, so they are in the zero-row list and every

@@ -1036,6 +1036,56 @@ mttkrp_kernel(const KParams p)
 
 using KernelFn = void (*)(const KParams);
 
+// Zeroes listed rows and (start, length) ranges of rows, all blocks of the grid
+// together (a range, at most about kGapPiece rows, is one block's work).  vec4:
+// ld, col0 and ncols are multiples of 4 (16-byte stores).
+__device__ __forceinline__ void zero_rows(float* out, int64_t ld, int col0, int ncols, bool vec4, const int32_t* zrows,
+                                          int64_t n_zero, const int32_t* gaps, int64_t n_gaps)
+{
+    const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
+    const int nv = vec4 ? ncols / 4 : ncols;  // stores per row
+    const int64_t total = n_zero * nv;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += nthreads) {
+        const int64_t r = zrows[i / nv];
+        const int j = (int)(i % nv);
+        if (vec4) *reinterpret_cast<float4*>(out + r * ld + col0 + 4 * j) = make_float4(0.f, 0.f, 0.f, 0.f);
+        else out[r * ld + col0 + j] = 0.f;
+    }
+    for (int64_t gi = blockIdx.x; gi < n_gaps; gi += gridDim.x) {
+        const int64_t start = gaps[2 * gi], len = gaps[2 * gi + 1];
+        const int64_t n = len * nv;
+        for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
+            const int64_t r = start + i / nv;
+            const int j = (int)(i % nv);
+            if (vec4) *reinterpret_cast<float4*>(out + r * ld + col0 + 4 * j) = make_float4(0.f, 0.f, 0.f, 0.f);
+            else out[r * ld + col0 + j] = 0.f;
+        }
+    }
+}
+
+// MTTKRP in one launch (small_kernel).
+struct SmallParams {
+    const int32_t* out_idx;
+    const int32_t* in_idx[kMaxIn];
+    const float* val;
+    const void* fac[kMaxIn];
+    uint32_t fbytes[kMaxIn];
+    float* out;
+    int64_t ld;
+    int nnz, col0, ncols;
+    int n_units;
+    const int32_t* cut;      // [n_units + 1] positions
+    const int32_t* left;     // [n_units + 1] the split row that cut k lies in, or -1
+    const int32_t* split;    // per split row: its first unit, its number of units
+    unsigned* arrived;       // per split row, 0 between launches
+    float* share;            // [n_units][2][kSmallCols]
+    bool vec4;
+    const int32_t* zrows;
+    const int32_t* gaps;
+    int64_t n_zero, n_gaps;
+};
+using SmallFn = void (*)(const SmallParams);
+
 // Vector instances exist for up to 4 input modes; every other case takes the
 // column-tile path.
 constexpr int kMaxVecNin = 4;
@@ -1053,6 +1103,7 @@ KernelFn pick_mttkrp_bf16(int nin, Lanes v, bool buf);
 KernelFn pick_grad(int nin, Lanes v, bool buf);
 KernelFn pick_loss(int nin, Lanes v, bool buf);
 KernelFn pick_grad_loss(int nin, Lanes v, bool buf);
+SmallFn pick_small(int nin, FactorType ft, Lanes v);
 
 template <int NIN, int LPR, int RPL, typename T, int KIND>
 KernelFn pick_buf(bool exact, bool buf)

@@ -55,27 +55,7 @@ __global__ void __launch_bounds__(kBlock) init_kernel(float* out, int64_t ld, in
         if (queue && threadIdx.x < kQueueSlots) queue[threadIdx.x * kQueueStride] = 0u;
         if (loss && threadIdx.x == 0) *loss = 0.0;
     }
-    if (!out) return;
-    const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
-    const int nv = vec4 ? ncols / 4 : ncols;  // stores per row
-    const int64_t total = n_zero * nv;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += nthreads) {
-        const int64_t r = zrows[i / nv];
-        const int j = (int)(i % nv);
-        if (vec4) *reinterpret_cast<float4*>(out + r * ld + col0 + 4 * j) = make_float4(0.f, 0.f, 0.f, 0.f);
-        else out[r * ld + col0 + j] = 0.f;
-    }
-    // one (start, length) range per workgroup, at most about kGapPiece rows
-    for (int64_t gi = blockIdx.x; gi < n_gaps; gi += gridDim.x) {
-        const int64_t start = gaps[2 * gi], len = gaps[2 * gi + 1];
-        const int64_t n = len * nv;
-        for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-            const int64_t r = start + i / nv;
-            const int j = (int)(i % nv);
-            if (vec4) *reinterpret_cast<float4*>(out + r * ld + col0 + 4 * j) = make_float4(0.f, 0.f, 0.f, 0.f);
-            else out[r * ld + col0 + j] = 0.f;
-        }
-    }
+    if (out) zero_rows(out, ld, col0, ncols, vec4, zrows, n_zero, gaps, n_gaps);
 }
 
 // A factor of `rows` rows is read through a 32-bit buffer offset when one
@@ -290,6 +270,45 @@ hipError_t launch_permute32(void* dst, const void* src, const int32_t* perm, int
     return hipGetLastError();
 }
 
+// MTTKRP of a small tensor in one launch per column tile.
+static hipError_t launch_small(const LaunchArgs& a, SmallFn fn, int tile, int eb)
+{
+    const ModeDev& m = *a.m;
+    SmallParams k{};
+    k.out_idx = m.out_idx;
+    for (int w = 0; w < a.nin; ++w) {
+        k.in_idx[w] = m.in_idx[w];
+        k.fac[w] = a.in_factors[w];
+        k.fbytes[w] = (uint32_t)((uint64_t)a.in_rows[w] * a.rank * eb);
+    }
+    k.val = m.val;
+    k.out = a.out;
+    k.ld = a.rank;
+    k.nnz = (int)m.nnz;
+    k.n_units = m.small.n_units;
+    k.cut = m.small.cut;
+    k.left = m.small.left;
+    k.split = m.small.split;
+    k.arrived = m.small.arrived;
+    k.share = m.small.share;
+    k.zrows = m.small.zrows;
+    k.n_zero = m.small.n_zero;
+    k.gaps = m.gaps;
+    k.n_gaps = m.n_gaps;
+    for (int col0 = 0; col0 < a.rank; col0 += tile) {
+        k.col0 = col0;
+        k.ncols = std::min(tile, a.rank - col0);
+        k.vec4 = a.rank % 4 == 0 && col0 % 4 == 0 && k.ncols % 4 == 0;
+        // blocks beside the units' for the untouched rows: 8 stores per lane, or a range
+        const int64_t stores = (k.n_zero * (k.vec4 ? k.ncols / 4 : k.ncols) + 511) / 512;
+        const int64_t grid = std::max<int64_t>(k.n_units, std::min<int64_t>(4096, std::max(stores, k.n_gaps)));
+        void* args[] = {&k};
+        hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)grid), dim3(64), args, 0, a.stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_mttkrp(const LaunchArgs& a)
 {
     const ModeDev& m = *a.m;
@@ -306,6 +325,8 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
     int tile = parts == 1 ? a.rank : ((a.rank + parts - 1) / parts + 3) & ~3;
     Lanes v = choose_lanes(tile, a.ftype, a.nin);
     if (tile != a.rank) v.exact = false;
+    if (!grad && buf && v.lpr && m.small.n_units > 0)
+        if (SmallFn small = pick_small(a.nin, a.ftype, v)) return launch_small(a, small, tile, eb);
     // An exact rank's instance with the hot-row cache is used where the cache
     // is; the residual forms (no cache) always take the exact one.
     if (!grad && buf && m.nnz < kHotMinNnz) v.exact = false;

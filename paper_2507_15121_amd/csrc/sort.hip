@@ -533,6 +533,79 @@ __global__ void __launch_bounds__(kHotMax) hot_tables(const unsigned long long* 
     }
 }
 
+// ------------------------------------------------------------------ small units
+// One block.  Cut k is the start of the row at position k * unit, or that position
+// itself inside a row longer than kSmallRow (a split row).  Such a row's units
+// are the one before its first cut to the one after its last.
+__global__ void __launch_bounds__(1024) small_units(const int32_t* keys, int n, int unit, int units, int32_t* cut,
+                                                    int32_t* left, int32_t* split, unsigned* arrived, int32_t* info)
+{
+    __shared__ int s_sum[1024];
+    __shared__ int s_most;
+    const int tid = threadIdx.x;
+    if (tid == 0) s_most = 0;
+    const int per = (units + 1 + 1023) / 1024;
+    const int k0 = min(units + 1, tid * per), k1 = min(units + 1, k0 + per);
+    // left[k] for now: the start of the split row that cut k lies in, or -1
+    for (int k = k0; k < k1; ++k) {
+        const int x = (int)min((int64_t)k * unit, (int64_t)n);
+        int c = x, in = -1;
+        if (x < n) {
+            const int32_t row = keys[x];
+            int lo = -1, hi = x;                     // first position of the row
+            while (hi - lo > 1) {
+                const int mid = lo + (hi - lo) / 2;
+                if (keys[mid] < row) lo = mid;
+                else hi = mid;
+            }
+            // longer than kSmallRow: its entry kSmallRow past the first is still the row
+            if (hi + kSmallRow < n && keys[hi + kSmallRow] == row) in = x > hi ? hi : -1;
+            else c = hi;
+        }
+        cut[k] = c;
+        left[k] = in;
+    }
+    __syncthreads();
+    // split rows in order: cut k is the first of its row
+    auto first = [&](int k) { return left[k] >= 0 && left[k - 1] != left[k]; };   // left[0] = -1
+    int c = 0;
+    for (int k = max(k0, 1); k < k1; ++k) c += first(k);
+    s_sum[tid] = c;
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {
+        const int y = tid >= off ? s_sum[tid - off] : 0;
+        __syncthreads();
+        s_sum[tid] += y;
+        __syncthreads();
+    }
+    int id = s_sum[tid] - c;
+    // (the rows' starts stay in left[] until every thread has read them)
+    for (int k = max(k0, 1); k < k1; ++k)
+        if (first(k)) {
+            int e = k + 1;
+            while (e <= units && left[e] == left[k]) ++e;
+            split[2 * id] = k - 1;
+            split[2 * id + 1] = e - k + 1;
+            arrived[id] = 0u;
+            atomicMax(&s_most, e - k + 1);
+            ++id;
+        }
+    __syncthreads();
+    // left[k] = the row's id: those of earlier threads' rows come first
+    id = s_sum[tid] - c - 1;
+    int32_t own[8];   // per <= 5 (units <= 4096)
+    for (int k = k0; k < k1; ++k) {
+        if (k >= 1 && first(k)) ++id;
+        own[k - k0] = left[k] >= 0 ? id : -1;
+    }
+    __syncthreads();
+    for (int k = k0; k < k1; ++k) left[k] = own[k - k0];
+    if (tid == 0) {
+        info[0] = s_sum[1023];
+        info[1] = s_most;
+    }
+}
+
 int stream_grid(int64_t n, int per_thread)
 {
     const int64_t per_block = (int64_t)kSortBlock * per_thread;
@@ -631,6 +704,14 @@ hipError_t launch_gather_records(int order, const void* rec, const int32_t* perm
     s.words = order + 1;
     for (int j = 0; j <= order; ++j) s.to[j] = static_cast<uint32_t*>(cols[j]);
     return gather_any(s, false, const_cast<void*>(rec), perm, n, st);
+}
+
+hipError_t launch_small_units(const int32_t* keys, int64_t n, int unit, int units, int32_t* cut, int32_t* left,
+                              int32_t* split, unsigned* arrived, int32_t* info, hipStream_t st)
+{
+    if (n < 1 || n > kSmallNnz || units < 1 || units > 4096) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(small_units, dim3(1), dim3(1024), 0, st, keys, (int)n, unit, units, cut, left, split, arrived, info);
+    return hipGetLastError();
 }
 
 int row_list_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>((n + 4095) / 4096, 2048)); }

@@ -226,6 +226,22 @@ amped_status amped_cp_grad(amped_tensor_t t, int mode, int rank, const float *co
                            float scale, float *grad, void *stream);
 
 /*
+ * amped_cp_grad with scale * (*dev_scale) in place of scale: the factor dL_out of
+ * a backward pass stays on the device, so the host does not wait for it.
+ *   dev_scale  DEVICE, one double, read by the launch
+ */
+amped_status amped_cp_grad_scaled(amped_tensor_t t, int mode, int rank, const float *const *factors,
+                                  float scale, const double *dev_scale, float *grad, void *stream);
+
+/*
+ * x[i] *= (float)*dev_scale for i < n: the factor dL_out of a gradient that
+ * amped_cp_loss_grad gave before it was known.  x is left alone when it is 1.
+ *   x          DEVICE, n floats, 16-byte aligned
+ *   dev_scale  DEVICE, one double
+ */
+amped_status amped_scale(float *x, int64_t n, const double *dev_scale, void *stream);
+
+/*
  * amped_cp_grad and amped_cp_loss in one pass over the layout of `mode` (the
  * CP model of Sec. 2.1 and the gradient of its loss): every mode's layout
  * holds every stored entry, so the residuals e(k) the gradient recomputes

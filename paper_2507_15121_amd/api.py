@@ -21,7 +21,7 @@ STATUS_NAMES = {0: "OK", 1: "INVALID", 2: "RANGE", 3: "NOMEM", 4: "HIP", 5: "UNS
 # every symbol declared in include/amped.h
 EXPORTED = ["amped_tensor_create", "amped_tensor_destroy", "amped_tensor_info", "amped_tensor_layout",
             "amped_layout_host", "amped_mttkrp", "amped_mttkrp_bf16", "amped_cp_loss", "amped_cp_grad",
-            "amped_cp_loss_grad", "amped_gram", "amped_gram_noalloc", "amped_cp_als_sweep", "amped_last_error", "amped_version"]
+            "amped_cp_grad_scaled", "amped_scale", "amped_cp_loss_grad", "amped_gram", "amped_gram_noalloc", "amped_cp_als_sweep", "amped_last_error", "amped_version"]
 
 
 class AmpedError(RuntimeError):
@@ -57,6 +57,8 @@ def lib():
         L.amped_mttkrp_bf16.argtypes = [vp, i32, i32, pvp, vp, vp]
         L.amped_cp_loss.argtypes = [vp, i32, pvp, vp, vp]
         L.amped_cp_grad.argtypes = [vp, i32, i32, pvp, ctypes.c_float, vp, vp]
+        L.amped_cp_grad_scaled.argtypes = [vp, i32, i32, pvp, ctypes.c_float, vp, vp, vp]
+        L.amped_scale.argtypes = [vp, i64, vp, vp]
         L.amped_cp_loss_grad.argtypes = [vp, i32, i32, pvp, ctypes.c_float, vp, vp, vp]
         L.amped_gram.argtypes = [vp, i64, i32, vp, vp]
         L.amped_gram_noalloc.argtypes = [vp, i64, i32, vp, vp]
@@ -263,6 +265,36 @@ def cp_grad(t: Tensor, mode: int, factors, scale: float, out=None, stream=None):
     _check(lib().amped_cp_grad(t.handle, int(mode), rank, ptrs, ctypes.c_float(scale),
                                ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream)))
     return out
+
+
+def cp_grad_scaled(t: Tensor, mode: int, factors, scale: float, dev_scale, out=None, stream=None):
+    """cp_grad() with scale times a 0-dim float64 device tensor, which the host
+    does not wait for."""
+    torch = _torch()
+    ptrs, rank = _ptr_array(t, factors, torch.float32, None)
+    out = _out(t, mode, rank, out, factors[0])
+    _one_double(dev_scale)
+    _check(lib().amped_cp_grad_scaled(t.handle, int(mode), rank, ptrs, ctypes.c_float(scale),
+                                      ctypes.c_void_p(dev_scale.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+                                      _stream_ptr(stream)))
+    return out
+
+
+def scale_(x, dev_scale, stream=None):
+    """x *= dev_scale in place (float32 device tensor times a 0-dim float64 one);
+    x is left alone when the factor is 1."""
+    torch = _torch()
+    if x.dtype != torch.float32 or not x.is_cuda or not x.is_contiguous():
+        raise ValueError("x must be a contiguous float32 CUDA/HIP tensor")
+    _one_double(dev_scale)
+    _check(lib().amped_scale(ctypes.c_void_p(x.data_ptr()), x.numel(), ctypes.c_void_p(dev_scale.data_ptr()),
+                             _stream_ptr(stream)))
+    return x
+
+
+def _one_double(s):
+    if s.dtype != _torch().float64 or s.numel() != 1 or not s.is_cuda:
+        raise ValueError("the scale must be one float64 on the device")
 
 
 def cp_loss_grad(t: Tensor, mode: int, factors, scale: float, out=None, loss=None, stream=None):

@@ -9,7 +9,8 @@ rows: nothing per nonzero is kept between the passes.
 
 ``SparseCPLoss`` evaluates the loss alone in its forward pass
 (``amped_cp_loss``) and every needed gradient in backward (``amped_cp_grad``
-with scale = -2 * grad_output).  ``sparse_cp_loss`` picks, when autograd will
+with scale = -2 * grad_output, which stays on the device: a backward that read
+it on the host first waited for the whole forward pass).  ``sparse_cp_loss`` picks, when autograd will
 need gradients, ``SparseCPLossFused``: its forward pass runs
 ``amped_cp_loss_grad``, which yields the loss and the first needed mode's
 gradient (unscaled by grad_output) in one pass, and keeps that gradient until
@@ -35,19 +36,16 @@ class SparseCPLoss(torch.autograd.Function):
         t = ctx.tensor
         early = ctx.early
         ctx.early = None
-        scale = None
+        grad_out = grad_out.detach()
         grads = [None]
         for d in range(len(factors)):
             if not ctx.needs_input_grad[d + 1]:
                 grads.append(None)
             elif early is not None and early[0] == d:
-                # -2 * MTTKRP_d(E) from the forward pass, times dL_out on the device
-                grads.append(early[1].mul_(grad_out))
+                # -2 * MTTKRP_d(E) from the forward pass, times dL_out
+                grads.append(api.scale_(early[1], grad_out))
             else:
-                if scale is None:
-                    # the loss is float64 on the device; the gradient scale is read once
-                    scale = -2.0 * float(grad_out)
-                grads.append(api.cp_grad(t, d, factors, scale))
+                grads.append(api.cp_grad_scaled(t, d, factors, -2.0, grad_out))
         return tuple(grads)
 
 

@@ -990,7 +990,8 @@ amped_status check_call(amped_tensor_t t, int mode, int rank, const void* const*
 }
 
 amped_status run_mttkrp(amped_tensor_t t, int mode, int rank, const void* const* factors, float* out, void* stream,
-                        amped::FactorType ft, amped::Kind kind, float scale, double* loss = nullptr)
+                        amped::FactorType ft, amped::Kind kind, float scale, double* loss = nullptr,
+                        const double* dev_scale = nullptr)
 {
     const bool grad = (kind != amped::Kind::Mttkrp);
     amped_status st = check_call(t, mode, rank, factors, out, grad, grad ? "grad" : "out");
@@ -1013,6 +1014,7 @@ amped_status run_mttkrp(amped_tensor_t t, int mode, int rank, const void* const*
         }
     a.own_factor = grad ? static_cast<const float*>(factors[mode]) : nullptr;
     a.scale = scale;
+    a.dev_scale = dev_scale;
     a.out = out;
     a.loss = loss;
     a.stream = static_cast<hipStream_t>(stream);
@@ -1052,6 +1054,28 @@ amped_status amped_cp_grad(amped_tensor_t t, int mode, int rank, const float* co
     g_err.clear();
     return run_mttkrp(t, mode, rank, reinterpret_cast<const void* const*>(factors), grad, stream,
                       amped::FactorType::F32, amped::Kind::ResidualGrad, scale);
+}
+
+amped_status amped_cp_grad_scaled(amped_tensor_t t, int mode, int rank, const float* const* factors, float scale,
+                                  const double* dev_scale, float* grad, void* stream)
+{
+    g_err.clear();
+    if (!dev_scale) return fail(AMPED_ERR_INVALID, "dev_scale is NULL");
+    return run_mttkrp(t, mode, rank, reinterpret_cast<const void* const*>(factors), grad, stream,
+                      amped::FactorType::F32, amped::Kind::ResidualGrad, scale, nullptr, dev_scale);
+}
+
+amped_status amped_scale(float* x, int64_t n, const double* dev_scale, void* stream)
+{
+    g_err.clear();
+    if (n < 0) return fail(AMPED_ERR_INVALID, "n = %lld < 0", (long long)n);
+    if (n > 0 && (!x || !dev_scale)) return fail(AMPED_ERR_INVALID, "x or dev_scale is NULL");
+    if (!aligned16(x)) return fail(AMPED_ERR_INVALID, "x is not 16-byte aligned");
+    int dev = 0;
+    amped_status st = check_device(&dev);
+    if (st != AMPED_OK) return st;
+    hipError_t e = amped::launch_scale(x, n, dev_scale, static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? AMPED_OK : hip_fail(e, "amped_scale");
 }
 
 amped_status amped_cp_loss_grad(amped_tensor_t t, int mode, int rank, const float* const* factors, float scale,

@@ -272,6 +272,7 @@ struct LaunchArgs {
     const int32_t* in_hot[kMaxOrder - 1] = {};     // their hot-row tables
     const float* own_factor = nullptr;             // factor of the output mode (ResidualGrad)
     float scale = 1.0f;                            // ResidualGrad output scale
+    const double* dev_scale = nullptr;             // a device-resident factor of it (nullable)
     float* out = nullptr;
     double* loss = nullptr;                        // ResidualGradLoss: fp64 loss
     bool loss_accumulate = false;                  // add to *loss instead of resetting it
@@ -281,6 +282,9 @@ struct LaunchArgs {
 // Enqueue init + MTTKRP (or fused residual gradient).  Returns hipSuccess or the
 // launch error.
 hipError_t launch_mttkrp(const LaunchArgs& a);
+
+// x[i] *= (float)*s for i < n; nothing is read or written when *s is 1.
+hipError_t launch_scale(float* x, int64_t n, const double* s, hipStream_t st);
 
 // Enqueue the CP loss over the given layout (any mode's layout holds every
 // nonzero once).  all_factors are in mode order with the layout's output mode

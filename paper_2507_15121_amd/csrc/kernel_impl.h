@@ -118,6 +118,7 @@ struct KParams {
     int col0;       // first column handled by this launch
     int ncols;      // columns handled by this launch
     float scale;
+    const double* dev_scale;  // multiplies scale (NULL: 1)
     uint32_t fbytes[kMaxIn];  // input factor sizes in bytes (buffer addressing)
     uint32_t own_bytes;
     const void* zero_row;     // 16 zero bytes: what padding entries read on the 64-bit path
@@ -507,7 +508,7 @@ mttkrp_kernel(const KParams p)
     const int over = EXACT ? 0 : p.col0 + s * RPL - c;   // leading columns that an earlier lane holds
     const uint64_t rb = (uint64_t)ld * sizeof(T);
     const uint64_t rb_own = (uint64_t)ld * sizeof(float);
-    const float oscale = GRAD ? p.scale : 1.0f;
+    const float oscale = !GRAD ? 1.0f : p.dev_scale ? (float)((double)p.scale * *p.dev_scale) : p.scale;
     const char* lbase[NIN];
 #pragma unroll
     for (int w = 0; w < NIN; ++w) lbase[w] = static_cast<const char*>(p.fac[w]) + (int64_t)c * sizeof(T);

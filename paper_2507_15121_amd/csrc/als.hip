@@ -241,10 +241,28 @@ constexpr double kSolveFp32MaxCond = 1e4;
 // as leave each one to four entries (16 above rank 96).  With the matrices in
 // LDS, or above rank 64 in global memory, and three barriers per pivot it took 62
 // us at rank 32 and about 5 ms at rank 100; now 19 us and 171 us (57 us at 64).
+//
+// Two launches of a small mode are left out.  With `nslab` partials given S is their
+// sum (in slab order, as gram_reduce adds up to 32 slabs).  With M given, every block
+// of the grid does the same algebra and then computes its own `per` rows of A = M W,
+// with als_solve's sums in its order; block 0 alone writes the R x R results (no block
+// reads G_d).  A sweep of 100k nonzeros at rank 16 takes 92.5 instead of 109.5 us.
+struct SmallMode {
+    const float* partial;    // [nslab][R][R], or NULL
+    int nslab;
+    const float* M;          // rows x R, or NULL
+    float* A;
+    int rows;
+    int per;                 // rows per block: at most kSolvePerThread entries per thread
+};
+constexpr int kFoldSlabs = 8;
+constexpr int kSolvePerThread = 4;
+constexpr int kSolveBlocks = 256;   // at most: one per CU
+
 template <int RA, int TI>
 __global__ void __launch_bounds__(TI * TI) als_small(double* G, const double* S, int N, int d, int R, double* T,
                                                      double* W, int* wide, double* lambda, int last,
-                                                     const double* xnorm2, double* fit)
+                                                     const double* xnorm2, double* fit, SmallMode mode)
 {
     constexpr int RP = RA * TI, NT = TI * TI, LD = RP + 1;
     constexpr bool ST = RP <= 64;                           // S, then T, in LDS too
@@ -255,8 +273,32 @@ __global__ void __launch_bounds__(TI * TI) als_small(double* G, const double* S,
     double(*const s_part)[RP] = reinterpret_cast<double(*)[RP]>(s_inv);   // TI x RP, until s_inv is filled
     const int tid = threadIdx.x, ti = tid / TI, tj = tid % TI;
     const int RR = R * R;
+    float* const s_m = reinterpret_cast<float*>(s_st + RP * LD);   // this block's rows of M
+    int rows_here = 0;
     if constexpr (ST) {
-        for (int e = tid; e < RR; e += NT) s_st[e / R * LD + e % R] = S[e];
+        if (mode.M) {
+            const int r0 = (int)blockIdx.x * mode.per;
+            rows_here = min(mode.per, mode.rows - r0);
+            const float* src = mode.M + (int64_t)r0 * R;
+#pragma unroll
+            for (int k = 0; k < kSolvePerThread; ++k) {
+                const int e = tid + k * NT;
+                if (e < rows_here * R) s_m[e] = src[e];
+            }
+        }
+        for (int e = tid; e < RR; e += NT) {
+            double x = 0.0;
+            if (mode.partial) {
+                float v[kFoldSlabs];
+#pragma unroll
+                for (int k = 0; k < kFoldSlabs; ++k) v[k] = k < mode.nslab ? mode.partial[k * RR + e] : 0.f;
+#pragma unroll
+                for (int k = 0; k < kFoldSlabs; ++k) x += (double)v[k];
+            } else {
+                x = S[e];
+            }
+            s_st[e / R * LD + e % R] = x;
+        }
     }
     auto row_of = [&](int x) { return ti + TI * x; };
     auto col_of = [&](int x) { return tj + TI * x; };
@@ -352,7 +394,9 @@ __global__ void __launch_bounds__(TI * TI) als_small(double* G, const double* S,
     // precision of the update's product M W (als_solve): fp32 sums while kappa
     // <= kSolveFp32MaxCond, fp64 sums above (or when kappa is not finite).
     const double kappa = vnorm * norm1(v);
-    if (tid == 0) *wide = (kappa <= kSolveFp32MaxCond) ? 0 : 1;   // NaN: fp64
+    const bool is_wide = !(kappa <= kSolveFp32MaxCond);   // NaN: fp64
+    const bool first = blockIdx.x == 0;
+    if (first && tid == 0) *wide = is_wide ? 1 : 0;
 #pragma unroll
     for (int i = 0; i < RA; ++i)
 #pragma unroll
@@ -411,7 +455,8 @@ __global__ void __launch_bounds__(TI * TI) als_small(double* G, const double* S,
         for (int j = 0; j < RA; ++j)
             if (row_of(i) == col_of(j)) s_lam[row_of(i)] = p[i][j] > 0.0 ? sqrt(p[i][j]) : 0.0;
     __syncthreads();
-    for (int r = tid; r < R; r += NT) lambda[r] = s_lam[r];
+    if (first)
+        for (int r = tid; r < R; r += NT) lambda[r] = s_lam[r];
     double xh = 0.0;
 #pragma unroll
     for (int i = 0; i < RA; ++i)
@@ -421,8 +466,11 @@ __global__ void __launch_bounds__(TI * TI) als_small(double* G, const double* S,
             if (r >= R || c >= R) continue;
             const double lr = s_lam[r], lc = s_lam[c];
             const double g = (lr > 0.0 && lc > 0.0) ? p[i][j] / (lr * lc) : 0.0;
+            const double x = lc > 0.0 ? v[i][j] / lc : 0.0;
+            if constexpr (ST) s_inv[r * LD + c] = x;   // V^{-1} is no longer read
+            if (!first) continue;
             G[(int64_t)d * RR + r * R + c] = g;
-            W[r * R + c] = lc > 0.0 ? v[i][j] / lc : 0.0;
+            W[r * R + c] = x;
             if (last) {
                 double h = g;
                 for (int w = 0; w < N; ++w)
@@ -430,7 +478,7 @@ __global__ void __launch_bounds__(TI * TI) als_small(double* G, const double* S,
                 xh += lr * lc * h;
             }
         }
-    if (last) {
+    if (last && first) {
         // <X, Xhat> = sum_r lambda_r (S W)_rr = trace(S V^{-1}) over columns
         // with lambda_r > 0; ||Xhat||^2 = lambda^T (Hadamard of all G) lambda,
         // its per-thread sums added in a fixed order.
@@ -445,6 +493,27 @@ __global__ void __launch_bounds__(TI * TI) als_small(double* G, const double* S,
             const double x2 = *xnorm2;
             const double res = x2 - 2.0 * inner + model;
             *fit = x2 > 0.0 ? 1.0 - sqrt(res > 0.0 ? res : 0.0) / sqrt(x2) : 0.0;
+        }
+    }
+    if constexpr (ST) {
+        if (mode.M) {
+            __syncthreads();
+            float* dst = mode.A + (int64_t)blockIdx.x * mode.per * R;
+            for (int e = tid; e < rows_here * R; e += NT) {
+                const int c = e % R;
+                const float* m = s_m + (e - c);
+                if (is_wide) {
+                    double x = 0.0;
+#pragma unroll 4
+                    for (int k = 0; k < R; ++k) x = fma((double)m[k], s_inv[k * LD + c], x);
+                    dst[e] = (float)x;
+                } else {
+                    float x = 0.f;
+#pragma unroll 8
+                    for (int k = 0; k < R; ++k) x = fmaf(m[k], (float)s_inv[k * LD + c], x);
+                    dst[e] = x;
+                }
+            }
         }
     }
 }
@@ -610,7 +679,8 @@ int64_t als_gram_slabs(int64_t rows, int R)
     return std::max<int64_t>(gram_slabs(rows), n);
 }
 
-static hipError_t launch_gram_set(GramSet& set, const int64_t* nslab, int R, float* partial, hipStream_t st)
+static hipError_t launch_gram_set(GramSet& set, const int64_t* nslab, int R, float* partial, hipStream_t st,
+                                  bool reduce = true)
 {
     if (R < 1 || R > 128 || set.n < 1 || set.n > kGramMany) return hipErrorInvalidValue;
     set.begin[0] = 0;
@@ -628,7 +698,7 @@ static hipError_t launch_gram_set(GramSet& set, const int64_t* nslab, int R, flo
     case 3: hipLaunchKernelGGL(gram_partial<3>, grid, dim3(256), 0, st, set, R, partial); break;
     default: hipLaunchKernelGGL(gram_partial<4>, grid, dim3(256), 0, st, set, R, partial); break;
     }
-    hipLaunchKernelGGL(gram_reduce, dim3((R * R + 31) / 32, set.n), dim3(1024), 0, st, set, R, partial);
+    if (reduce) hipLaunchKernelGGL(gram_reduce, dim3((R * R + 31) / 32, set.n), dim3(1024), 0, st, set, R, partial);
     return hipGetLastError();
 }
 
@@ -708,13 +778,43 @@ hipError_t launch_gram_noalloc(const float* A, int64_t rows, int R, double* G, h
     return launch_gram(A, rows, R, ptr, G, st, nslab);
 }
 
-hipError_t launch_als_small(double* G, const double* S, int N, int d, int R, double* scratch, double* W, int* wide,
-                            double* lambda, bool last, const double* xnorm2, double* fit, hipStream_t st)
+static hipError_t launch_als_solve(const float* M, const double* W, const int* wide, float* A, int64_t rows, int R,
+                                   hipStream_t st);
+
+hipError_t launch_als_update(const float* M, float* A, int64_t rows, float* partial, double* G, double* S, int N, int d,
+                             int R, double* scratch, double* W, int* wide, double* lambda, bool last,
+                             const double* xnorm2, double* fit, hipStream_t st)
 {
+    const int64_t nslab = als_gram_slabs(rows, R);
+    SmallMode mode{};
+    GramSet set{};
+    set.n = 1;
+    set.A[0] = M;
+    set.rows[0] = rows;
+    set.G[0] = S;
+    const bool fold = R <= 64 && nslab <= kFoldSlabs;
+    hipError_t e = launch_gram_set(set, &nslab, R, partial, st, !fold);
+    if (e != hipSuccess) return e;
+    if (fold) {
+        mode.partial = partial;
+        mode.nslab = (int)nslab;
+    }
+    // rank 64's block has 1024 threads, so 4096 entries of M; up to rank 32 it has 256
+    const int block = R <= 32 ? 256 : 1024;
+    const int64_t per = std::max(1, kSolvePerThread * block / R);
+    const int64_t nblock = (rows + per - 1) / per;
+    const bool solve = R <= 64 && nblock <= kSolveBlocks;
+    if (solve) {
+        mode.M = M;
+        mode.A = A;
+        mode.rows = (int)rows;
+        mode.per = (int)per;
+    }
     auto launch = [&](auto kernel, int rp, int threads) {
-        const size_t lds = (size_t)rp * (rp + 1) * sizeof(double) * (rp <= 64 ? 2 : 1);
-        hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), lds, st, G, S, N, d, R, scratch, W, wide, lambda,
-                           last ? 1 : 0, xnorm2, fit);
+        const size_t lds = (size_t)rp * (rp + 1) * sizeof(double) * (rp <= 64 ? 2 : 1) +
+                           (rp <= 64 ? (size_t)kSolvePerThread * threads * sizeof(float) : 0);
+        hipLaunchKernelGGL(kernel, dim3(solve ? (unsigned)nblock : 1), dim3(threads), lds, st, G, S, N, d, R, scratch,
+                           W, wide, lambda, last ? 1 : 0, xnorm2, fit, mode);
     };
     // one to four entries per thread while the block has them: fewer waves have
     // cheaper barriers but more arithmetic per pivot (rank 32: one wave of 16
@@ -724,10 +824,11 @@ hipError_t launch_als_small(double* G, const double* S, int N, int d, int R, dou
     else if (R <= 64) launch(als_small<2, 32>, 64, 1024);
     else if (R <= 96) launch(als_small<3, 32>, 96, 1024);
     else launch(als_small<4, 32>, 128, 1024);
-    return hipGetLastError();
+    if ((e = hipGetLastError()) != hipSuccess || solve) return e;
+    return launch_als_solve(M, W, wide, A, rows, R, st);
 }
 
-hipError_t launch_als_solve(const float* M, const double* W, const int* wide, float* A, int64_t rows, int R,
+static hipError_t launch_als_solve(const float* M, const double* W, const int* wide, float* A, int64_t rows, int R,
                             hipStream_t st)
 {
     if (rows <= 0) return hipSuccess;

@@ -1217,13 +1217,9 @@ amped_status amped_cp_als_sweep(amped_tensor_t t, int rank, float* const* factor
         st = run_mttkrp(t, d, rank, reinterpret_cast<const void* const*>(factors), w.M, stream,
                         amped::FactorType::F32, amped::Kind::Mttkrp, 1.0f);
         if (st != AMPED_OK) return st;
-        if ((e = amped::launch_als_grams(&w.M, &t->dims[d], 1, rank, w.partial, w.S, s)) != hipSuccess)
-            return hip_fail(e, "gram");
-        if ((e = amped::launch_als_small(w.G, w.S, N, d, rank, w.scratch, w.W, w.wide, lambda, d == N - 1,
-                                         w.xnorm2, fit, s)) != hipSuccess)
+        if ((e = amped::launch_als_update(w.M, factors[d], t->dims[d], w.partial, w.G, w.S, N, d, rank, w.scratch, w.W,
+                                          w.wide, lambda, d == N - 1, w.xnorm2, fit, s)) != hipSuccess)
             return hip_fail(e, "als update");
-        if ((e = amped::launch_als_solve(w.M, w.W, w.wide, factors[d], t->dims[d], rank, s)) != hipSuccess)
-            return hip_fail(e, "als solve");
     }
     w.have_grams = true;   // G now holds the Gram matrices of the factors just written
     return AMPED_OK;

@@ -333,8 +333,8 @@ struct Arena {
 // Copies host arrays to the device, in the order given, on a stream of its own.
 // A plain hipMemcpy of pageable memory reaches 28 GB/s here; the host threads
 // copying pieces of 8 MB into two pinned buffers, from which the copy engine reads
-// one while they fill the other, 53 GB/s, the host link's rate.  Arrays below a
-// piece are left to hipMemcpy.
+// one while they fill the other, 53 GB/s, the host link's rate.  A first array below
+// a piece is left to hipMemcpy.
 struct Uploader {
     static constexpr size_t kPiece = size_t(8) << 20;
     hipStream_t stream = nullptr;
@@ -345,7 +345,7 @@ struct Uploader {
 
     hipError_t put(void* dst, const void* src, size_t bytes)
     {
-        if (bytes < kPiece) return hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
+        if (bytes < kPiece && !stream) return hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
         hipError_t e = hipSuccess;
         if (!stream) {
             if ((e = hipStreamCreateWithFlags(&stream, hipStreamNonBlocking)) != hipSuccess) return e;
@@ -377,30 +377,42 @@ struct Uploader {
         const int b = next ^ 1;   // the last piece's event
         return used[b] ? hipStreamWaitEvent(s, busy[b], 0) : hipSuccess;
     }
-    ~Uploader()
+    void finish()
     {
         if (stream) {
             (void)hipStreamSynchronize(stream);
             (void)hipStreamDestroy(stream);
         }
-        for (hipEvent_t ev : busy)
+        for (hipEvent_t& ev : busy) {
             if (ev) (void)hipEventDestroy(ev);
+            ev = nullptr;
+        }
         if (pinned) (void)hipHostFree(pinned);
+        stream = nullptr;
+        pinned = nullptr;
+        used[0] = used[1] = false;
     }
+    ~Uploader() { finish(); }
 };
 
 // Device-resident layouts, built on the device.
 //
-// The COO goes straight into mode 0's arrays.  Unless it is in lexicographic order
-// already, stable radix sorts over the modes, last mode first, give that order
-// (each starts when its column has arrived); a mode's order is one more stable
-// sort of it by i_d, whose sorted keys are the out_idx column, and the other
-// columns are gathered through it from one record per nonzero.  The row lists
-// come from the sorted keys too.  The host only copies the COO in and waits once
-// for the lists' sizes (and once for the order check of an input that looks
-// sorted).  The arrays are one allocation, the scratch another: with one for each
-// array, the keys copied back and the checks and lists made on the host, 5M
-// order-3 nonzeros took 17.7 ms and their release 3.2; now 3.6 and 0.3.
+// The index columns are copied in last mode first, the values after them.  Unless
+// the COO is in lexicographic order already, stable radix sorts over the modes, each
+// starting when its column has arrived, give that order; a mode's order is one more
+// stable sort of it by i_d, whose sorted keys are the out_idx column and give the
+// row lists.  All that is on its way while the values arrive; they go into
+// lexicographic order, and the modes' other columns are gathered from one record per
+// nonzero.  The host only copies and waits once for the lists' sizes (and once for
+// the order check of an input that looks sorted).
+// The arrays are one allocation, the scratch another of about a record per nonzero:
+// the raw columns lie where the records go, the sorts' buffers in columns of modes
+// that are gathered later, each mode's order in its own value column.  Allocating,
+// above all freeing, costs about 1.2 us per MB.
+// 5M order-3 nonzeros took 17.7 ms, and their release 3.2, with an allocation for
+// each array, the keys copied back and the checks and lists made on the host; 3.6 and
+// 0.3 with all of it on the device, the values first and a scratch of 180 MB; now
+// 2.9.
 amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, const float* values, int64_t cap)
 {
     const int order = t->order;
@@ -474,16 +486,17 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
             }
         }
 
-        // scratch: records (or, where they are larger and do not fit, a copy of the
-        // COO), two key and two value buffers for the sorts, the mode's order
-        const int rw = (int)amped::record_words(order);
+        // scratch: the raw COO and in its place the records (where those are larger
+        // and do not fit, columns are gathered one by one)
+        const int rw = (int)amped::record_words(order), last = order - 1;
         bool records = rw <= order + 1 || cap == 0;
         const int blocks = amped::row_list_blocks(nnz);
         const size_t scratch_words = (size_t)amped::sort_scratch_words(nnz);
         auto temp_bytes = [&](bool rec) {
             return Arena::step(sizeof(Status)) + (size_t)order * Arena::step((size_t)blocks * 16) +
-                   Arena::step(amped::kHotMax * 8) + Arena::step(scratch_words * 4) + 5 * Arena::step(n * 4) +
-                   (rec ? Arena::step((size_t)rw * 4 * n) : (size_t)(order + 1) * Arena::step(n * 4));
+                   Arena::step(amped::kHotMax * 8) + Arena::step(scratch_words * 4) +
+                   (order == 2 ? 2 * Arena::step(n * 4) : 0) +
+                   std::max(rec ? Arena::step((size_t)rw * 4 * n) : 0, (size_t)(order + 1) * Arena::step(n * 4));
         };
         hipError_t e = hipMalloc(&temp, temp_bytes(records));
         if (e != hipSuccess && records) {
@@ -498,116 +511,146 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
         for (int d = 0; d < order; ++d) counts[d] = ta.take<uint32_t>((size_t)blocks * 4);
         unsigned long long* best = ta.take<unsigned long long>(amped::kHotMax);
         uint32_t* scratch = ta.take<uint32_t>(scratch_words);
-        uint32_t* kbuf[2] = {ta.take<uint32_t>(n), ta.take<uint32_t>(n)};
-        int32_t* lex[2] = {ta.take<int32_t>(n), ta.take<int32_t>(n)};
-        int32_t* order_buf = ta.take<int32_t>(n);
-        uint32_t* rec = ta.take<uint32_t>(0);
-        uint32_t* raw[kMaxOrder + 1] = {};
-        if (!records)
-            for (int w = 0; w <= order; ++w) raw[w] = ta.take<uint32_t>(n);
+        // The sorts' second key buffer and second order buffer are columns of the last
+        // mode, the lexicographic order is one of mode 1's (order 2 has too few), and
+        // mode d's order lies where its values go: the gather's threads read an entry
+        // before they write that place.
+        uint32_t* const keys2 = reinterpret_cast<uint32_t*>(cols[last][0]);
+        int32_t* const order2 = order > 2 ? cols[last][1] : ta.take<int32_t>(n);
+        int32_t* const lex = order > 2 ? cols[1][0] : ta.take<int32_t>(n);
+        uint32_t* const rec = ta.take<uint32_t>(0);
+        int32_t* raw[kMaxOrder + 1];
+        for (int w = 0; w <= order; ++w) raw[w] = ta.take<int32_t>(n);
 
         HIP_OR_FAIL(hipStreamCreateWithFlags(&stream, hipStreamNonBlocking), "hipStreamCreate");
         std::memset(&status, 0, sizeof(status));
         for (int w = 0; w < order; ++w) status.bad[w] = ~0ull;
         HIP_OR_FAIL(hipMemcpy(d_status, &status, sizeof(status), hipMemcpyHostToDevice), "hipMemcpy(status)");
 
-        // the lexicographic order
-        int passes = 0;
-        for (int w = 0; w < order; ++w) passes += amped::sort_passes(bits_for(dims[w] - 1));
-        int at = -1, to = (passes - 1) & 1;   // lex[at] holds the order so far; the last pass writes lex[0]
+        // the lexicographic order, and in it mode 0's keys
+        int bits[kMaxOrder], np[kMaxOrder], passes = 0;
+        for (int w = 0; w < order; ++w) {
+            bits[w] = bits_for(dims[w] - 1);
+            np[w] = amped::sort_passes(bits[w]);
+            passes += np[w];
+        }
+        uint32_t* const kbuf[2] = {reinterpret_cast<uint32_t*>(cols[0][0]), keys2};
+        int32_t* const vbuf[2] = {lex, order2};
+        int at = -1, to = (passes - 1) & 1;   // vbuf[at] holds the order so far; the last pass writes vbuf[0]
         auto sort_by = [&](int w) -> hipError_t {
-            const int np = amped::sort_passes(bits_for(dims[w] - 1));
-            if (np == 0) return hipSuccess;
-            const uint32_t* keys = reinterpret_cast<const uint32_t*>(cols[0][w]);
+            if (np[w] == 0) return hipSuccess;
+            const uint32_t* keys = reinterpret_cast<const uint32_t*>(raw[w]);
             if (at >= 0) {
-                hipError_t er = amped::launch_permute32(kbuf[at], keys, lex[at], nnz, stream);
+                hipError_t er = amped::launch_permute32(kbuf[at], keys, vbuf[at], nnz, stream);
                 if (er != hipSuccess) return er;
                 keys = kbuf[at];
             }
-            hipError_t er = amped::launch_stable_sort(keys, at >= 0 ? lex[at] : nullptr, kbuf, lex, to, scratch, nnz,
-                                                      bits_for(dims[w] - 1), stream);
-            at = (to + np - 1) & 1;
+            hipError_t er = amped::launch_stable_sort(keys, at >= 0 ? vbuf[at] : nullptr, kbuf, vbuf, to, scratch, nnz,
+                                                      bits[w], stream);
+            at = (to + np[w] - 1) & 1;
             to = at ^ 1;
             return er;
         };
-        // a look at the first entries settles it for most unsorted inputs
+        auto copy = [&](void* dst, const void* src) {
+            return hipMemcpyAsync(dst, src, n * 4, hipMemcpyDeviceToDevice, stream);
+        };
+        bool sorted = amped::is_lexicographic_prefix(order, nnz, indices, std::min<int64_t>(nnz, 16384));
+        const bool looks_sorted = sorted;   // a look at the first entries settles it for most unsorted inputs
+        auto lex_column = [&](int w) -> hipError_t {
+            if (sorted || (w == 0 && np[0] > 0)) return hipSuccess;
+            return passes ? amped::launch_permute32(cols[0][w], raw[w], lex, nnz, stream) : copy(cols[0][w], raw[w]);
+        };
+        // the modes' orders and row lists' sizes from mode 0's index columns
+        auto mode_orders = [&]() -> hipError_t {
+            hipError_t er = hipSuccess;
+            for (int w = 0; w < order; ++w)
+                if ((er = lex_column(w)) != hipSuccess) return er;
+            for (int d = 0; d < order; ++d) {
+                if (d > 0 && np[d] > 0) {
+                    uint32_t* kb[2] = {reinterpret_cast<uint32_t*>(cols[d][d]), keys2};
+                    int32_t* vb[2] = {cols[d][order], order2};
+                    er = amped::launch_stable_sort(reinterpret_cast<const uint32_t*>(cols[0][d]), nullptr, kb, vb,
+                                                   (np[d] - 1) & 1, scratch, nnz, bits[d], stream);
+                } else if (d > 0) {
+                    er = copy(cols[d][d], cols[0][d]);
+                }
+                if (er != hipSuccess) return er;
+                if ((er = amped::launch_count_rows(cols[d][d], nnz, dims[d], t->unit, counts[d], &d_status->totals[d],
+                                                   stream)) != hipSuccess)
+                    return er;
+                if (small) {
+                    auto& sm = t->mode[d].small;
+                    int32_t* cut = ka.take<int32_t>(units + 1);
+                    int32_t* left = ka.take<int32_t>(units + 1);
+                    int32_t* split = ka.take<int32_t>(2 * units);
+                    unsigned* arrived = ka.take<unsigned>(units);
+                    if ((er = amped::launch_small_units(cols[d][d], nnz, small_len, (int)units, cut, left, split,
+                                                        arrived, d_status->small[d], stream)) != hipSuccess)
+                        return er;
+                    sm.cut = cut;
+                    sm.left = left;
+                    sm.split = split;
+                    sm.arrived = arrived;
+                }
+            }
+            return er;
+        };
         Uploader up;
-        bool lexi = amped::is_lexicographic_prefix(order, nnz, indices, std::min<int64_t>(nnz, 16384));
-        const bool early = !lexi;
-        for (int w = order; w >= 0; --w) {
-            const void* src = w < order ? static_cast<const void*>(indices + (int64_t)w * nnz) : values;
-            HIP_OR_FAIL(up.put(cols[0][w], src, n * 4), "copy of the COO");
+        for (int w = last; w >= 0; --w) {
+            int32_t* dst = sorted ? cols[0][w] : raw[w];
+            HIP_OR_FAIL(up.put(dst, indices + (int64_t)w * nnz, n * 4), "copy of the COO");
             HIP_OR_FAIL(up.before(stream), "hipStreamWaitEvent");
-            if (w == order) continue;
-            HIP_OR_FAIL(amped::launch_check_range(cols[0][w], dims[w], nnz, &d_status->bad[w], stream), "range check");
-            if (early) HIP_OR_FAIL(sort_by(w), "radix sort");
+            HIP_OR_FAIL(amped::launch_check_range(dst, dims[w], nnz, &d_status->bad[w], stream), "range check");
+            if (!sorted) HIP_OR_FAIL(sort_by(w), "radix sort");
         }
-        if (lexi) {
+        // the launches (about 40) go between the first pieces and the rest, so that the
+        // link has work meanwhile
+        const size_t ahead = std::min(n, 2 * Uploader::kPiece / 4);
+        int32_t* const dst = sorted ? cols[0][order] : raw[order];
+        HIP_OR_FAIL(up.put(dst, values, ahead * 4), "copy of the COO");
+        if (!sorted) HIP_OR_FAIL(mode_orders(), "mode orders");
+        if (ahead < n) HIP_OR_FAIL(up.put(dst + ahead, values + ahead, (n - ahead) * 4), "copy of the COO");
+        HIP_OR_FAIL(up.before(stream), "hipStreamWaitEvent");
+        if (looks_sorted) {
             HIP_OR_FAIL(amped::launch_check_sorted(order, cols[0], nnz, &d_status->unsorted, stream), "order check");
             HIP_OR_FAIL(hipMemcpyAsync(&status, d_status, sizeof(status), hipMemcpyDeviceToHost, stream), "status");
             HIP_OR_FAIL(hipStreamSynchronize(stream), "layout build");
-            lexi = status.unsorted == 0;
-            if (!lexi)
-                for (int w = order - 1; w >= 0; --w) HIP_OR_FAIL(sort_by(w), "radix sort");
+            sorted = status.unsorted == 0;
+            if (!sorted) {
+                for (int w = 0; w <= order; ++w) HIP_OR_FAIL(copy(raw[w], cols[0][w]), "copy");
+                for (int w = last; w >= 0; --w) HIP_OR_FAIL(sort_by(w), "radix sort");
+            }
+            HIP_OR_FAIL(mode_orders(), "mode orders");
         }
-        const int32_t* lex_order = lexi || passes == 0 ? nullptr : lex[0];   // NULL: the input's own order
+        HIP_OR_FAIL(lex_column(order), "gather");
 
-        // the modes' arrays
-        if (records) {
+        // the other columns
+        for (int d = 0; d < order && t->keep_perm; ++d) {
+            const bool own = d > 0 && np[d] > 0, lexed = !sorted && passes > 0;
+            const int32_t* perm = own ? cols[d][order] : lex;
+            HIP_OR_FAIL(own && lexed ? amped::launch_permute32(t->perm[d], lex, perm, nnz, stream)
+                        : own || lexed ? copy(t->perm[d], perm)
+                                       : amped::launch_iota(t->perm[d], nnz, stream), "permutation");
+        }
+        if (records)
             HIP_OR_FAIL(amped::launch_pack_records(order, reinterpret_cast<const void* const*>(cols[0]), rec, nnz,
                                                    stream), "pack");
-        } else {
-            for (int w = 0; w <= order; ++w)
-                HIP_OR_FAIL(hipMemcpyAsync(raw[w], cols[0][w], n * 4, hipMemcpyDeviceToDevice, stream), "copy");
-        }
-        auto gather = [&](const int32_t* perm, int32_t* const* to_cols) -> hipError_t {
-            if (records)
-                return amped::launch_gather_records(order, rec, perm, reinterpret_cast<void* const*>(to_cols), nnz,
-                                                    stream);
-            for (int w = 0; w <= order; ++w) {
-                hipError_t er = to_cols[w] ? amped::launch_permute32(to_cols[w], raw[w], perm, nnz, stream) : hipSuccess;
-                if (er != hipSuccess) return er;
-            }
-            return hipSuccess;
-        };
-        if (lex_order) HIP_OR_FAIL(gather(lex_order, cols[0]), "gather");
-        for (int d = 0; d < order; ++d) {
-            int32_t* perm = t->keep_perm ? t->perm[d] : order_buf;
-            const int bits = bits_for(dims[d] - 1), np = amped::sort_passes(bits);
-            if (d > 0 && np > 0) {
-                uint32_t* kb[2] = {reinterpret_cast<uint32_t*>(cols[d][d]), kbuf[1]};
-                int32_t* vb[2] = {perm, lex[1]};
-                HIP_OR_FAIL(amped::launch_stable_sort(reinterpret_cast<const uint32_t*>(cols[0][d]), lex_order, kb, vb,
-                                                      (np - 1) & 1, scratch, nnz, bits, stream), "radix sort");
+        for (int d = 1; d < order; ++d) {
+            const int32_t* perm = cols[d][order];
+            if (np[d] > 0 && records) {
                 int32_t* others[kMaxOrder + 1];
                 for (int w = 0; w <= order; ++w) others[w] = w == d ? nullptr : cols[d][w];
-                HIP_OR_FAIL(gather(perm, others), "gather");
-            } else {
-                // this mode's order is the lexicographic one
-                if (d > 0)
-                    for (int w = 0; w <= order; ++w)
-                        HIP_OR_FAIL(hipMemcpyAsync(cols[d][w], cols[0][w], n * 4, hipMemcpyDeviceToDevice, stream), "copy");
-                if (t->keep_perm) {
-                    if (lex_order)
-                        HIP_OR_FAIL(hipMemcpyAsync(perm, lex_order, n * 4, hipMemcpyDeviceToDevice, stream), "copy");
-                    else HIP_OR_FAIL(amped::launch_iota(perm, nnz, stream), "iota");
-                }
+                HIP_OR_FAIL(amped::launch_gather_records(order, rec, perm, reinterpret_cast<void* const*>(others), nnz,
+                                                         stream), "gather");
+                continue;
             }
-            HIP_OR_FAIL(amped::launch_count_rows(t->mode[d].out_idx, nnz, dims[d], t->unit, counts[d],
-                                                 &d_status->totals[d], stream), "row counts");
-            if (small) {
-                int32_t* cut = ka.take<int32_t>(units + 1);
-                int32_t* left = ka.take<int32_t>(units + 1);
-                int32_t* split = ka.take<int32_t>(2 * units);
-                unsigned* arrived = ka.take<unsigned>(units);
-                HIP_OR_FAIL(amped::launch_small_units(t->mode[d].out_idx, nnz, small_len, (int)units, cut, left, split,
-                                                      arrived, d_status->small[d], stream), "small units");
-                t->mode[d].small.cut = cut;
-                t->mode[d].small.left = left;
-                t->mode[d].small.split = split;
-                t->mode[d].small.arrived = arrived;
+            for (int w = 0; w <= order; ++w) {
+                if (w == d) continue;
+                HIP_OR_FAIL(np[d] > 0 ? amped::launch_permute32(cols[d][w], cols[0][w], perm, nnz, stream)
+                                      : copy(cols[d][w], cols[0][w]), "gather");
             }
         }
+        up.finish();   // while the stream works
         HIP_OR_FAIL(hipMemcpyAsync(&status, d_status, sizeof(status), hipMemcpyDeviceToHost, stream), "status");
         HIP_OR_FAIL(hipStreamSynchronize(stream), "layout build");
         for (int w = 0; w < order; ++w)
@@ -839,8 +882,11 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
     const int64_t layout_bytes = (int64_t)order * (order + 1) * 4 * (nnz + 4);
     int64_t row_bytes = 0;
     for (int d = 0; d < order; ++d) row_bytes += 4 * dims[d] + 4 * amped::kHotTableLen;
-    // device sort: lexicographic order, key and value ping-pong buffers, scratch
-    const int64_t sort_bytes = 16 * nnz + 4 * amped::sort_scratch_words(nnz);
+    // device sort: lexicographic order, key and value ping-pong buffers, 256 counts
+    // per 4096 nonzeros and their sums.  (Most of the buffers now lie in arrays of
+    // modes not yet built; what a cap admits is unchanged.)
+    const int64_t sort_counts = (nnz + 4095) / 4096 * 256;
+    const int64_t sort_bytes = 16 * nnz + 4 * (sort_counts + (sort_counts + 4095) / 4096 + 64);
     // host-resident layouts: two shard buffers of whole chunks instead
     const int64_t n_chunks = (nnz + chunk - 1) / chunk;
     const int64_t shard_chunks =

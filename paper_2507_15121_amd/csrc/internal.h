@@ -141,8 +141,8 @@ bool is_lexicographic(int order, int64_t nnz, const int32_t* idx);
 bool is_lexicographic_prefix(int order, int64_t nnz, const int32_t* idx, int64_t len);
 
 // Device layout build: a stable LSD radix sort of n (key, value) pairs by the
-// low key_bits bits of the keys, 8 bits per pass (sort_passes(key_bits) passes,
-// at least one must be needed).  The first pass reads (keys, vals) and writes
+// low key_bits bits of the keys, in sort_passes(key_bits) passes (at least one must
+// be needed).  The first pass reads (keys, vals) and writes
 // (kbuf[first], vbuf[first]), the next ones alternate between the two buffer
 // pairs; vals NULL: the positions.  keys or vals may be a buffer of the pair that
 // is not written first.  scratch holds sort_scratch_words(n) 32-bit words.

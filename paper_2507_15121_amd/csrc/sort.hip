@@ -1,19 +1,26 @@
 // Device side of the per-mode layout builder (preprocessing, Sec. 5.7; not
 // part of the timed MTTKRP): a stable least-significant-digit radix sort of
-// (key, value) pairs, 8 bits per pass.
+// (key, value) pairs, up to 10 bits per pass.
 //
-// One pass over n pairs, with tiles of kTile consecutive pairs per block:
-//   1. histogram: each block counts the digits of its tile (LDS atomics) and
-//      writes the 256 counts digit-major, hist[digit * nblocks + block];
-//   2. scan: an exclusive prefix sum over that array gives, for every (digit,
-//      block), where the block's pairs with that digit start in the output;
-//   3. scatter: each block walks its tile again in order, 256 pairs per round.
-//      A pair's rank among equal digits of the tile is the count from earlier
-//      rounds + from earlier waves of the round + from earlier lanes of its
-//      wave (lanes with the same digit are found by matching the 8 digit bits
-//      with ballots), so equal digits keep their input order and every pass,
-//      hence the whole sort, is stable.
-// A block's 16 loads per thread go out together, before its rounds.
+// One pass over n pairs, with tiles of kTile consecutive pairs per block, each
+// wave owning a quarter of the tile:
+//   1. histogram: each block counts the digits of its tile and writes its counts,
+//      hist[block * digits + digit];
+//   2. scan, down the columns of that array: groups of blocks, then the groups'
+//      sums and the digits' starts;
+//   3. scatter: each wave walks its quarter in order, 64 pairs per round.  A pair's
+//      rank among equal digits of the quarter is the count from earlier rounds +
+//      from earlier lanes (lanes with the same digit are found by matching the
+//      digit's bits with ballots; the first of them adds their number to the wave's
+//      counter), so equal digits keep their input order and every pass, hence the
+//      whole sort, is stable.  The tile is put in digit order in LDS and leaves as
+//      one run per digit.
+// All accesses but the runs' ends are whole lines, and no pass has a step that a
+// crowded digit makes serial.  With 8 bits per pass, counts digit-major, one LDS
+// atomic per key in the histogram and rounds of 256 pairs written straight to
+// their places, a pass over 5M pairs took 60 to 95 us (20 histogram, 12 scan, 25
+// to 68 scatter); now 45 to 60 (6 to 10, 10, 25 to 40), and 17 to 20 bits need two
+// passes instead of three.
 //
 // Beside the sort: the check of the coordinates (range, lexicographic order),
 // the gather of a mode's arrays through its order (a nonzero as one record of
@@ -35,140 +42,204 @@ constexpr int kSortBlock = 256;
 constexpr int kSortWaves = kSortBlock / 64;
 constexpr int kRounds = 16;
 constexpr int64_t kTile = (int64_t)kSortBlock * kRounds;  // pairs per block
-constexpr int kRadix = 256;
-constexpr int kScanItems = 16;                              // per thread in the scan kernels
-constexpr int64_t kScanTile = (int64_t)kSortBlock * kScanItems;
+constexpr int kMaxDigitBits = 10;
 
-__global__ void __launch_bounds__(kSortBlock) radix_histogram(const uint32_t* keys, int64_t n, int shift,
-                                                              uint32_t* hist, int64_t nblocks)
+// The lanes of `among` whose digit equals this lane's.
+template <int B>
+__device__ __forceinline__ uint64_t match_digit(uint32_t dg, uint64_t among)
 {
-    __shared__ uint32_t h[kRadix];
-    h[threadIdx.x] = 0;
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        const bool bit = (dg >> b) & 1u;
+        const uint64_t ones = __ballot(bit);
+        among &= bit ? ones : ~ones;
+    }
+    return among;
+}
+
+// B: the most bits a digit may have; bits: those it has.  The lanes count in several
+// copies, on different banks: one copy takes a wave's equal digits one at a time, and
+// matching the digits with ballots first (as the scatter does) costs the same 10 us
+// of a pass over 5M keys.
+template <int B>
+__global__ void __launch_bounds__(kSortBlock) radix_histogram(const uint32_t* keys, int64_t n, int shift, int bits,
+                                                              uint32_t* hist)
+{
+    constexpr int kCopies = B <= 8 ? 16 : 8, LD = (1 << B) + 2;
+    __shared__ uint32_t h[kCopies * LD];
+    const int tid = threadIdx.x, nd = 1 << bits;
+    for (int d = tid; d < kCopies * LD; d += kSortBlock) h[d] = 0;
     __syncthreads();
-    const int64_t t0 = (int64_t)blockIdx.x * kTile + threadIdx.x;
+    uint32_t* const mine = h + (tid & (kCopies - 1)) * LD;
+    const int64_t t0 = (int64_t)blockIdx.x * kTile + tid;
     uint32_t key[kRounds];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) key[r] = t0 + r * kSortBlock < n ? keys[t0 + r * kSortBlock] : 0u;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r)
-        if (t0 + r * kSortBlock < n) atomicAdd(&h[(key[r] >> shift) & (kRadix - 1)], 1u);
+        if (t0 + r * kSortBlock < n) atomicAdd(&mine[(key[r] >> shift) & (nd - 1)], 1u);
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+    for (int d = tid; d < nd; d += kSortBlock) {
+        uint32_t x = 0;
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c) x += h[c * LD + d];
+        hist[(int64_t)blockIdx.x * nd + d] = x;
+    }
 }
 
-// Exclusive scan of kScanTile items per block in place; the tile total goes
-// to sums[block].
-__global__ void __launch_bounds__(kSortBlock) scan_tiles(uint32_t* a, int64_t n, uint32_t* sums)
+// Exclusive sums, per digit, over a group's blocks, in place; the group's total
+// goes to sums[group * digits + digit].
+__global__ void __launch_bounds__(kSortBlock) scan_groups(uint32_t* hist, int64_t nblocks, int64_t group, int nd,
+                                                          uint32_t* sums)
 {
-    __shared__ uint32_t s[kSortBlock];
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    uint32_t v[kScanItems];
-    uint32_t tot = 0;
+    const int d = blockIdx.y * kSortBlock + threadIdx.x;
+    if (d >= nd) return;
+    const int64_t b0 = (int64_t)blockIdx.x * group, b1 = min(b0 + group, nblocks);
+    uint32_t run = 0;
+    for (int64_t b = b0; b < b1; b += 8) {
+        uint32_t x[8];
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        const int64_t i = base + j;
-        v[j] = i < n ? a[i] : 0u;
-        const uint32_t x = v[j];
-        v[j] = tot;
-        tot += x;
-    }
-    s[threadIdx.x] = tot;
-    __syncthreads();
-    // inclusive Hillis-Steele scan of the thread totals
-    for (int off = 1; off < kSortBlock; off <<= 1) {
-        const uint32_t y = threadIdx.x >= (unsigned)off ? s[threadIdx.x - off] : 0u;
-        __syncthreads();
-        s[threadIdx.x] += y;
-        __syncthreads();
-    }
-    const uint32_t excl = s[threadIdx.x] - tot;
+        for (int k = 0; k < 8; ++k) x[k] = b + k < b1 ? hist[(b + k) * nd + d] : 0u;
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        const int64_t i = base + j;
-        if (i < n) a[i] = v[j] + excl;
-    }
-    if (threadIdx.x == kSortBlock - 1) sums[blockIdx.x] = s[threadIdx.x];
-}
-
-// Exclusive scan of the tile totals by one block, in order, with a carry.
-__global__ void __launch_bounds__(kSortBlock) scan_sums(uint32_t* sums, int64_t m)
-{
-    __shared__ uint32_t s[kSortBlock];
-    __shared__ uint32_t carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int64_t b = 0; b < m; b += kSortBlock) {
-        const int64_t i = b + threadIdx.x;
-        const uint32_t x = i < m ? sums[i] : 0u;
-        s[threadIdx.x] = x;
-        __syncthreads();
-        for (int off = 1; off < kSortBlock; off <<= 1) {
-            const uint32_t y = threadIdx.x >= (unsigned)off ? s[threadIdx.x - off] : 0u;
-            __syncthreads();
-            s[threadIdx.x] += y;
-            __syncthreads();
+        for (int k = 0; k < 8; ++k) {
+            if (b + k < b1) hist[(b + k) * nd + d] = run;
+            run += x[k];
         }
-        if (i < m) sums[i] = carry + s[threadIdx.x] - x;
-        __syncthreads();
-        if (threadIdx.x == kSortBlock - 1) carry += s[threadIdx.x];
-        __syncthreads();
     }
+    sums[(int64_t)blockIdx.x * nd + d] = run;
 }
 
-// vals_in NULL: the values are the positions.  sums: the exclusive sums of the
-// scan tiles, not yet added to the offsets.
+// The same over the groups, by one block with a thread per digit; starts[digit] is
+// where the digit's pairs start.
+__global__ void __launch_bounds__(1 << kMaxDigitBits) scan_digits(uint32_t* sums, int64_t groups, int nd,
+                                                                  uint32_t* starts)
+{
+    __shared__ uint32_t s_wave[(1 << kMaxDigitBits) / 64];
+    const int d = threadIdx.x, lane = d & 63, wave = d >> 6;
+    uint32_t run = 0;
+    if (d < nd) {
+        for (int64_t g = 0; g < groups; g += 8) {
+            uint32_t x[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k] = g + k < groups ? sums[(g + k) * nd + d] : 0u;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (g + k < groups) sums[(g + k) * nd + d] = run;
+                run += x[k];
+            }
+        }
+    }
+    uint32_t incl = run;
+    for (int m = 1; m < 64; m <<= 1) {
+        const uint32_t y = __shfl_up(incl, m, 64);
+        incl += lane >= m ? y : 0u;
+    }
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += s_wave[w];
+    if (d < nd) starts[d] = incl - run;
+}
+
+// vals_in NULL: the values are the positions.
+template <int B>
 __global__ void __launch_bounds__(kSortBlock) radix_scatter(const uint32_t* keys_in, const int32_t* vals_in,
                                                             uint32_t* keys_out, int32_t* vals_out, int64_t n,
-                                                            int shift, const uint32_t* offsets, const uint32_t* sums,
-                                                            int64_t nblocks)
+                                                            int shift, int bits, const uint32_t* hist,
+                                                            const uint32_t* sums, const uint32_t* starts,
+                                                            int64_t group)
 {
-    __shared__ uint32_t s_base[kRadix];               // next output position per digit
-    __shared__ uint32_t s_cnt[kSortWaves][kRadix];    // per wave, digit counts of the round
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int64_t t0 = (int64_t)blockIdx.x * kTile + tid;
-    uint32_t keys[kRounds];
+    constexpr int D = 1 << B, PER = (D + kSortBlock - 1) / kSortBlock;
+    constexpr int kWords = kSortWaves * D > 2 * (int)kTile ? kSortWaves * D : 2 * (int)kTile;
+    __shared__ uint32_t s_mem[kWords];     // digit counts per wave, then the tile in digit order
+    __shared__ uint32_t s_delta[D];        // a digit's place in the output minus its place in the tile
+    __shared__ uint32_t s_wave[kSortWaves];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, nd = 1 << bits;
+    const int64_t first = (int64_t)blockIdx.x * kTile;
+    const int count = (int)min((int64_t)kTile, n - first);
+    const int p0 = wave * (64 * kRounds) + lane;
+    uint32_t keys[kRounds], rank[kRounds];
     int32_t vals[kRounds];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int64_t i = t0 + r * kSortBlock;
-        keys[r] = i < n ? keys_in[i] : 0u;
-        vals[r] = i < n ? (vals_in ? vals_in[i] : (int32_t)i) : 0;
+        const int p = p0 + r * 64;
+        keys[r] = p < count ? keys_in[first + p] : 0u;
+        vals[r] = p < count ? (vals_in ? vals_in[first + p] : (int32_t)(first + p)) : 0;
     }
-    const int64_t slot = (int64_t)tid * nblocks + blockIdx.x;
-    s_base[tid] = offsets[slot] + sums[slot / kScanTile];
+    uint32_t out[PER];   // where the digits tid * PER ... of this tile start
 #pragma unroll
-    for (int w = 0; w < kSortWaves; ++w) s_cnt[w][tid] = 0;
+    for (int k = 0; k < PER; ++k) {
+        const int d = tid * PER + k;
+        out[k] = d < nd ? hist[(int64_t)blockIdx.x * nd + d] + sums[((int64_t)blockIdx.x / group) * nd + d] + starts[d]
+                        : 0u;
+    }
+    for (int d = tid; d < kSortWaves * D; d += kSortBlock) s_mem[d] = 0;
     __syncthreads();
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    uint32_t* const cnt = s_mem + wave * D;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const bool valid = t0 + r * kSortBlock < n;
-        const uint32_t dg = (keys[r] >> shift) & (kRadix - 1);
-        uint64_t same = __ballot(valid);
+        const bool valid = p0 + r * 64 < count;
+        const uint32_t dg = (keys[r] >> shift) & (nd - 1);
+        const uint64_t same = match_digit<B>(dg, __ballot(valid));
+        const uint64_t below = same & ((1ull << lane) - 1);
+        uint32_t before = 0;
+        if (valid && below == 0) before = atomicAdd(&cnt[dg], (uint32_t)__popcll(same));
+        const int leader = valid ? __ffsll((unsigned long long)same) - 1 : lane;
+        rank[r] = __shfl(before, leader, 64) + (uint32_t)__popcll(below);
+    }
+    __syncthreads();
+    // places in the tile: digits in order, within a digit the waves in order
+    uint32_t total = 0, tot[PER];
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (dg >> b) & 1u;
-            const uint64_t ones = __ballot(valid && bit);
-            same &= bit ? ones : ~ones;
-        }
-        const uint32_t rank = (uint32_t)__popcll(same & below);
-        if (valid && rank == 0) s_cnt[wave][dg] = (uint32_t)__popcll(same);
-        __syncthreads();
-        if (valid) {
-            uint32_t pos = s_base[dg] + rank;
-            for (int w = 0; w < wave; ++w) pos += s_cnt[w][dg];
-            keys_out[pos] = keys[r];
-            vals_out[pos] = vals[r];
-        }
-        __syncthreads();
-        uint32_t tot = 0;
+    for (int k = 0; k < PER; ++k) {
+        const int d = tid * PER + k;
+        tot[k] = 0;
+        if (d < D) {
 #pragma unroll
-        for (int w = 0; w < kSortWaves; ++w) {
-            tot += s_cnt[w][tid];
-            s_cnt[w][tid] = 0;
+            for (int w = 0; w < kSortWaves; ++w) tot[k] += s_mem[w * D + d];
         }
-        s_base[tid] += tot;
-        __syncthreads();
+        total += tot[k];
+    }
+    uint32_t at = total;
+    for (int m = 1; m < 64; m <<= 1) {
+        const uint32_t y = __shfl_up(at, m, 64);
+        at += lane >= m ? y : 0u;
+    }
+    if (lane == 63) s_wave[wave] = at;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) at += s_wave[w];
+    at -= total;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int d = tid * PER + k;
+        if (d < D) {
+            s_delta[d] = out[k] - at;
+#pragma unroll
+            for (int w = 0; w < kSortWaves; ++w) {
+                const uint32_t x = s_mem[w * D + d];
+                s_mem[w * D + d] = at;
+                at += x;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) rank[r] += cnt[(keys[r] >> shift) & (nd - 1)];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        if (p0 + r * 64 >= count) continue;
+        s_mem[rank[r]] = keys[r];
+        s_mem[kTile + rank[r]] = (uint32_t)vals[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int p = r * kSortBlock + tid;
+        if (p >= count) continue;
+        const uint32_t key = s_mem[p];
+        const uint32_t to = s_delta[(key >> shift) & (nd - 1)] + (uint32_t)p;
+        keys_out[to] = key;
+        vals_out[to] = (int32_t)s_mem[kTile + p];
     }
 }
 
@@ -185,12 +256,18 @@ int grid_for(int64_t items, int64_t per_block)
 
 }  // namespace
 
+// Blocks per group of the column scans: about as many groups as blocks in one.
+static int64_t scan_group(int64_t nblocks)
+{
+    int64_t g = 1;
+    while (g * g < nblocks) ++g;
+    return g;
+}
+
 int64_t sort_scratch_words(int64_t n)
 {
-    const int64_t nblocks = (n + kTile - 1) / kTile;
-    const int64_t hist = nblocks * kRadix;
-    const int64_t tiles = (hist + kScanTile - 1) / kScanTile;
-    return hist + tiles + 64;
+    const int64_t nblocks = (n + kTile - 1) / kTile, group = scan_group(nblocks);
+    return (nblocks + (nblocks + group - 1) / group + 1) << kMaxDigitBits;
 }
 
 hipError_t launch_iota(int32_t* a, int64_t n, hipStream_t st)
@@ -200,25 +277,32 @@ hipError_t launch_iota(int32_t* a, int64_t n, hipStream_t st)
     return hipGetLastError();
 }
 
-int sort_passes(int key_bits) { return (key_bits + 7) / 8; }
+int sort_passes(int key_bits) { return (key_bits + kMaxDigitBits - 1) / kMaxDigitBits; }
 
 hipError_t launch_stable_sort(const uint32_t* keys, const int32_t* vals, uint32_t* const* kbuf, int32_t* const* vbuf,
                               int first, uint32_t* scratch, int64_t n, int key_bits, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    const int64_t nblocks = (n + kTile - 1) / kTile;
-    const int64_t hist_len = nblocks * kRadix;
-    const int64_t tiles = (hist_len + kScanTile - 1) / kScanTile;
-    uint32_t* hist = scratch;
-    uint32_t* sums = scratch + hist_len;
+    const int64_t nblocks = (n + kTile - 1) / kTile, group = scan_group(nblocks);
+    const int64_t groups = (nblocks + group - 1) / group;
+    const int passes = sort_passes(key_bits);
     int to = first;
-    for (int shift = 0; shift < key_bits; shift += 8) {
-        hipLaunchKernelGGL(radix_histogram, dim3((unsigned)nblocks), dim3(kSortBlock), 0, st, keys, n, shift, hist,
-                           nblocks);
-        hipLaunchKernelGGL(scan_tiles, dim3((unsigned)tiles), dim3(kSortBlock), 0, st, hist, hist_len, sums);
-        hipLaunchKernelGGL(scan_sums, dim3(1), dim3(kSortBlock), 0, st, sums, tiles);
-        hipLaunchKernelGGL(radix_scatter, dim3((unsigned)nblocks), dim3(kSortBlock), 0, st, keys, vals, kbuf[to],
-                           vbuf[to], n, shift, hist, sums, nblocks);
+    for (int p = 0; p < passes; ++p) {
+        // the key's bits in equal parts
+        const int shift = key_bits * p / passes, bits = key_bits * (p + 1) / passes - shift, nd = 1 << bits;
+        uint32_t* hist = scratch;
+        uint32_t* sums = hist + nblocks * nd;
+        uint32_t* starts = sums + groups * nd;
+        auto pass = [&](auto histogram, auto scatter) {
+            hipLaunchKernelGGL(histogram, dim3((unsigned)nblocks), dim3(kSortBlock), 0, st, keys, n, shift, bits, hist);
+            hipLaunchKernelGGL(scan_groups, dim3((unsigned)groups, (nd + kSortBlock - 1) / kSortBlock),
+                               dim3(kSortBlock), 0, st, hist, nblocks, group, nd, sums);
+            hipLaunchKernelGGL(scan_digits, dim3(1), dim3(1 << kMaxDigitBits), 0, st, sums, groups, nd, starts);
+            hipLaunchKernelGGL(scatter, dim3((unsigned)nblocks), dim3(kSortBlock), 0, st, keys, vals, kbuf[to],
+                               vbuf[to], n, shift, bits, hist, sums, starts, group);
+        };
+        if (bits <= 8) pass(radix_histogram<8>, radix_scatter<8>);
+        else pass(radix_histogram<kMaxDigitBits>, radix_scatter<kMaxDigitBits>);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         keys = kbuf[to];
@@ -327,10 +411,10 @@ struct RowStep {
     int32_t shared = -1;           // the shared row
     bool first = false;            // p is the first of its row
 };
-__device__ __forceinline__ RowStep row_step(const int32_t* keys, int64_t p, int64_t n, int64_t rows, int64_t unit)
+__device__ __forceinline__ RowStep row_step(const int32_t* keys, int64_t p, int64_t n, int64_t rows, int64_t unit,
+                                            int64_t cur, int64_t prev)   // keys[p], keys[p - 1] (p = 0: -1)
 {
     RowStep s;
-    const int64_t cur = keys[p], prev = p > 0 ? keys[p - 1] : -1;
     s.first = cur != prev;
     if (s.first) {
         s.start0 = prev + 1;
@@ -359,7 +443,7 @@ __global__ void __launch_bounds__(kSortBlock) count_rows(const int32_t* keys, in
     const int64_t p1 = min((int64_t)(blockIdx.x + 1) * len, n);
     uint32_t c[4] = {0, 0, 0, 0};
     for (int64_t p = (int64_t)blockIdx.x * len + threadIdx.x; p < p1; p += kSortBlock) {
-        const RowStep s = row_step(keys, p, n, rows, unit);
+        const RowStep s = row_step(keys, p, n, rows, unit, keys[p], p > 0 ? keys[p - 1] : -1);
         c[0] += s.shared >= 0;
         c[1] += lone_rows(s.gap0) + lone_rows(s.gap1);
         c[2] += gap_pieces(s.gap0) + gap_pieces(s.gap1);
@@ -426,19 +510,32 @@ __global__ void __launch_bounds__(kSortBlock) fill_rows(const int32_t* keys, int
     }
     __syncthreads();
     const int64_t pa = (int64_t)blockIdx.x * len, p1 = min(pa + len, n);
+    // the next round's keys are loaded while a round is computed: 36 us for 5M keys
+    // without, 24 with
+    int32_t cur = 0, prev = -1;
+    auto load = [&](int64_t p) {
+        if (p >= p1) return;
+        cur = keys[p];
+        prev = p > 0 ? keys[p - 1] : -1;
+    };
+    load(pa + threadIdx.x);
     for (int64_t q = pa; q < p1; q += kSortBlock) {
         const int64_t p = q + threadIdx.x;
         RowStep s;
-        if (p < p1) s = row_step(keys, p, n, rows, unit);
+        const int32_t cur0 = cur, prev0 = prev;
+        load(p + kSortBlock);
+        if (p < p1) s = row_step(keys, p, n, rows, unit, cur0, prev0);
         uint32_t c[3] = {s.shared >= 0 ? 1u : 0u, lone_rows(s.gap0) + lone_rows(s.gap1),
                          gap_pieces(s.gap0) + gap_pieces(s.gap1)};
         uint32_t at[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             uint32_t x = c[k];   // inclusive sum over the wave
-            for (int m = 1; m < 64; m <<= 1) {
-                const uint32_t y = __shfl_up(x, m, 64);
-                x += lane >= m ? y : 0u;
+            if (__ballot(x != 0)) {
+                for (int m = 1; m < 64; m <<= 1) {
+                    const uint32_t y = __shfl_up(x, m, 64);
+                    x += lane >= m ? y : 0u;
+                }
             }
             at[k] = x - c[k];
             if (lane == 63) s_sum[k][wave] = x;

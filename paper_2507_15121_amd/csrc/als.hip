@@ -19,7 +19,8 @@
 //    the product is the row).  Per-slab fp32 partials are summed in fp64 by
 //    gram_reduce, in slab order (deterministic).
 //  * als_small: one block, fp64 in registers: V, V^{-1} (Gauss-Jordan), P, lambda,
-//    the new G_d, W and, after the last mode, the fit.
+//    the new G_d, W and, after the last mode, the fit; in small modes also the
+//    partials' sum and, in as many blocks as the rows need, A_d.
 //  * als_solve: A_d = M W, a persistent grid over tiles of rows (256 at
 //    R <= 32) staged through LDS beside W; the next tile's rows are loaded
 //    into registers while the current one is computed.

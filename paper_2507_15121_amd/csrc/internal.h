@@ -26,13 +26,18 @@ constexpr int64_t kMaxChunk = int64_t(1) << 28;
 // more; 2M 103 us (one per wave), 128 us (512); 5M 309, 233, 248 us; 10M 600, 446,
 // 428, 450 us (order 4: 740, 703, 740 us with the last three); 20M 868 us (5120),
 // 809, 830; rank 64 with bfloat16 factors 1002, 934, 955; 50M 2090, -, 2071, 2045;
-// 200M 8694, -, 8756, 8626.
+// 200M 8694, -, 8756, 8626.  From 64M on the unit is 4096 all the same: a heavy row
+// takes one fp32 atomic per unit, and their rounding then decides the result's error
+// (40M nonzeros, units of 2048 and 4096: 4.0e-7 and 4.1e-7 of the outputs' norm; 100M
+// 4.7e-7 and 4.4e-7; 200M 5.6e-7 and 4.9e-7; 8192, whose sums in registers are longer,
+// 5.2e-7 to 5.6e-7).
 constexpr int64_t kGridWaves = 2048;
 constexpr int64_t kTileNnz = 256;      // a unit is whole tiles of the kernel
 constexpr int64_t kMaxRoundUnit = 2560;
 inline int64_t work_unit(int64_t nnz)
 {
-    if (nnz > kGridWaves * kMaxRoundUnit) return nnz < (int64_t(32) << 20) ? 1024 : 2048;
+    if (nnz > kGridWaves * kMaxRoundUnit)
+        return nnz < (int64_t(32) << 20) ? 1024 : nnz < (int64_t(64) << 20) ? 2048 : 4096;
     const int64_t tiles = (nnz + kGridWaves * kTileNnz - 1) / (kGridWaves * kTileNnz);
     return kTileNnz * (tiles > 0 ? tiles : 1);
 }

@@ -4,27 +4,30 @@
 //
 // Work decomposition (one GPU's share of the paper's scheme, Sec. 3-4):
 //  * A mode's nonzeros are sorted by output index (Sec. 3.1: all nonzeros of
-//    one output index together) and cut into chunks of CH nonzeros, the
-//    equal-size inter-shard partitions of Sec. 3.1/3.2.
+//    one output index together) and cut into units of equal nonzero counts,
+//    the inter-shard partitions of Sec. 3.1/3.2.  (The layout contract's chunks
+//    are those units where a caller names their length; the kernels' `chunk`
+//    is always the unit.)
 //  * A persistent grid of wave64s replaces the hardware block scheduler of
-//    Sec. 4.2: each wave takes the next chunk from a device atomic counter
-//    until none is left, so skewed slices spread over all CUs.
-//  * Inside a chunk the wave is G groups of LPR lanes.  Each lane holds RPL
+//    Sec. 4.2: each wave starts with a unit of its own and takes further ones
+//    from device atomic counters until none is left, so skewed slices spread
+//    over all CUs.
+//  * Inside a unit the wave is G groups of LPR lanes.  Each lane holds RPL
 //    consecutive columns of a factor row (16 bytes; 8 for bf16 rows of 32
 //    bytes, and of 64 bytes when at most two factors are gathered), so a group
 //    loads a whole row with one coalesced access.  Group g walks its own contiguous run of
-//    the chunk's nonzeros in order and keeps the running sum of the current
+//    the unit's nonzeros in order and keeps the running sum of the current
 //    output row in registers (the elementwise computation, EC of Sec. 3,
 //    reduced over consecutive equal output indices instead of one atomic per
 //    nonzero as in Alg. 2).
 //  * A row that starts and ends inside one group's run is written once with a
 //    plain store.  Pieces of rows that cross group boundaries are parked in
-//    LDS and summed at the end of the chunk; only rows that cross a chunk
+//    LDS and summed at the end of the unit; only rows that cross a unit's
 //    boundary are added to memory with fp32 atomics (Sec. 3.2 uses atomics
 //    between SMs), after the init kernel has zeroed them.
 //  * Untouched output rows are zeroed once, by the init kernel.
-//  * MTTKRP keeps the most-used rows of each input factor in LDS (hot-row
-//    cache); their gathers issue no memory request.
+//  * From 32M nonzeros on, MTTKRP keeps the most-used rows of each input factor
+//    in LDS (hot-row cache); their gathers issue no memory request.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

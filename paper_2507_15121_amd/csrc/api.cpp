@@ -243,7 +243,8 @@ amped_status upload_tables(amped_tensor_s* t, ModeDev& m, int d, const HostModeL
         m.gaps = static_cast<int32_t*>(p);
     }
     m.nnz = t->nnz;
-    m.chunk = m.residual_chunk = t->unit;
+    m.unit = t->unit;
+    m.chunk = m.residual_chunk = t->unit * (t->own_units && lay.heavy ? amped::heavy_units(t->unit) : 1);
     m.n_chunks = (t->nnz + t->unit - 1) / t->unit;
     m.rows = t->dims[d];
     m.n_zero = (int64_t)lay.zero_rows.size();
@@ -427,6 +428,7 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
         amped::RowTotals totals[kMaxOrder];
         unsigned long long bad[kMaxOrder];
         int32_t small[kMaxOrder][2];   // split rows, most units of one
+        int32_t heavy[kMaxOrder];      // heavy rows
         unsigned unsorted, pad;
     } status;
     const size_t n = (size_t)nnz;
@@ -443,8 +445,15 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
     const size_t units = small ? (n + small_len - 1) / small_len : 0;
     const size_t small_bytes = small ? (size_t)order * (2 * Arena::step((units + 1) * 4) + Arena::step(units * 8) +
                                                         Arena::step(units * 4)) : 0;
+    // the heavy rows of units shorter than a chunk
+    const int n_units = (int)((nnz + t->unit - 1) / t->unit);
+    const bool heavy = t->own_units && nnz > 0 && t->unit < amped::kDefaultChunk && n_units > amped::kHeavyCuts;
+    const size_t heavy_cuts = (size_t)(n_units + amped::kHeavyCuts), heavy_max = (size_t)amped::heavy_rows_max(n_units);
+    const size_t slot_floats = (size_t)amped::heavy_slots_max(n_units) * amped::kSlotCols;
+    const size_t heavy_bytes = heavy ? (size_t)order * (Arena::step(heavy_cuts * 8) + Arena::step(heavy_max * 16) +
+                                                        Arena::step(slot_floats * 4)) : 0;
     Arena ka, ta;
-    HIP_OR_FAIL(t->alloc(&keep, keep_bytes + small_bytes), "hipMalloc(layouts)");
+    HIP_OR_FAIL(t->alloc(&keep, keep_bytes + small_bytes + heavy_bytes), "hipMalloc(layouts)");
     ka.base = static_cast<char*>(keep);
     {
         unsigned* queues = ka.take<unsigned>(words);
@@ -454,7 +463,7 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
         for (int d = 0; d < order; ++d) {
             ModeDev& m = t->mode[d];
             m.nnz = nnz;
-            m.chunk = t->unit;
+            m.unit = m.chunk = t->unit;
             m.n_chunks = (nnz + t->unit - 1) / t->unit;
             m.residual_chunk = t->unit * (t->own_units ? amped::residual_units(nnz, t->unit) : 1);
             m.rows = dims[d];
@@ -578,6 +587,17 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
                 if ((er = amped::launch_count_rows(cols[d][d], nnz, dims[d], t->unit, counts[d], &d_status->totals[d],
                                                    stream)) != hipSuccess)
                     return er;
+                if (heavy) {
+                    auto& hv = t->mode[d].heavy;
+                    int2* cut = ka.take<int2>(heavy_cuts);
+                    int4* rows = ka.take<int4>(heavy_max);
+                    if ((er = amped::launch_heavy_rows(cols[d][d], nnz, t->unit, n_units, rows, cut,
+                                                       &d_status->heavy[d], stream)) != hipSuccess)
+                        return er;
+                    hv.cut = cut;
+                    hv.rows = rows;
+                    hv.slot = ka.take<float>(slot_floats);
+                }
                 if (small) {
                     auto& sm = t->mode[d].small;
                     int32_t* cut = ka.take<int32_t>(units + 1);
@@ -686,6 +706,7 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
             m.n_zero = tot.shared + tot.lone;
             m.n_gaps = tot.gaps;
             t->touched[d] = tot.touched;
+            if (heavy) m.heavy.n = status.heavy[d];
             if (one_launch(d)) {
                 m.small.n_units = (int)units;
                 m.small.zrows = zero + tot.shared;
@@ -916,6 +937,11 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
     t->n_chunks = (nnz + chunk - 1) / chunk;
     t->unit = chunk;
     t->own_units = !opts || opts->chunk_nnz == 0;
+    // under a cap that does not hold what short units need beside the layouts, the units
+    // are the chunks
+    if (t->own_units && !host_layout && cap > 0 &&
+        peak + amped::short_unit_bytes(order, nnz, amped::work_unit(nnz)) > cap)
+        t->own_units = false;
     if (t->own_units)
         t->unit = host_layout ? amped::stream_work_unit(std::min(stage_len, nnz)) : amped::work_unit(nnz);
     t->device = dev;

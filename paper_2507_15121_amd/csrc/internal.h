@@ -7,6 +7,7 @@
 #include <vector>
 
 #include <hip/hip_runtime_api.h>
+#include <hip/hip_vector_types.h>
 
 namespace amped {
 
@@ -59,6 +60,16 @@ inline int64_t stream_work_unit(int64_t shard)
     while (u < kDefaultChunk && u * kGridWaves < shard) u *= 2;
     return u;
 }
+// Heavy rows: those with kHeavyCuts or more edges of units shorter than kDefaultChunk
+// inside.  One fp32 atomic per unit would make their error grow with the number of
+// units (factors in (0, 1), a row of 199k nonzeros, rank 32: units of 512, 1024, 2048,
+// 4096 2.9e-7, 2.5e-7, 1.4e-7, 1.1e-7 of the row), so their pieces go to slots
+// instead and close_rows adds them in fp64 (3.6e-8 at any unit).  Streamed layouts
+// have no slots: there such a mode's launches take heavy_units units at a time, whole
+// chunks or a little more.
+constexpr int kHeavyCuts = 8;         // residual_units() is at most this
+constexpr int kSlotCols = 256;         // columns of a launch at most
+inline int64_t heavy_units(int64_t unit) { return (kDefaultChunk + unit - 1) / unit; }
 // Least nonzeros of a launch that keeps the most-used factor rows in LDS.  Every
 // block copies them first, about 10 us, and the instances with the copy hold 70
 // more registers; all modes at rank 32 without and with it: 5M nonzeros 235 and
@@ -120,6 +131,7 @@ struct HostModeLayout {
     std::vector<int32_t> zero_rows;   // rows shared by two or more work units, then untouched rows of short runs
     std::vector<int32_t> gaps;        // (start, length) pairs of long untouched-row runs
     std::vector<int32_t> hot;         // hot-row tables of this mode's rows [kHotTableLen]
+    bool heavy = false;               // some row is a heavy row
     int64_t touched = 0;              // distinct output indices
 };
 
@@ -182,6 +194,24 @@ hipError_t launch_fill_rows(const int32_t* keys, int64_t n, int64_t rows, int64_
 // most units of one.
 hipError_t launch_small_units(const int32_t* keys, int64_t n, int unit, int units, int32_t* cut, int32_t* left,
                               int32_t* split, unsigned* arrived, int32_t* info, hipStream_t st);
+// The heavy rows of a mode with n_units units, from sorted keys: rows[h] = (row, its
+// first and last unit, the slot of its first unit's piece; unit k's piece has that plus k
+// minus the first), and for k < n_units + kHeavyCuts cut[k] = (that slot, the same less
+// the first unit) where unit k starts inside heavy row h, else kNoSlot twice.  *n_rows =
+// heavy rows, at most heavy_rows_max(n_units); their slots are at most
+// heavy_slots_max(n_units).
+constexpr int kNoSlot = -0x7FFFFFFF;
+constexpr int64_t heavy_rows_max(int64_t n_units) { return n_units / kHeavyCuts + 1; }
+constexpr int64_t heavy_slots_max(int64_t n_units) { return n_units + heavy_rows_max(n_units); }
+hipError_t launch_heavy_rows(const int32_t* keys, int64_t n, int64_t unit, int n_units, int4* rows, int2* cut,
+                             int32_t* n_rows, hipStream_t st);
+// Device bytes that units shorter than a chunk take beside the layouts: the tables and
+// slots of heavy rows.
+inline int64_t short_unit_bytes(int order, int64_t nnz, int64_t unit)
+{
+    const int64_t n = (nnz + unit - 1) / unit;
+    return order * (8 * (n + kHeavyCuts) + 16 * heavy_rows_max(n) + heavy_slots_max(n) * kSlotCols * 4 + 3 * 256);
+}
 // Hot-row tables (kHotTableLen entries) from sorted keys; best: kHotMax zeros.
 hipError_t launch_hot_tables(const int32_t* keys, int64_t n, unsigned long long* best, int32_t* hot, hipStream_t st);
 // a[i] = i for i < n.
@@ -243,6 +273,14 @@ struct ModeDev {
     const int32_t* hot = nullptr;                  // hot-row tables of this mode [kHotTableLen]
     const void* zero_row = nullptr;                // 16 zero bytes
     float* sink = nullptr;                         // kSinkFloats floats of write-only scratch
+    // Heavy rows (n = 0: none)
+    struct Heavy {
+        int n = 0;
+        const int4* rows = nullptr;
+        const int2* cut = nullptr;
+        float* slot = nullptr;             // slots of at most kSlotCols floats
+    } heavy;
+    int64_t unit = 0;                              // nonzeros per unit (chunk: per unit of a launch)
     // MTTKRP in one launch (n_units = 0: not for this mode)
     struct Small {
         int n_units = 0;

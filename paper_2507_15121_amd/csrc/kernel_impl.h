@@ -24,7 +24,8 @@
 //    plain store.  Pieces of rows that cross group boundaries are parked in
 //    LDS and summed at the end of the unit; only rows that cross a unit's
 //    boundary are added to memory with fp32 atomics (Sec. 3.2 uses atomics
-//    between SMs), after the init kernel has zeroed them.
+//    between SMs), after the init kernel has zeroed them; the pieces of rows
+//    that span many short units go to slots, which close_rows adds in fp64.
 //  * Untouched output rows are zeroed once, by the init kernel.
 //  * From 32M nonzeros on, MTTKRP keeps the most-used rows of each input factor
 //    in LDS (hot-row cache); their gathers issue no memory request.
@@ -126,6 +127,9 @@ struct KParams {
     uint32_t own_bytes;
     const void* zero_row;     // 16 zero bytes: what padding entries read on the 64-bit path
     float* sink;              // 64 * 8 floats that absorb stores which must not land
+    const int2* hcut;         // heavy rows' cuts (NULL: none; launch_heavy_rows)
+    float* hslot;             // their slots of slot_stride(ncols) floats each
+    int per_chunk;            // units per chunk
     int prev_key;             // output index just before position 0 of these arrays (-1: none)
     int next_key;             // output index just after position nnz - 1 (-1: none)
     const int32_t* hot[kMaxIn];  // per input: direct-mapped table of hot_k rows kept in LDS
@@ -143,6 +147,9 @@ __host__ __device__ constexpr size_t hot_lds_bytes(int nin, int k, int row_bytes
 {
     return k > 0 ? hot_row_offset(nin, k) + (size_t)nin * k * row_bytes : 16;
 }
+
+// A heavy row's slot: whole 16 bytes.
+__host__ __device__ constexpr int slot_stride(int ncols) { return (ncols + 3) & ~3; }
 
 // Raw buffer resource over [base, base + bytes): word 3 is the gfx9-family
 // default for untyped dword access.
@@ -649,6 +656,14 @@ mttkrp_kernel(const KParams p)
             k_last = p.out_idx[max(min(ge, p.nnz) - 1, (int64_t)0)];
             k_next = p.out_idx[min(ge, top)];
         }
+        // the heavy rows that the unit starts and ends in
+        int h_left = kNoSlot, h_right = kNoSlot;
+        if constexpr (OUT) {
+            if (p.hcut) {
+                h_left = p.hcut[(int64_t)chunk * p.per_chunk].y;
+                h_right = p.hcut[((int64_t)chunk + 1) * p.per_chunk].x;
+            }
+        }
         auto open_run = [&]() {
             if constexpr (OUT) {
                 if (gon) {
@@ -982,11 +997,22 @@ mttkrp_kernel(const KParams p)
             auto emit = [&]() {
                 if (cur < 0) return;
                 float* o = p.out + (int64_t)cur * ld + p.col0 + lane;
+                bool add = cur_ext != 0;
+                if (add) {
+                    // a heavy row's piece is stored to its slot: the row's first one
+                    // if it starts here, else that of the unit's first position
+                    const int h = cur_ext & 1 ? h_left : h_right;
+                    if (h != kNoSlot) {
+                        const int slot = cur_ext & 1 ? h + chunk * p.per_chunk : h;
+                        o = p.hslot + (int64_t)slot * slot_stride(p.ncols) + lane;
+                        add = false;
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < CL; ++i) {
                     if (!col_on[i]) continue;
                     const float v = cacc[i] * oscale;
-                    if (cur_ext) atomicAdd(o + 64 * i, v);
+                    if (add) atomicAdd(o + 64 * i, v);
                     else o[64 * i] = v;
                 }
             };

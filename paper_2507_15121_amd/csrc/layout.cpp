@@ -207,6 +207,11 @@ void tables_from_keys(int64_t nnz, int64_t rows, int64_t chunk, int64_t unit, co
         const int32_t r = key(p);
         if (key(p - 1) == r && (lay.zero_rows.empty() || lay.zero_rows.back() != r)) lay.zero_rows.push_back(r);
     }
+    lay.heavy = false;
+    for (int64_t p = kHeavyCuts * unit; p < nnz && !lay.heavy; p += unit) {
+        const int32_t r = key(p);   // the cuts at p and the 7 before it lie inside one row
+        lay.heavy = key(p - (kHeavyCuts - 1) * unit - 1) == r;
+    }
     // distinct output indices; untouched rows as long runs or single rows
     int nt = omp_get_max_threads();
     if (nt < 1) nt = 1;

@@ -703,6 +703,68 @@ __global__ void __launch_bounds__(1024) small_units(const int32_t* keys, int n, 
     }
 }
 
+// ------------------------------------------------------------------ heavy rows
+// One block.  The cuts inside a row are consecutive; its last one is found by
+// bisection.  (Indices out of range may leave the keys unsorted; the call then fails,
+// after this kernel, which stays inside its arrays whatever the keys are.)
+__global__ void __launch_bounds__(1024) heavy_rows(const int32_t* keys, int64_t n, int64_t unit, int units, int4* rows,
+                                                   int2* cut, int32_t* n_rows)
+{
+    __shared__ int s_rows[1024], s_slots[1024];
+    const int tid = threadIdx.x, most = (int)heavy_rows_max(units);
+    for (int k = tid; k < units + kHeavyCuts; k += 1024) cut[k] = make_int2(kNoSlot, kNoSlot);
+    const int per = (units + 1023) / 1024;
+    const int k0 = min(units, tid * per), k1 = min(units, k0 + per);
+    // whether cut k is the first one inside a heavy row
+    auto first = [&](int k) {
+        if (k < 1 || k + kHeavyCuts - 1 >= units) return false;
+        const int64_t p = (int64_t)k * unit;
+        const int32_t row = keys[p];
+        return keys[p - 1] == row && (k == 1 || keys[p - unit - 1] != row) && keys[p + (kHeavyCuts - 1) * unit] == row;
+    };
+    auto last = [&](int k) {
+        const int32_t row = keys[(int64_t)k * unit];
+        int lo = k + kHeavyCuts - 1, hi = units;
+        while (hi - lo > 1) {
+            const int mid = lo + (hi - lo) / 2;
+            if (keys[(int64_t)mid * unit] == row) lo = mid;
+            else hi = mid;
+        }
+        return lo;
+    };
+    int nr = 0, ns = 0;
+    for (int k = k0; k < k1; ++k)
+        if (first(k)) {
+            ++nr;
+            ns += last(k) - k + 2;
+        }
+    s_rows[tid] = nr;
+    s_slots[tid] = ns;
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {
+        const int x = tid >= off ? s_rows[tid - off] : 0, y = tid >= off ? s_slots[tid - off] : 0;
+        __syncthreads();
+        s_rows[tid] += x;
+        s_slots[tid] += y;
+        __syncthreads();
+    }
+    int h = s_rows[tid] - nr, slot = s_slots[tid] - ns;
+    for (int k = k0; k < k1; ++k)
+        if (first(k)) {
+            const int e = last(k);
+            if (h < most) rows[h] = make_int4(keys[(int64_t)k * unit], k - 1, e, slot);
+            ++h;
+            slot += e - k + 2;
+        }
+    __syncthreads();
+    const int total = min(s_rows[1023], most);
+    for (int r = tid >> 6; r < total; r += 16) {
+        const int4 v = rows[r];
+        for (int k = v.y + 1 + (tid & 63); k <= v.z; k += 64) cut[k] = make_int2(v.w, v.w - v.y);
+    }
+    if (tid == 0) *n_rows = total;
+}
+
 int stream_grid(int64_t n, int per_thread)
 {
     const int64_t per_block = (int64_t)kSortBlock * per_thread;
@@ -808,6 +870,14 @@ hipError_t launch_small_units(const int32_t* keys, int64_t n, int unit, int unit
 {
     if (n < 1 || n > kSmallNnz || units < 1 || units > 4096) return hipErrorInvalidValue;
     hipLaunchKernelGGL(small_units, dim3(1), dim3(1024), 0, st, keys, (int)n, unit, units, cut, left, split, arrived, info);
+    return hipGetLastError();
+}
+
+hipError_t launch_heavy_rows(const int32_t* keys, int64_t n, int64_t unit, int n_units, int4* rows, int2* cut,
+                             int32_t* n_rows, hipStream_t st)
+{
+    if (n_units < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(heavy_rows, dim3(1), dim3(1024), 0, st, keys, n, unit, n_units, rows, cut, n_rows);
     return hipGetLastError();
 }
 

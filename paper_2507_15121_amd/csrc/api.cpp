@@ -686,7 +686,8 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
             return small && status.small[d][1] <= (nnz <= amped::kSmallSplitNnz ? amped::kSmallSpan : 0);
         };
         auto share_bytes = [&](int d) {
-            return one_launch(d) && status.small[d][0] > 0 ? Arena::step(units * 2 * amped::kSmallCols * 4) : 0;
+            return one_launch(d) && status.small[d][0] > 0
+                       ? Arena::step((units + (size_t)status.small[d][0]) * amped::kSmallCols * 8) : 0;
         };
         size_t list_bytes = 0;
         for (int d = 0; d < order; ++d)
@@ -711,7 +712,10 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
                 m.small.n_units = (int)units;
                 m.small.zrows = zero + tot.shared;
                 m.small.n_zero = tot.lone;
-                if (status.small[d][0] > 0) m.small.share = la.take<float>(units * 2 * amped::kSmallCols);
+                if (status.small[d][0] > 0) {
+                    m.small.share = la.take<uint64_t>((units + (size_t)status.small[d][0]) * amped::kSmallCols);
+                    HIP_OR_FAIL(hipMemsetAsync(m.small.share, 0, share_bytes(d), stream), "hipMemset(shares)");
+                }
             }
             if (m.n_zero + m.n_gaps > 0)
                 HIP_OR_FAIL(amped::launch_fill_rows(m.out_idx, nnz, dims[d], t->unit, counts[d], tot.shared, zero, gaps,

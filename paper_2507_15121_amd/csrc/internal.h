@@ -288,7 +288,7 @@ struct ModeDev {
         const int32_t* left = nullptr;     // [n_units + 1] the split row that a cut lies in, or -1
         const int32_t* split = nullptr;    // pairs: a split row's first unit, its number of units
         unsigned* arrived = nullptr;       // per split row, 0 between launches
-        float* share = nullptr;            // [n_units][2][kSmallCols], when any row is split
+        uint64_t* share = nullptr;         // [n_units + split rows][kSmallCols], 0 between launches, when any row is split
         const int32_t* zrows = nullptr;    // the untouched rows of the zero-row list
         int64_t n_zero = 0;
     } small;

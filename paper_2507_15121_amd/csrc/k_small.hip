@@ -20,6 +20,9 @@
 namespace amped {
 namespace dev {
 
+constexpr uint64_t kShareMark = uint64_t(1) << 32;
+constexpr int kShareTries = 1 << 14;
+
 // Lane s of a group reads RPL columns from min(s RPL, ncols - RPL) on, as the
 // large kernel's instances for any rank do.
 template <int NIN, int LPR, int RPL, typename T>
@@ -191,46 +194,61 @@ __global__ void __launch_bounds__(64) small_kernel(const SmallParams p)
                     put(cur, sum);
                     return;
                 }
-                // this unit's share of split row h, counted in once it is written; the
-                // last unit to arrive adds all shares.  Shares and counters move by
-                // agent-scope atomic stores, adds and loads only, which this GPU
-                // performs past the per-XCD L2s, so a share is in its place when its
-                // store has been acknowledged: the fences wait for that (and keep the
-                // order), without the write-back of a whole L2 that an agent-scope
-                // release would add to every unit.
+                // This unit's share of split row h, then the unit is counted in; the last
+                // one to arrive adds all shares.  The counter says who adds, not that the
+                // others' shares are visible yet: relaxed atomics on different locations
+                // have no order between blocks.  So a share is one 64-bit atomic of its
+                // value and a mark, and the adder reads a share until the mark is there,
+                // which is the order of a single location; the share's wave has counted
+                // itself in and waits for nobody, so it comes.  (No fences: an agent-scope
+                // release writes an L2 back, which took split modes of 250k nonzeros from 9
+                // to 18 us.)  The adder clears the marks for the next launch.
                 const int h = from_left ? left : right;
-                float* mine = p.share + ((int64_t)2 * unit + (from_left ? 0 : 1)) * kSmallCols;
+                uint64_t* mine = p.share + (int64_t)(unit + h) * kSmallCols + lane;
 #pragma unroll
                 for (int i = 0; i < CL; ++i)
-                    __hip_atomic_store(mine + lane + 64 * i, sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                __builtin_amdgcn_s_waitcnt(0);
+                    __hip_atomic_store(mine + 64 * i, kShareMark | __float_as_uint(sum[i]), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
                 const int f = p.split[2 * h], n = p.split[2 * h + 1];   // its first unit and how many
                 unsigned before = 0;
                 if (lane == 0)
                     before = __hip_atomic_fetch_add(p.arrived + h, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 before = (unsigned)__builtin_amdgcn_readfirstlane((int)before);
                 if (before + 1 != (unsigned)n) return;
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
                 float total[CL];
 #pragma unroll
                 for (int i = 0; i < CL; ++i) total[i] = 0.f;
+                uint64_t* const all = p.share + (int64_t)(f + h) * kSmallCols + lane;
                 for (int k0 = 0; k0 < n; k0 += 8) {
-                    float x[8][CL];
+                    uint64_t x[8][CL];
+                    bool here = false;
+                    // (bounded all the same: calls of one mode at once, which the API
+                    // forbids, could leave a mark out for good)
+                    for (int tries = 0; !here && tries < kShareTries; ++tries) {
+                        here = true;
+#pragma unroll
+                        for (int k = 0; k < 8; ++k)
+#pragma unroll
+                            for (int i = 0; i < CL; ++i) {
+                                x[k][i] = k0 + k < n ? __hip_atomic_load(all + (int64_t)(k0 + k) * kSmallCols + 64 * i,
+                                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                                     : kShareMark;
+                            }
+#pragma unroll
+                        for (int k = 0; k < 8; ++k)
+#pragma unroll
+                            for (int i = 0; i < CL; ++i) here = here && (x[k][i] & kShareMark) != 0;
+                        here = __builtin_amdgcn_ballot_w64(!here) == 0;
+                    }
 #pragma unroll
                     for (int k = 0; k < 8; ++k)
 #pragma unroll
                         for (int i = 0; i < CL; ++i) {
-                            // the first unit holds the row's start at its right end
-                            const int64_t slot = (int64_t)2 * (f + k0 + k) + (k0 + k == 0 ? 1 : 0);
-                            x[k][i] = k0 + k < n ? __hip_atomic_load(p.share + slot * kSmallCols + lane + 64 * i,
-                                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                                 : 0.f;
+                            total[i] += __uint_as_float((uint32_t)x[k][i]);
+                            if (k0 + k < n)
+                                __hip_atomic_store(all + (int64_t)(k0 + k) * kSmallCols + 64 * i, uint64_t(0),
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         }
-#pragma unroll
-                    for (int k = 0; k < 8; ++k)
-#pragma unroll
-                        for (int i = 0; i < CL; ++i) total[i] += x[k][i];
                 }
                 put(cur, total);
                 if (lane == 0)   // for the next launch

@@ -1108,7 +1108,7 @@ struct SmallParams {
     const int32_t* left;     // [n_units + 1] the split row that cut k lies in, or -1
     const int32_t* split;    // per split row: its first unit, its number of units
     unsigned* arrived;       // per split row, 0 between launches
-    float* share;            // [n_units][2][kSmallCols]
+    uint64_t* share;         // [n_units + split rows][kSmallCols]: unit u's of split row h is u + h; 0 between launches
     bool vec4;
     const int32_t* zrows;
     const int32_t* gaps;

@@ -215,9 +215,9 @@ __global__ void __launch_bounds__(64) small_kernel(const SmallParams p)
                     before = __hip_atomic_fetch_add(p.arrived + h, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 before = (unsigned)__builtin_amdgcn_readfirstlane((int)before);
                 if (before + 1 != (unsigned)n) return;
-                float total[CL];
+                double total[CL];   // fp64: the error does not grow with the units
 #pragma unroll
-                for (int i = 0; i < CL; ++i) total[i] = 0.f;
+                for (int i = 0; i < CL; ++i) total[i] = 0.0;
                 uint64_t* const all = p.share + (int64_t)(f + h) * kSmallCols + lane;
                 for (int k0 = 0; k0 < n; k0 += 8) {
                     uint64_t x[8][CL];
@@ -244,13 +244,15 @@ __global__ void __launch_bounds__(64) small_kernel(const SmallParams p)
                     for (int k = 0; k < 8; ++k)
 #pragma unroll
                         for (int i = 0; i < CL; ++i) {
-                            total[i] += __uint_as_float((uint32_t)x[k][i]);
+                            total[i] += (double)__uint_as_float((uint32_t)x[k][i]);
                             if (k0 + k < n)
                                 __hip_atomic_store(all + (int64_t)(k0 + k) * kSmallCols + 64 * i, uint64_t(0),
                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         }
                 }
-                put(cur, total);
+#pragma unroll
+                for (int i = 0; i < CL; ++i) sum[i] = (float)total[i];
+                put(cur, sum);
                 if (lane == 0)   // for the next launch
                     __hip_atomic_store(p.arrived + h, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             };

@@ -64,3 +64,26 @@ def test_shares_in_a_graph():
         np.testing.assert_array_equal(out.cpu().numpy(), ref)
         np.testing.assert_array_equal(hip_mttkrp(t, 0, dfac), ref)
     t.close()
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32])
+@pytest.mark.parametrize("factors", ["f32", "bf16"])
+def test_shares_are_added_in_fp64(rank, factors):
+    """The longest split row of a launch, 64 units, all terms positive.  The result is
+    rounded once (2^-24); a share is a sum of up to 4 + 32 terms of the 64-nonzero unit
+    (2^-23 sqrt(36 / 36) at most), independent over 64 of them: 1.5e-8.  (Added in fp32
+    the 64 shares alone would bring 2^-23 sqrt(64 / 36) = 1.6e-7.)"""
+    rng = np.random.default_rng(rank)
+    dims, nnz = (20, 400, 300), 4096 + 900
+    idx = np.stack([rng.integers(0, d, nnz) for d in dims]).astype(np.int32)
+    idx[0] = np.where(np.arange(nnz) < 4000, 7, rng.integers(8, 20, nnz))
+    val = rng.random(nnz, dtype=np.float32) + np.float32(0.1)
+    fac = [rng.random((d, rank), dtype=np.float32) + np.float32(0.1) for d in dims]
+    t = api.Tensor(idx, val, dims)
+    dev = dev_factors(fac, torch.bfloat16 if factors == "bf16" else None)
+    fac = [f.float().cpu().numpy() for f in dev]
+    at = np.flatnonzero(idx[0] == 7)
+    ref = (val[at].astype(np.float64)[:, None] * fac[1][idx[1, at]].astype(np.float64) * fac[2][idx[2, at]].astype(np.float64)).sum(0)
+    got = hip_mttkrp(t, 0, dev, bf16=factors == "bf16")[7]
+    assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 2.0 ** -24 + 1.5e-8
+    t.close()

@@ -36,6 +36,7 @@
 #include <utility>
 
 #include "internal.h"
+#include "lanes.h"
 
 namespace amped {
 namespace dev {
@@ -1119,13 +1120,6 @@ using SmallFn = void (*)(const SmallParams);
 // Vector instances exist for up to 4 input modes; every other case takes the
 // column-tile path.
 constexpr int kMaxVecNin = 4;
-
-// How the columns of a launch are spread over a lane group: lpr lanes of rpl
-// columns (lpr = 0: the column-tile path), exactly or with overlap.
-struct Lanes {
-    int lpr = 0, rpl = 1;
-    bool exact = true;
-};
 
 // Kernel pickers, one translation unit each (compiled in parallel).
 KernelFn pick_mttkrp_f32(int nin, Lanes v, bool buf);

@@ -66,33 +66,6 @@ bool fits_buffer(int64_t rows, int rank, int elem_bytes)
     return (uint64_t)(rows + 1) * (uint64_t)rank * (uint64_t)elem_bytes <= (1ull << 32);
 }
 
-// How a launch spreads `cols` columns over a lane group.  One load per lane
-// covers the row, so the loads of a nonzero take cols * size / 16 lanes of the
-// address unit's time instead of a whole wave's (the column-tile path walks one
-// nonzero per wave step: 597 us for all modes of 3M nonzeros at rank 20, against
-// 167 us here; their gradients 1513 and 186 us).  fp32 rows: 4 columns (16 bytes) per lane.
-//  bfloat16 rows of up to 32 columns: 4 columns (8 bytes), so that a wave still
-// covers 8 rows per gather at rank 32, except above 16 columns with three or more
-// gathered factors, where 16-byte lanes (16 rows per gather instruction) measured
-// faster, in every mode of the order-4 tensors, and slower on the order-3 ones;
-// wider ones 8 columns.  Rows start on 4 bytes, so odd bfloat16 ranks take the
-// column-tile path, as do fewer columns than a lane reads.
-Lanes choose_lanes(int cols, FactorType ft, int nin)
-{
-    Lanes v;
-    const bool f32 = ft == FactorType::F32;
-    v.rpl = f32 || cols <= 16 || (cols <= 32 && nin <= 2) ? 4 : 8;
-    if (cols < v.rpl || (!f32 && cols % 2)) return Lanes{};
-    const int need = (cols + v.rpl - 1) / v.rpl;
-    v.lpr = v.rpl == 4 ? 2 : 4;
-    while (v.lpr < need) v.lpr *= 2;
-    v.exact = cols == v.lpr * v.rpl && v.lpr >= 4 && v.lpr <= (f32 ? 32 : 16);
-    return v;
-}
-
-// Most columns of one launch on the vector path.
-constexpr int kMaxVecCols = 256;
-
 // Launch shape of an MTTKRP-kernel instance on the current device: the
 // hot-row cache slots K (largest power of two whose LDS, with the kernel's
 // static LDS, fits one block; capped by AMPED_HOT_MAX if set, 0 = no cache),
@@ -414,11 +387,7 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
         if (!fits_buffer(a.in_rows[w], a.rank, eb)) buf = false;
     const bool grad = a.kind != Kind::Mttkrp;   // the residual forms read the output mode's factor
     if (grad && !fits_buffer(m.rows, a.rank, 4)) buf = false;
-    // ranks above one launch's columns: equal launches, of whole 16-byte pieces
-    const int parts = (a.rank + kMaxVecCols - 1) / kMaxVecCols;
-    int tile = parts == 1 ? a.rank : ((a.rank + parts - 1) / parts + 3) & ~3;
-    Lanes v = choose_lanes(tile, a.ftype, a.nin);
-    if (tile != a.rank) v.exact = false;
+    auto [tile, v] = split_columns(a.rank, a.ftype, a.nin);
     if (!grad && buf && v.lpr && m.small.n_units > 0)
         if (SmallFn small = pick_small(a.nin, a.ftype, v)) return launch_small(a, small, tile, eb);
     // An exact rank's instance with the hot-row cache is used where the cache

@@ -89,6 +89,7 @@ struct amped_tensor_s {
     std::vector<void*> pinned;
     std::vector<int32_t> hperm[kMaxOrder];  // kept permutations (keep_perm)
     void* ring[2] = {};                     // packed blocks of half a shard
+    size_t ring_offsets = 0;                // where the blocks' offsets lie behind them, if they are copied too
     int32_t* stage = nullptr;               // (order + 1) arrays of stage_stride() entries
     int next_ring = 0;
     bool ring_used[2] = {};                 // consumed[] holds the buffer's last use
@@ -222,9 +223,10 @@ amped_status check_device(int* dev)
         }                                                \
     } while (0)
 
-// A mode's row lists (zero rows, hot-row tables, long gaps) to the device,
-// and its sizes.
-amped_status upload_tables(amped_tensor_s* t, ModeDev& m, int d, const HostModeLayout& lay, void* queues, void* aux)
+// A mode's row lists (zero rows, long gaps, hot-row tables where launches use them) to
+// the device, and its sizes.
+amped_status upload_tables(amped_tensor_s* t, ModeDev& m, int d, const HostModeLayout& lay, void* queues, void* aux,
+                           bool hot)
 {
     amped_status st = AMPED_OK;
     void* p = nullptr;
@@ -234,9 +236,11 @@ amped_status upload_tables(amped_tensor_s* t, ModeDev& m, int d, const HostModeL
                     "hipMemcpy(zero rows)");
         m.zero_rows = static_cast<int32_t*>(p);
     }
-    HIP_OR_FAIL(t->alloc(&p, lay.hot.size() * 4), "hipMalloc(hot rows)");
-    HIP_OR_FAIL(hipMemcpy(p, lay.hot.data(), lay.hot.size() * 4, hipMemcpyHostToDevice), "hipMemcpy(hot rows)");
-    m.hot = static_cast<int32_t*>(p);
+    if (hot) {
+        HIP_OR_FAIL(t->alloc(&p, lay.hot.size() * 4), "hipMalloc(hot rows)");
+        HIP_OR_FAIL(hipMemcpy(p, lay.hot.data(), lay.hot.size() * 4, hipMemcpyHostToDevice), "hipMemcpy(hot rows)");
+        m.hot = static_cast<int32_t*>(p);
+    }
     if (!lay.gaps.empty()) {
         HIP_OR_FAIL(t->alloc(&p, lay.gaps.size() * 4), "hipMalloc(gaps)");
         HIP_OR_FAIL(hipMemcpy(p, lay.gaps.data(), lay.gaps.size() * 4, hipMemcpyHostToDevice), "hipMemcpy(gaps)");
@@ -260,8 +264,15 @@ cleanup:
 
 // Host-resident layouts: the host order builder sorts every mode, the layout
 // arrays are gathered into pinned host memory, and the device receives the
-// row lists, two shard staging buffers, a copy stream and its events.
-amped_status build_host_layout(amped_tensor_s* t, const int32_t* indices, const float* values)
+// row lists, the staging buffers, a copy stream and its events.
+//  The blocks' offsets stay on the device, unless the cap does not hold them (they grow
+// with the nonzeros): then each half shard's are copied with it, a second small copy.
+// What is admitted under a cap is two shards of plain arrays, the row lists and the
+// hot-row tables.  The staging arrays are one of them; a packed block is at least 32
+// bytes shorter than its plain arrays, which pays for its offset; the blocks at a shard's
+// ends, and the queues, take less than the hot-row tables, which only shards have that
+// are large enough for the difference.
+amped_status build_host_layout(amped_tensor_s* t, const int32_t* indices, const float* values, int64_t cap)
 {
     const int order = t->order;
     const int64_t nnz = t->nnz;
@@ -284,7 +295,7 @@ amped_status build_host_layout(amped_tensor_s* t, const int32_t* indices, const 
     t->stage = static_cast<int32_t*>(p);
     try {
         const std::vector<int32_t> lex = amped::lex_order(order, t->dims, nnz, indices);
-        size_t most = 0;   // bytes of the longest block
+        size_t most = 0, offsets = 0;   // bytes of the longest block, of all blocks' offsets
         for (int d = 0; d < order; ++d) {
             HostModeLayout lay;
             amped::mode_order(t->dims, nnz, indices, lex, d, lay.perm);
@@ -295,19 +306,30 @@ amped_status build_host_layout(amped_tensor_s* t, const int32_t* indices, const 
             h.data = static_cast<uint32_t*>(p);
             h.fill(nnz, indices, values, lay.perm.data());
             for (int64_t b = 0; b < h.blocks(); ++b) most = std::max(most, (size_t)(h.bytes(b + 1) - h.bytes(b)));
-            if (h.blocks() > 0) {
-                HIP_OR_FAIL(t->alloc(&p, h.offset.size() * 4), "hipMalloc(block offsets)");
-                HIP_OR_FAIL(hipMemcpy(p, h.offset.data(), h.offset.size() * 4, hipMemcpyHostToDevice),
-                            "hipMemcpy(block offsets)");
-                h.dev_offset = static_cast<uint32_t*>(p);
-            }
-            st = upload_tables(t, t->mode[d], d, lay, queues, aux);
+            offsets += h.blocks() > 0 ? h.offset.size() * 4 : 0;
+            st = upload_tables(t, t->mode[d], d, lay, queues, aux, t->stage_len >= amped::kHotMinNnz);
             if (st != AMPED_OK) return st;
             if (t->keep_perm) t->hperm[d] = std::move(lay.perm);
         }
         // half of the most blocks that a shard touches
         const size_t half = ((size_t)(t->stage_len / amped::kPackBlock) + 3) / 2;
-        for (int b = 0; b < 2; ++b) HIP_OR_FAIL(t->alloc(&t->ring[b], half * most), "hipMalloc(staging)");
+        t->ring_offsets = half * most;
+        const bool travel = cap > 0 && t->device_bytes + (int64_t)(2 * half * most + offsets) > cap;
+        for (int b = 0; b < 2; ++b)
+            HIP_OR_FAIL(t->alloc(&t->ring[b], half * most + (travel && nnz > 0 ? (half + 1) * 4 : 0)), "hipMalloc(staging)");
+        for (int d = 0; d < order && nnz > 0; ++d) {
+            amped::PackedMode& h = t->hmode[d];
+            const size_t bytes = h.offset.size() * 4;
+            if (travel) {
+                HIP_OR_FAIL(t->host_alloc(&p, bytes), "hipHostMalloc(block offsets)");
+                std::memcpy(p, h.offset.data(), bytes);
+                h.pinned_offset = static_cast<uint32_t*>(p);
+            } else {
+                HIP_OR_FAIL(t->alloc(&p, bytes), "hipMalloc(block offsets)");
+                HIP_OR_FAIL(hipMemcpy(p, h.offset.data(), bytes, hipMemcpyHostToDevice), "hipMemcpy(block offsets)");
+                h.dev_offset = static_cast<uint32_t*>(p);
+            }
+        }
     } catch (const std::bad_alloc&) {
         return fail(AMPED_ERR_NOMEM, "host allocation failed");
     }
@@ -476,7 +498,7 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
             for (int d = 0; d < order; ++d) {
                 HostModeLayout lay;
                 amped::mode_tables_sorted(nullptr, 0, dims[d], t->chunk, lay);
-                st = upload_tables(t, t->mode[d], d, lay, queues, aux);
+                st = upload_tables(t, t->mode[d], d, lay, queues, aux, false);
                 if (st != AMPED_OK) return st;
             }
             t->loss_dev = t->mode[0];
@@ -500,10 +522,13 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
         const int rw = (int)amped::record_words(order), last = order - 1;
         bool records = rw <= order + 1 || cap == 0;
         const int blocks = amped::row_list_blocks(nnz);
-        const size_t scratch_words = (size_t)amped::sort_scratch_words(nnz);
+        const bool hot = nnz >= amped::kHotMinNnz;   // hot-row tables, where launches use them
+        size_t scratch_words = 0;
+        for (int w = 0; w < order; ++w)
+            scratch_words = std::max(scratch_words, (size_t)amped::sort_scratch_words(nnz, bits_for(dims[w] - 1)));
         auto temp_bytes = [&](bool rec) {
             return Arena::step(sizeof(Status)) + (size_t)order * Arena::step((size_t)blocks * 16) +
-                   Arena::step(amped::kHotMax * 8) + Arena::step(scratch_words * 4) +
+                   (hot ? Arena::step(amped::kHotMax * 8) : 0) + Arena::step(scratch_words * 4) +
                    (order == 2 ? 2 * Arena::step(n * 4) : 0) +
                    std::max(rec ? Arena::step((size_t)rw * 4 * n) : 0, (size_t)(order + 1) * Arena::step(n * 4));
         };
@@ -518,7 +543,7 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
         Status* d_status = ta.take<Status>(1);
         uint32_t* counts[kMaxOrder];
         for (int d = 0; d < order; ++d) counts[d] = ta.take<uint32_t>((size_t)blocks * 4);
-        unsigned long long* best = ta.take<unsigned long long>(amped::kHotMax);
+        unsigned long long* best = ta.take<unsigned long long>(hot ? amped::kHotMax : 0);
         uint32_t* scratch = ta.take<uint32_t>(scratch_words);
         // The sorts' second key buffer and second order buffer are columns of the last
         // mode, the lexicographic order is one of mode 1's (order 2 has too few), and
@@ -679,8 +704,7 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
                 goto cleanup;
             }
 
-        // the row lists, and the hot-row tables where launches use them
-        const bool hot = nnz >= amped::kHotMinNnz;
+        // the row lists and hot-row tables
         // the shares of rows that span units, where the mode takes the one launch
         auto one_launch = [&](int d) {
             return small && status.small[d][1] <= (nnz <= amped::kSmallSplitNnz ? amped::kSmallSpan : 0);
@@ -778,7 +802,6 @@ amped_status stream_shards(amped_tensor_s* t, int d, const ModeDev& base, hipStr
     const int64_t stride = t->stage_stride();
     amped::UnpackArgs u;
     u.order = order;
-    u.offset = h.dev_offset;
     for (int j = 0; j < order - 1; ++j) u.bits[j] = h.bits[j];
     int i = 0;
     for (int64_t start = 0; start < nnz; ++i) {
@@ -800,10 +823,17 @@ amped_status stream_shards(amped_tensor_s* t, int d, const ModeDev& base, hipStr
                                     (size_t)(h.bytes(h1) - h.bytes(h0)), hipMemcpyHostToDevice, t->copy_stream)) !=
                 hipSuccess)
                 return hip_fail(e, "hipMemcpyAsync(shard)");
+            u.offset = h.dev_offset + h0;
+            if (!h.dev_offset) {
+                uint32_t* to = reinterpret_cast<uint32_t*>(static_cast<char*>(t->ring[b]) + t->ring_offsets);
+                if ((e = hipMemcpyAsync(to, h.pinned_offset + h0, (size_t)(h1 - h0 + 1) * 4, hipMemcpyHostToDevice,
+                                        t->copy_stream)) != hipSuccess)
+                    return hip_fail(e, "hipMemcpyAsync(block offsets)");
+                u.offset = to;
+            }
             if ((e = hipEventRecord(t->copied[b], t->copy_stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
             if ((e = hipStreamWaitEvent(s, t->copied[b], 0)) != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
             u.packed = static_cast<const uint32_t*>(t->ring[b]);
-            u.first = h0;
             u.blocks = h1 - h0;
             for (int j = 0; j <= order; ++j) u.to[j] = t->stage + j * stride + (h0 - b0) * amped::kPackBlock;
             if ((e = amped::launch_unpack(u, s)) != hipSuccess) return hip_fail(e, "unpack");
@@ -912,7 +942,8 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
     // modes not yet built; what a cap admits is unchanged.)
     const int64_t sort_counts = (nnz + 4095) / 4096 * 256;
     const int64_t sort_bytes = 16 * nnz + 4 * (sort_counts + (sort_counts + 4095) / 4096 + 64);
-    // host-resident layouts: two shard buffers of whole chunks instead
+    // host-resident layouts: two shard buffers of whole chunks instead (what they are
+    // filled with now: build_host_layout)
     const int64_t n_chunks = (nnz + chunk - 1) / chunk;
     const int64_t shard_chunks =
         std::max<int64_t>(1, std::min(((shard_opt > 0 ? shard_opt : (int64_t)1 << 25) + chunk - 1) / chunk,
@@ -953,7 +984,7 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
     if (host_layout) {
         t->host_layout = true;
         t->stage_len = stage_len;
-        st = build_host_layout(t, indices, values);
+        st = build_host_layout(t, indices, values, cap);
     } else {
         st = build_device_layout(t, indices, values, cap);
     }

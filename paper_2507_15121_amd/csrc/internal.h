@@ -2,6 +2,7 @@
 // the HIP kernel launchers.  Not installed; not part of the ABI.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -162,8 +163,8 @@ bool is_lexicographic_prefix(int order, int64_t nnz, const int32_t* idx, int64_t
 // be needed).  The first pass reads (keys, vals) and writes
 // (kbuf[first], vbuf[first]), the next ones alternate between the two buffer
 // pairs; vals NULL: the positions.  keys or vals may be a buffer of the pair that
-// is not written first.  scratch holds sort_scratch_words(n) 32-bit words.
-int64_t sort_scratch_words(int64_t n);
+// is not written first.  scratch holds sort_scratch_words(n, key_bits) 32-bit words.
+int64_t sort_scratch_words(int64_t n, int key_bits);
 int sort_passes(int key_bits);
 hipError_t launch_stable_sort(const uint32_t* keys, const int32_t* vals, uint32_t* const* kbuf, int32_t* const* vbuf,
                               int first, uint32_t* scratch, int64_t n, int key_bits, hipStream_t st);
@@ -205,12 +206,17 @@ constexpr int64_t heavy_rows_max(int64_t n_units) { return n_units / kHeavyCuts 
 constexpr int64_t heavy_slots_max(int64_t n_units) { return n_units + heavy_rows_max(n_units); }
 hipError_t launch_heavy_rows(const int32_t* keys, int64_t n, int64_t unit, int n_units, int4* rows, int2* cut,
                              int32_t* n_rows, hipStream_t st);
-// Device bytes that units shorter than a chunk take beside the layouts: the tables and
-// slots of heavy rows.
+// The most device bytes that units sized by the library take beside the layouts: the
+// tables and slots of heavy rows, the tables and shares of the one-launch MTTKRP.
 inline int64_t short_unit_bytes(int order, int64_t nnz, int64_t unit)
 {
     const int64_t n = (nnz + unit - 1) / unit;
-    return order * (8 * (n + kHeavyCuts) + 16 * heavy_rows_max(n) + heavy_slots_max(n) * kSlotCols * 4 + 3 * 256);
+    int64_t mode = 8 * (n + kHeavyCuts) + 16 * heavy_rows_max(n) + heavy_slots_max(n) * kSlotCols * 4 + 3 * 256;
+    if (nnz > 0 && nnz <= kSmallNnz) {
+        const int64_t u = (nnz + small_unit(nnz) - 1) / small_unit(nnz), split = std::min(u, nnz / (kSmallRow + 1));
+        mode += 8 * (u + 1) + 12 * u + (u + split) * kSmallCols * 8 + 5 * 256;
+    }
+    return order * mode;
 }
 // Hot-row tables (kHotTableLen entries) from sorted keys; best: kHotMax zeros.
 hipError_t launch_hot_tables(const int32_t* keys, int64_t n, unsigned long long* best, int32_t* hot, hipStream_t st);
@@ -234,7 +240,8 @@ struct PackedMode {
     int mode = 0, in_mode[kMaxOrder - 1] = {};
     std::vector<uint32_t> offset;          // [blocks + 1]
     uint32_t* data = nullptr;
-    uint32_t* dev_offset = nullptr;        // offset on the device
+    uint32_t* dev_offset = nullptr;        // offset on the device, or (dev_offset NULL)
+    uint32_t* pinned_offset = nullptr;     // in pinned memory, copied with the blocks
 
     int64_t blocks() const { return offset.empty() ? 0 : (int64_t)offset.size() - 1; }
     int64_t bytes(int64_t block) const { return offset.empty() ? 0 : (int64_t)offset[block] * 32; }
@@ -247,15 +254,14 @@ struct PackedMode {
 };
 
 // -------------------------------------------------------------- device layout
-// Packed blocks [first, first + blocks) (offset: the mode's, on the device; packed
-// holds them from block `first` on) to plain arrays: to[0] output indices, then
-// the input indices, then the values.
+// The blocks at `packed` (block k starts 8 (offset[k] - offset[0]) words in) to plain
+// arrays: to[0] output indices, then the input indices, then the values.
 struct UnpackArgs {
     int order = 0;
     int bits[kMaxOrder - 1] = {};
     const uint32_t* packed = nullptr;
     const uint32_t* offset = nullptr;
-    int64_t first = 0, blocks = 0;
+    int64_t blocks = 0;
     int32_t* to[kMaxOrder + 1] = {};
 };
 hipError_t launch_unpack(const UnpackArgs& u, hipStream_t st);

@@ -264,10 +264,12 @@ static int64_t scan_group(int64_t nblocks)
     return g;
 }
 
-int64_t sort_scratch_words(int64_t n)
+int64_t sort_scratch_words(int64_t n, int key_bits)
 {
     const int64_t nblocks = (n + kTile - 1) / kTile, group = scan_group(nblocks);
-    return (nblocks + (nblocks + group - 1) / group + 1) << kMaxDigitBits;
+    const int passes = sort_passes(key_bits);
+    if (passes == 0) return 0;
+    return (nblocks + (nblocks + group - 1) / group + 1) << ((key_bits + passes - 1) / passes);
 }
 
 hipError_t launch_iota(int32_t* a, int64_t n, hipStream_t st)
@@ -803,7 +805,7 @@ __global__ void __launch_bounds__(256) unpack_kernel(UnpackArgs u)
     const int lane = threadIdx.x & 63;
     const int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (k >= u.blocks) return;
-    const uint32_t* w = u.packed + (int64_t)(u.offset[u.first + k] - u.offset[u.first]) * 8;
+    const uint32_t* w = u.packed + (int64_t)(u.offset[k] - u.offset[0]) * 8;
     const uint32_t base = w[0], kb = w[1];
     w += 8;
     auto column = [&](uint32_t b, uint32_t add, int32_t* to) {

@@ -34,7 +34,11 @@ amped_status fail(amped_status st, const char* fmt, ...)
     va_start(ap, fmt);
     std::vsnprintf(buf, sizeof(buf), fmt, ap);
     va_end(ap);
-    g_err = buf;
+    try {
+        g_err = buf;
+    } catch (const std::bad_alloc&) {   // the status alone then
+        g_err.clear();
+    }
     return st;
 }
 
@@ -113,10 +117,21 @@ struct amped_tensor_s {
         bool have_grams = false;   // G matches the factors the last sweep wrote
     } als;
 
+    // space for one more entry, so that adding it cannot throw
+    static bool room(std::vector<void*>& v)
+    {
+        try {
+            if (v.size() == v.capacity()) v.reserve(2 * v.size() + 8);
+        } catch (const std::bad_alloc&) {
+            return false;
+        }
+        return true;
+    }
     hipError_t alloc(void** p, size_t bytes)
     {
         *p = nullptr;
         if (bytes == 0) return hipSuccess;
+        if (!room(allocs)) return hipErrorOutOfMemory;
         hipError_t e = hipMalloc(p, bytes);
         if (e == hipSuccess) {
             allocs.push_back(*p);
@@ -136,6 +151,7 @@ struct amped_tensor_s {
     {
         *p = nullptr;
         if (bytes == 0) return hipSuccess;
+        if (!room(pinned)) return hipErrorOutOfMemory;
         hipError_t e = hipHostMalloc(p, bytes, hipHostMallocDefault);
         if (e == hipSuccess) pinned.push_back(*p);
         return e;
@@ -909,10 +925,11 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
     // this call checks them here first, since a bad index is reported before a
     // bad option, a low cap or a missing device.
     auto unless_bad_index = [&](amped_status err) {
-        const std::string msg = g_err;
+        std::string msg;
+        msg.swap(g_err);
         const amped_status bad = validate_range(order, dims, nnz, indices);
         if (bad != AMPED_OK) return bad;
-        g_err = msg;
+        g_err.swap(msg);
         return err;
     };
     int64_t chunk = amped::kDefaultChunk, cap = 0, shard_opt = 0;
@@ -981,12 +998,16 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
         t->unit = host_layout ? amped::stream_work_unit(std::min(stage_len, nnz)) : amped::work_unit(nnz);
     t->device = dev;
     t->keep_perm = keep_perm;
-    if (host_layout) {
-        t->host_layout = true;
-        t->stage_len = stage_len;
-        st = build_host_layout(t, indices, values, cap);
-    } else {
-        st = build_device_layout(t, indices, values, cap);
+    try {
+        if (host_layout) {
+            t->host_layout = true;
+            t->stage_len = stage_len;
+            st = build_host_layout(t, indices, values, cap);
+        } else {
+            st = build_device_layout(t, indices, values, cap);
+        }
+    } catch (const std::bad_alloc&) {
+        st = fail(AMPED_ERR_NOMEM, "host allocation failed");
     }
     if (st != AMPED_OK) {
         (void)hipDeviceSynchronize();

@@ -1013,7 +1013,8 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
         (void)hipDeviceSynchronize();
         t->free_all();
         delete t;
-        return st;
+        // (the build may have stopped before its own check)
+        return st == AMPED_ERR_RANGE || host_layout ? st : unless_bad_index(st);
     }
     *out = t;
     return AMPED_OK;

@@ -255,18 +255,27 @@ static void host_failures(const Coo& c, const amped_options& o, const char* what
     }
 }
 
-// the n-th device allocation fails, for every n
-static void device_failures(const Coo& c, const amped_options& o, const char* what)
+// the n-th device allocation fails, for every n; a bad index is reported before that
+static void device_failures(Coo c, const amped_options& o, const char* what)
 {
-    for (long n = 0; n < 100; ++n) {
-        amped_tensor_t t = nullptr;
-        g.left = n;
-        const amped_status st = c.create(&o, &t);
-        g.left = -1;
-        CHECK(st == AMPED_OK || st == AMPED_ERR_NOMEM, "%s: status %d (device allocation %ld)", what, (int)st, n);
-        if (t) amped_tensor_destroy(t);
-        clean(what);
-        if (st == AMPED_OK) return;
+    for (int bad = 0; bad < 2; ++bad) {
+        if (bad && c.nnz == 0) return;
+        if (bad) c.idx[(size_t)(c.nnz / 2)] = (int32_t)c.dims[0];
+        for (long n = 0; n < 100; ++n) {
+            amped_tensor_t t = nullptr;
+            g.left = n;
+            amped_status st = c.create(&o, &t);
+            const bool failed = g.left == 0;
+            g.left = -1;
+            if (bad && !(st == AMPED_OK && !failed))   // (the device's own check does nothing here)
+                CHECK(st == AMPED_ERR_RANGE, "%s: status %d with a bad index (device allocation %ld)", what, (int)st, n);
+            if (!bad) CHECK(st == AMPED_OK || st == AMPED_ERR_NOMEM, "%s: status %d (device allocation %ld)", what, (int)st, n);
+            if (st == AMPED_ERR_RANGE)
+                CHECK(std::strstr(amped_last_error(), "indices[0]"), "%s: message %s", what, amped_last_error());
+            if (t) amped_tensor_destroy(t);
+            clean(what);
+            if (st == AMPED_OK) break;
+        }
     }
 }
 

@@ -36,16 +36,18 @@ class SparseCPLoss(torch.autograd.Function):
         t = ctx.tensor
         early = ctx.early
         ctx.early = None
-        grad_out = grad_out.detach()
+        # with create_graph the derivative of the early gradient, which is linear in
+        # dL_out, is recorded by torch's product
+        record = torch.is_grad_enabled() and grad_out.requires_grad
         grads = [None]
         for d in range(len(factors)):
             if not ctx.needs_input_grad[d + 1]:
                 grads.append(None)
             elif early is not None and early[0] == d:
                 # -2 * MTTKRP_d(E) from the forward pass, times dL_out
-                grads.append(api.scale_(early[1], grad_out))
+                grads.append(early[1].mul_(grad_out) if record else api.scale_(early[1], grad_out))
             else:
-                grads.append(api.cp_grad_scaled(t, d, factors, -2.0, grad_out))
+                grads.append(api.cp_grad_scaled(t, d, factors, -2.0, grad_out.detach()))
         return tuple(grads)
 
 

@@ -236,8 +236,8 @@ amped_status amped_cp_grad_scaled(amped_tensor_t t, int mode, int rank, const fl
 /*
  * x[i] *= (float)*dev_scale for i < n: the factor dL_out of a gradient that
  * amped_cp_loss_grad gave before it was known.  x is left alone when it is 1.
- *   x          DEVICE, n floats, 16-byte aligned
- *   dev_scale  DEVICE, one double
+ *   x          DEVICE, n floats, 16-byte aligned, on the current device
+ *   dev_scale  DEVICE, one double, on the same device
  */
 amped_status amped_scale(float *x, int64_t n, const double *dev_scale, void *stream);
 

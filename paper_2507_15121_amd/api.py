@@ -287,6 +287,11 @@ def scale_(x, dev_scale, stream=None):
     if x.dtype != torch.float32 or not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous float32 CUDA/HIP tensor")
     _one_double(dev_scale)
+    if dev_scale.device != x.device:
+        raise ValueError("the scale must be on x's device")
+    if x.device.index != torch.cuda.current_device():   # the call runs on the current device
+        with torch.cuda.device(x.device):
+            return scale_(x, dev_scale, stream)
     _check(lib().amped_scale(ctypes.c_void_p(x.data_ptr()), x.numel(), ctypes.c_void_p(dev_scale.data_ptr()),
                              _stream_ptr(stream)))
     return x

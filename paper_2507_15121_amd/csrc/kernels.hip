@@ -388,7 +388,8 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
     const bool grad = a.kind != Kind::Mttkrp;   // the residual forms read the output mode's factor
     if (grad && !fits_buffer(m.rows, a.rank, 4)) buf = false;
     auto [tile, v] = split_columns(a.rank, a.ftype, a.nin);
-    if (!grad && buf && v.lpr && m.small.n_units > 0)
+    // (the load-balance build records the queue's kernel at every size)
+    if (!AMPED_QUEUE_STATS && !grad && buf && v.lpr && m.small.n_units > 0)
         if (SmallFn small = pick_small(a.nin, a.ftype, v)) return launch_small(a, small, tile, eb);
     // An exact rank's instance with the hot-row cache is used where the cache
     // is; the residual forms (no cache) always take the exact one.

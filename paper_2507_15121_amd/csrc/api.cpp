@@ -466,7 +466,7 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
         amped::RowTotals totals[kMaxOrder];
         unsigned long long bad[kMaxOrder];
         int32_t small[kMaxOrder][2];   // split rows, most units of one
-        int32_t heavy[kMaxOrder];      // heavy rows
+        int32_t slots[kMaxOrder][2];   // light and heavy rows with slots
         unsigned unsorted, pad;
     } status;
     const size_t n = (size_t)nnz;
@@ -483,15 +483,16 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
     const size_t units = small ? (n + small_len - 1) / small_len : 0;
     const size_t small_bytes = small ? (size_t)order * (2 * Arena::step((units + 1) * 4) + Arena::step(units * 8) +
                                                         Arena::step(units * 4)) : 0;
-    // the heavy rows of units shorter than a chunk
+    // the rows that cross edges of units shorter than a chunk
     const int n_units = (int)((nnz + t->unit - 1) / t->unit);
-    const bool heavy = t->own_units && nnz > 0 && t->unit < amped::kDefaultChunk && n_units > amped::kHeavyCuts;
-    const size_t heavy_cuts = (size_t)(n_units + amped::kHeavyCuts), heavy_max = (size_t)amped::heavy_rows_max(n_units);
-    const size_t slot_floats = (size_t)amped::heavy_slots_max(n_units) * amped::kSlotCols;
-    const size_t heavy_bytes = heavy ? (size_t)order * (Arena::step(heavy_cuts * 8) + Arena::step(heavy_max * 16) +
-                                                        Arena::step(slot_floats * 4)) : 0;
+    const bool slots = t->own_units && nnz > 0 && t->unit < amped::kDefaultChunk;
+    const size_t cuts = (size_t)(n_units + amped::kHeavyCuts), light_max = (size_t)amped::light_rows_max(n_units),
+                 heavy_max = (size_t)amped::heavy_rows_max(n_units);
+    const size_t slot_floats = (size_t)amped::slots_max(n_units) * amped::kSlotCols;
+    const size_t slot_bytes = slots ? (size_t)order * (Arena::step(cuts * 8) + Arena::step(light_max * 16) +
+                                                       Arena::step(heavy_max * 16) + Arena::step(slot_floats * 4)) : 0;
     Arena ka, ta;
-    HIP_OR_FAIL(t->alloc(&keep, keep_bytes + small_bytes + heavy_bytes), "hipMalloc(layouts)");
+    HIP_OR_FAIL(t->alloc(&keep, keep_bytes + small_bytes + slot_bytes), "hipMalloc(layouts)");
     ka.base = static_cast<char*>(keep);
     {
         unsigned* queues = ka.take<unsigned>(words);
@@ -628,16 +629,19 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
                 if ((er = amped::launch_count_rows(cols[d][d], nnz, dims[d], t->unit, counts[d], &d_status->totals[d],
                                                    stream)) != hipSuccess)
                     return er;
-                if (heavy) {
-                    auto& hv = t->mode[d].heavy;
-                    int2* cut = ka.take<int2>(heavy_cuts);
-                    int4* rows = ka.take<int4>(heavy_max);
-                    if ((er = amped::launch_heavy_rows(cols[d][d], nnz, t->unit, n_units, rows, cut,
-                                                       &d_status->heavy[d], stream)) != hipSuccess)
+                if (slots) {
+                    auto& sl = t->mode[d].slots;
+                    int2* cut = ka.take<int2>(cuts);
+                    int4* light = ka.take<int4>(light_max);
+                    int4* heavy = ka.take<int4>(heavy_max);
+                    if ((er = amped::launch_slot_rows(cols[d][d], nnz, t->unit, n_units, light, heavy, cut,
+                                                      d_status->slots[d], stream)) != hipSuccess)
                         return er;
-                    hv.cut = cut;
-                    hv.rows = rows;
-                    hv.slot = ka.take<float>(slot_floats);
+                    sl.cut = cut;
+                    sl.light = light;
+                    sl.heavy = heavy;
+                    sl.slot = ka.take<float>(slot_floats);
+                    sl.all = amped::least_cuts(n_units) == 1;
                 }
                 if (small) {
                     auto& sm = t->mode[d].small;
@@ -747,7 +751,17 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
             m.n_zero = tot.shared + tot.lone;
             m.n_gaps = tot.gaps;
             t->touched[d] = tot.touched;
-            if (heavy) m.heavy.n = status.heavy[d];
+            if (slots) {
+                m.slots.n_light = status.slots[d][0];
+                m.slots.n_heavy = status.slots[d][1];
+                m.slots.zrows = zero + tot.shared;
+                m.slots.n_zero = tot.lone;
+                // without heavy rows: atomics and the init kernel
+                if (m.slots.n_heavy == 0) {
+                    m.slots.slot = nullptr;
+                    m.slots.all = false;
+                }
+            }
             if (one_launch(d)) {
                 m.small.n_units = (int)units;
                 m.small.zrows = zero + tot.shared;

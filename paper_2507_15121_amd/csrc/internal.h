@@ -64,13 +64,22 @@ inline int64_t stream_work_unit(int64_t shard)
 // Heavy rows: those with kHeavyCuts or more edges of units shorter than kDefaultChunk
 // inside.  One fp32 atomic per unit would make their error grow with the number of
 // units (factors in (0, 1), a row of 199k nonzeros, rank 32: units of 512, 1024, 2048,
-// 4096 2.9e-7, 2.5e-7, 1.4e-7, 1.1e-7 of the row), so their pieces go to slots
-// instead and close_rows adds them in fp64 (3.6e-8 at any unit).  Streamed layouts
-// have no slots: there such a mode's launches take heavy_units units at a time, whole
-// chunks or a little more.
-constexpr int kHeavyCuts = 8;         // residual_units() is at most this
+// 4096 2.9e-7, 2.5e-7, 1.4e-7, 1.1e-7 of the row), so in a mode that has such rows the
+// pieces of rows with least_cuts or more edges inside go to slots, which close_kernel adds
+// in fp64 (3.6e-8 at any unit).
+//  With a wave for every unit that is every row that crosses an edge: the launch after the
+// kernel then zeroes the untouched rows, too, and the one before it, which zeroes what
+// atomics add to, is left out.  With more units than that the launch before is needed for
+// the queue, and rows with few edges stay atomics.  All modes of 300k, 1M and 3M nonzeros
+// with Zipf rows at rank 32: atomics only 37, 64 and 139 us; so 43, 72 and 150; with both
+// launches 48, 74 and 152 (a closing launch takes 4 to 6 us, 1.5 more than one that has
+// nothing to add).  10M, ALS sweep: 699 and 720 us; 20M rank 64 bfloat16: 945 and 981.
+//  Streamed layouts have no slots: there a mode with a heavy row takes heavy_units units at
+// a time, whole chunks or a little more.
+constexpr int kHeavyCuts = 8;          // residual_units() is at most this
 constexpr int kSlotCols = 256;         // columns of a launch at most
 inline int64_t heavy_units(int64_t unit) { return (kDefaultChunk + unit - 1) / unit; }
+constexpr int least_cuts(int64_t n_units) { return n_units <= kGridWaves ? 1 : kHeavyCuts; }
 // Least nonzeros of a launch that keeps the most-used factor rows in LDS.  Every
 // block copies them first, about 10 us, and the instances with the copy hold 70
 // more registers; all modes at rank 32 without and with it: 5M nonzeros 235 and
@@ -195,23 +204,24 @@ hipError_t launch_fill_rows(const int32_t* keys, int64_t n, int64_t rows, int64_
 // most units of one.
 hipError_t launch_small_units(const int32_t* keys, int64_t n, int unit, int units, int32_t* cut, int32_t* left,
                               int32_t* split, unsigned* arrived, int32_t* info, hipStream_t st);
-// The heavy rows of a mode with n_units units, from sorted keys: rows[h] = (row, its
-// first and last unit, the slot of its first unit's piece; unit k's piece has that plus k
-// minus the first), and for k < n_units + kHeavyCuts cut[k] = (that slot, the same less
-// the first unit) where unit k starts inside heavy row h, else kNoSlot twice.  *n_rows =
-// heavy rows, at most heavy_rows_max(n_units); their slots are at most
-// heavy_slots_max(n_units).
+// The rows of a mode with n_units units that have slots, from sorted keys, those with fewer
+// than kHeavyCuts unit edges inside (light, none when least_cuts is kHeavyCuts) and the
+// others: (row, its first and last unit, the slot of its first unit's piece); unit k's
+// piece has that slot plus k minus the first.  For k < n_units + kHeavyCuts cut[k] = (that
+// slot, the same less the first unit) where unit k starts inside such a row, else kNoSlot
+// twice.  counts = light rows, heavy rows.
 constexpr int kNoSlot = -0x7FFFFFFF;
+constexpr int64_t light_rows_max(int64_t n_units) { return least_cuts(n_units) == 1 ? n_units : 0; }
 constexpr int64_t heavy_rows_max(int64_t n_units) { return n_units / kHeavyCuts + 1; }
-constexpr int64_t heavy_slots_max(int64_t n_units) { return n_units + heavy_rows_max(n_units); }
-hipError_t launch_heavy_rows(const int32_t* keys, int64_t n, int64_t unit, int n_units, int4* rows, int2* cut,
-                             int32_t* n_rows, hipStream_t st);
+constexpr int64_t slots_max(int64_t n_units) { return n_units + light_rows_max(n_units) + heavy_rows_max(n_units); }
+hipError_t launch_slot_rows(const int32_t* keys, int64_t n, int64_t unit, int n_units, int4* light, int4* heavy, int2* cut,
+                            int32_t* counts, hipStream_t st);
 // The most device bytes that units sized by the library take beside the layouts: the
-// tables and slots of heavy rows, the tables and shares of the one-launch MTTKRP.
+// tables and slots of rows that cross units, the tables and shares of the one-launch MTTKRP.
 inline int64_t short_unit_bytes(int order, int64_t nnz, int64_t unit)
 {
     const int64_t n = (nnz + unit - 1) / unit;
-    int64_t mode = 8 * (n + kHeavyCuts) + 16 * heavy_rows_max(n) + heavy_slots_max(n) * kSlotCols * 4 + 3 * 256;
+    int64_t mode = 8 * (n + kHeavyCuts) + 16 * (light_rows_max(n) + heavy_rows_max(n)) + slots_max(n) * kSlotCols * 4 + 4 * 256;
     if (nnz > 0 && nnz <= kSmallNnz) {
         const int64_t u = (nnz + small_unit(nnz) - 1) / small_unit(nnz), split = std::min(u, nnz / (kSmallRow + 1));
         mode += 8 * (u + 1) + 12 * u + (u + split) * kSmallCols * 8 + 5 * 256;
@@ -279,13 +289,17 @@ struct ModeDev {
     const int32_t* hot = nullptr;                  // hot-row tables of this mode [kHotTableLen]
     const void* zero_row = nullptr;                // 16 zero bytes
     float* sink = nullptr;                         // kSinkFloats floats of write-only scratch
-    // Heavy rows (n = 0: none)
-    struct Heavy {
-        int n = 0;
-        const int4* rows = nullptr;
+    // Rows whose pieces have slots (slot NULL: none do)
+    struct Slots {
+        int n_light = 0, n_heavy = 0;
+        const int4* light = nullptr;
+        const int4* heavy = nullptr;
         const int2* cut = nullptr;
         float* slot = nullptr;             // slots of at most kSlotCols floats
-    } heavy;
+        bool all = false;                  // every row that crosses a unit edge has them
+        const int32_t* zrows = nullptr;    // all: the untouched rows of the zero-row list
+        int64_t n_zero = 0;
+    } slots;
     int64_t unit = 0;                              // nonzeros per unit (chunk: per unit of a launch)
     // MTTKRP in one launch (n_units = 0: not for this mode)
     struct Small {

@@ -272,7 +272,7 @@ __global__ void __launch_bounds__(64) small_kernel(const SmallParams p)
             }
         }
     }
-    zero_rows(p.out, ld, p.col0, p.ncols, p.vec4, p.zrows, p.n_zero, p.gaps, p.n_gaps);
+    zero_rows(p.out, ld, p.col0, p.ncols, p.vec4, p.zrows, p.n_zero, p.gaps, p.n_gaps, blockIdx.x, gridDim.x);
 }
 
 template <int NIN, typename T>

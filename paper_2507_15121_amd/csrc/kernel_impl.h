@@ -24,9 +24,10 @@
 //    plain store.  Pieces of rows that cross group boundaries are parked in
 //    LDS and summed at the end of the unit; only rows that cross a unit's
 //    boundary are added to memory with fp32 atomics (Sec. 3.2 uses atomics
-//    between SMs), after the init kernel has zeroed them; the pieces of rows
-//    that span many short units go to slots, which close_rows adds in fp64.
-//  * Untouched output rows are zeroed once, by the init kernel.
+//    between SMs), after the init kernel has zeroed them.  Where units are
+//    shorter than 4096 the pieces of rows that span many of them, or of all that
+//    cross an edge, go to slots instead, which close_kernel adds in fp64.
+//  * Untouched output rows are zeroed once, by the init kernel or close_kernel.
 //  * From 32M nonzeros on, MTTKRP keeps the most-used rows of each input factor
 //    in LDS (hot-row cache); their gathers issue no memory request.
 #include <hip/hip_runtime.h>
@@ -128,8 +129,8 @@ struct KParams {
     uint32_t own_bytes;
     const void* zero_row;     // 16 zero bytes: what padding entries read on the 64-bit path
     float* sink;              // 64 * 8 floats that absorb stores which must not land
-    const int2* hcut;         // heavy rows' cuts (NULL: none; launch_heavy_rows)
-    float* hslot;             // their slots of slot_stride(ncols) floats each
+    const int2* cut;          // where units start inside rows with slots (NULL: none; launch_slot_rows)
+    float* slot;              // the slots, of slot_stride(ncols) floats each
     int per_chunk;            // units per chunk
     int prev_key;             // output index just before position 0 of these arrays (-1: none)
     int next_key;             // output index just after position nnz - 1 (-1: none)
@@ -149,7 +150,7 @@ __host__ __device__ constexpr size_t hot_lds_bytes(int nin, int k, int row_bytes
     return k > 0 ? hot_row_offset(nin, k) + (size_t)nin * k * row_bytes : 16;
 }
 
-// A heavy row's slot: whole 16 bytes.
+// A row piece's slot: whole 16 bytes.
 __host__ __device__ constexpr int slot_stride(int ncols) { return (ncols + 3) & ~3; }
 
 // Raw buffer resource over [base, base + bytes): word 3 is the gfx9-family
@@ -657,12 +658,12 @@ mttkrp_kernel(const KParams p)
             k_last = p.out_idx[max(min(ge, p.nnz) - 1, (int64_t)0)];
             k_next = p.out_idx[min(ge, top)];
         }
-        // the heavy rows that the unit starts and ends in
+        // the slots of the rows that the unit starts and ends in
         int h_left = kNoSlot, h_right = kNoSlot;
         if constexpr (OUT) {
-            if (p.hcut) {
-                h_left = p.hcut[(int64_t)chunk * p.per_chunk].y;
-                h_right = p.hcut[((int64_t)chunk + 1) * p.per_chunk].x;
+            if (p.cut) {
+                h_left = p.cut[(int64_t)chunk * p.per_chunk].y;
+                h_right = p.cut[((int64_t)chunk + 1) * p.per_chunk].x;
             }
         }
         auto open_run = [&]() {
@@ -1000,12 +1001,12 @@ mttkrp_kernel(const KParams p)
                 float* o = p.out + (int64_t)cur * ld + p.col0 + lane;
                 bool add = cur_ext != 0;
                 if (add) {
-                    // a heavy row's piece is stored to its slot: the row's first one
-                    // if it starts here, else that of the unit's first position
+                    // a piece with a slot is stored there: the row's first one if it
+                    // starts here, else that of the unit's first position
                     const int h = cur_ext & 1 ? h_left : h_right;
                     if (h != kNoSlot) {
                         const int slot = cur_ext & 1 ? h + chunk * p.per_chunk : h;
-                        o = p.hslot + (int64_t)slot * slot_stride(p.ncols) + lane;
+                        o = p.slot + (int64_t)slot * slot_stride(p.ncols) + lane;
                         add = false;
                     }
                 }
@@ -1067,22 +1068,23 @@ mttkrp_kernel(const KParams p)
 
 using KernelFn = void (*)(const KParams);
 
-// Zeroes listed rows and (start, length) ranges of rows, all blocks of the grid
-// together (a range, at most about kGapPiece rows, is one block's work).  vec4:
+// Zeroes listed rows and (start, length) ranges of rows, nblocks blocks together (a
+// range, at most about kGapPiece rows, is one block's work), of which this is `block`.  vec4:
 // ld, col0 and ncols are multiples of 4 (16-byte stores).
 __device__ __forceinline__ void zero_rows(float* out, int64_t ld, int col0, int ncols, bool vec4, const int32_t* zrows,
-                                          int64_t n_zero, const int32_t* gaps, int64_t n_gaps)
+                                          int64_t n_zero, const int32_t* gaps, int64_t n_gaps, int64_t block,
+                                          int64_t nblocks)
 {
-    const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
+    const int64_t nthreads = nblocks * blockDim.x;
     const int nv = vec4 ? ncols / 4 : ncols;  // stores per row
     const int64_t total = n_zero * nv;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += nthreads) {
+    for (int64_t i = block * blockDim.x + threadIdx.x; i < total; i += nthreads) {
         const int64_t r = zrows[i / nv];
         const int j = (int)(i % nv);
         if (vec4) *reinterpret_cast<float4*>(out + r * ld + col0 + 4 * j) = make_float4(0.f, 0.f, 0.f, 0.f);
         else out[r * ld + col0 + j] = 0.f;
     }
-    for (int64_t gi = blockIdx.x; gi < n_gaps; gi += gridDim.x) {
+    for (int64_t gi = block; gi < n_gaps; gi += nblocks) {
         const int64_t start = gaps[2 * gi], len = gaps[2 * gi + 1];
         const int64_t n = len * nv;
         for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {

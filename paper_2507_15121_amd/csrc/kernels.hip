@@ -55,7 +55,7 @@ __global__ void __launch_bounds__(kBlock) init_kernel(float* out, int64_t ld, in
         if (queue && threadIdx.x < kQueueSlots) queue[threadIdx.x * kQueueStride] = 0u;
         if (loss && threadIdx.x == 0) *loss = 0.0;
     }
-    if (out) zero_rows(out, ld, col0, ncols, vec4, zrows, n_zero, gaps, n_gaps);
+    if (out) zero_rows(out, ld, col0, ncols, vec4, zrows, n_zero, gaps, n_gaps, blockIdx.x, gridDim.x);
 }
 
 // A factor of `rows` rows is read through a 32-bit buffer offset when one
@@ -171,11 +171,16 @@ Shape launch_shape(KernelFn fn, int block, int nin, int row_bytes, bool cache)
 // the CUs).
 int launch_grid(const Shape& sh, const KParams& k) { return (int)std::min<int64_t>(sh.grid, k.n_chunks); }
 
+// Whether a launch's part of every output row is whole 16-byte pieces.
+bool whole_vectors(const float* out, int64_t ld, int col0, int ncols)
+{
+    return ld % 4 == 0 && col0 % 4 == 0 && ncols % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
+}
+
 hipError_t launch_init(const ModeDev& m, float* out, int64_t ld, int col0, int ncols, double* loss,
                        hipStream_t st)
 {
-    const bool vec4 = (ld % 4 == 0) && (col0 % 4 == 0) && (ncols % 4 == 0) &&
-                      (reinterpret_cast<uintptr_t>(out) % 16 == 0);
+    const bool vec4 = whole_vectors(out, ld, col0, ncols);
     const int64_t work = std::max<int64_t>(m.n_zero * (vec4 ? ncols / 4 : ncols), m.n_gaps * kBlock);
     int grid = (int)std::min<int64_t>(std::max<int64_t>(1, (work + kBlock - 1) / kBlock), 4096);
     hipLaunchKernelGGL(init_kernel, dim3(grid), dim3(kBlock), 0, st, out, ld, col0, ncols, vec4, m.zero_rows,
@@ -213,9 +218,9 @@ KParams base_params(const ModeDev& m, int64_t chunk)
     k.prev_key = m.prev_key;
     k.next_key = m.next_key;
     k.per_chunk = 1;
-    if (m.heavy.n > 0) {
-        k.hcut = m.heavy.cut;
-        k.hslot = m.heavy.slot;
+    if (m.slots.slot) {
+        k.cut = m.slots.cut;
+        k.slot = m.slots.slot;
         k.per_chunk = (int)(chunk / m.unit);
     }
     return k;
@@ -240,64 +245,133 @@ __global__ void __launch_bounds__(kBlock) scale_kernel(float* x, int64_t n, cons
     for (int64_t i = 4 * n4 + i0; i < n; i += stride) x[i] *= f;
 }
 
-// A heavy row of the output from its pieces, each a chunk's (per_chunk units) sum, in
-// fp64 and in one order whatever the waves' was.  A block per row and 32 columns: cw
-// lanes of 4 columns per piece, the wave's pieces side by side, 8 in flight per lane,
-// then the wave's sums by shuffles and the block's through LDS.  What bounds it is
-// latency: the row, then one round of loads per 8192 / cw pieces of slots that other
-// XCDs have just written.
-// 4.8 us for 23 rows of up to 185 pieces at rank 32 (a mode of 5M nonzeros, whose kernel
-// takes 76), 11.4 for 195 rows of up to 1500 at rank 64 (20M, 315).
-constexpr int kCloseBlock = 1024, kCloseCols = 32;
-__global__ void __launch_bounds__(kCloseBlock) close_rows(const int4* rows, const float* slot, int stride, float* out,
-                                                          int64_t ld, int col0, int ncols, int cw, int per_chunk)
+// The output rows whose pieces have slots, each piece a chunk's (per_chunk units) sum, in
+// fp64 and in one order whatever the waves' was; and the untouched rows, where the init
+// kernel is left out.  Blocks: one per heavy row and 32 columns, then one per 16 light rows
+// (a wave each), then those that zero.  cw lanes of 4 columns hold a piece, a wave's or
+// block's pieces lie side by side, a heavy row's 8 deep; sums by shuffles, then through
+// LDS.  What bounds it is latency: the row, then one round of loads (a heavy row's 8 BLOCK
+// / cw pieces) of slots that other XCDs have just written.  4.8 us for 23 rows of up to 185
+// pieces at rank 32 (a mode of 5M nonzeros, whose kernel takes 76), 11.4 for 195 rows of up
+// to 1500 at rank 64 (20M, 315); blocks of 1024 threads where a row may have thousands.
+constexpr int kCloseCols = 32;
+struct CloseParams {
+    const int4* heavy;
+    const int4* light;
+    int n_heavy, n_light, heavy_blocks, light_blocks;
+    const float* slot;
+    float* out;
+    int64_t ld;
+    int stride, col0, ncols, cw, per_chunk;
+    bool vec4;
+    const int32_t* zrows;
+    const int32_t* gaps;
+    int64_t n_zero, n_gaps;
+};
+template <int BLOCK>
+__global__ void __launch_bounds__(BLOCK) close_kernel(const CloseParams p)
 {
-    constexpr int kWaves = kCloseBlock / 64;
+    constexpr int kWaves = BLOCK / 64;
     __shared__ double s[kWaves][kCloseCols];
-    const int4 r = rows[blockIdx.x];
-    // piece 0 is the first unit's, the others those of the chunks that start after it
-    const int chunk0 = r.y / per_chunk, pieces = r.z / per_chunk - chunk0 + 1;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, step = kCloseBlock / cw;
-    const int c4 = tid & (cw - 1), col = blockIdx.y * kCloseCols + 4 * c4;
-    const float* src = slot + (int64_t)r.w * stride + col;
-    auto at = [&](int k) { return (int64_t)(k == 0 ? 0 : (chunk0 + k) * per_chunk - r.y) * stride; };
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int k0 = tid / cw; k0 < pieces; k0 += 8 * step) {
-        float4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            v[u] = col < stride && k0 + u * step < pieces
-                       ? *reinterpret_cast<const float4*>(src + at(k0 + u * step))
-                       : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            acc[0] += (double)v[u].x;
-            acc[1] += (double)v[u].y;
-            acc[2] += (double)v[u].z;
-            acc[3] += (double)v[u].w;
-        }
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, block = blockIdx.x;
+    if (block >= p.heavy_blocks + p.light_blocks) {
+        const int first = p.heavy_blocks + p.light_blocks;
+        zero_rows(p.out, p.ld, p.col0, p.ncols, p.vec4, p.zrows, p.n_zero, p.gaps, p.n_gaps, block - first,
+                  gridDim.x - first);
+        return;
     }
-    for (int m = cw; m < 64; m <<= 1)
+    const bool is_heavy = block < p.heavy_blocks;
+    const int index = is_heavy ? block % p.n_heavy : (block - p.heavy_blocks) * kWaves + wave;
+    if (!is_heavy && index >= p.n_light) return;
+    const int4 r = is_heavy ? p.heavy[index] : p.light[index];
+    // piece 0 is the first unit's, the others those of the chunks that start after it
+    const int chunk0 = r.y / p.per_chunk, pieces = r.z / p.per_chunk - chunk0 + 1;
+    const int c4 = lane & (p.cw - 1);
+    const float* src = p.slot + (int64_t)r.w * p.stride + 4 * c4;
+    auto at = [&](int k) { return (int64_t)(k == 0 ? 0 : (chunk0 + k) * p.per_chunk - r.y) * p.stride; };
+    float* const row = p.out + (int64_t)r.x * p.ld + p.col0;
+    double acc[4];
+    // pieces first, first + step, ... of the columns from col on, D of them in flight
+    auto sum = [&](int col, int first, int step, auto depth) {
+        constexpr int D = decltype(depth)::value;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] += __shfl_xor(acc[i], m, 64);
-    if (lane < cw)
+        for (int i = 0; i < 4; ++i) acc[i] = 0.0;
+        for (int k0 = first; k0 < pieces; k0 += D * step) {
+            float4 v[D];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s[wave][4 * lane + i] = acc[i];
-    __syncthreads();
-    if (tid < 4 * cw && (int)blockIdx.y * kCloseCols + tid < ncols) {
-        double sum = 0.0;
+            for (int u = 0; u < D; ++u)
+                v[u] = col + 4 * c4 < p.stride && k0 + u * step < pieces
+                           ? *reinterpret_cast<const float4*>(src + col + at(k0 + u * step))
+                           : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) sum += s[w][tid];
-        out[(int64_t)r.x * ld + col0 + blockIdx.y * kCloseCols + tid] = (float)sum;
+            for (int u = 0; u < D; ++u) {
+                acc[0] += (double)v[u].x;
+                acc[1] += (double)v[u].y;
+                acc[2] += (double)v[u].z;
+                acc[3] += (double)v[u].w;
+            }
+        }
+        for (int m = p.cw; m < 64; m <<= 1)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += __shfl_xor(acc[i], m, 64);
+    };
+    if (is_heavy) {
+        const int col = block / p.n_heavy * kCloseCols;
+        sum(col, tid / p.cw, BLOCK / p.cw, std::integral_constant<int, 8>{});
+        if (lane < p.cw)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[wave][4 * lane + i] = acc[i];
+        __syncthreads();
+        if (tid < 4 * p.cw && col + tid < p.ncols) {
+            double x = 0.0;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) x += s[w][tid];
+            row[col + tid] = (float)x;
+        }
+        return;
+    }
+    for (int col = 0; col < p.ncols; col += kCloseCols) {
+        sum(col, lane / p.cw, 64 / p.cw, std::integral_constant<int, 1>{});
+        if (lane < p.cw)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (col + 4 * lane + i < p.ncols) row[col + 4 * lane + i] = (float)acc[i];
     }
 }
 
 hipError_t launch_close(const ModeDev& m, const KParams& k, hipStream_t st)
 {
-    int cw = 1;
-    while (4 * cw < std::min(k.ncols, kCloseCols)) cw *= 2;
-    const unsigned parts = (unsigned)((k.ncols + kCloseCols - 1) / kCloseCols);
-    hipLaunchKernelGGL(close_rows, dim3((unsigned)m.heavy.n, parts), dim3(kCloseBlock), 0, st, m.heavy.rows, m.heavy.slot, slot_stride(k.ncols), k.out, k.ld, k.col0, k.ncols, cw, k.per_chunk);
+    CloseParams c{};
+    c.heavy = m.slots.heavy;
+    c.light = m.slots.light;
+    c.n_heavy = m.slots.n_heavy;
+    c.n_light = m.slots.n_light;
+    c.heavy_blocks = c.n_heavy * ((k.ncols + kCloseCols - 1) / kCloseCols);
+    const int block = m.slots.all ? 256 : 1024;
+    c.light_blocks = (c.n_light + block / 64 - 1) / (block / 64);
+    c.slot = m.slots.slot;
+    c.out = k.out;
+    c.ld = k.ld;
+    c.stride = slot_stride(k.ncols);
+    c.col0 = k.col0;
+    c.ncols = k.ncols;
+    c.cw = 1;
+    while (4 * c.cw < std::min(k.ncols, kCloseCols)) c.cw *= 2;
+    c.per_chunk = k.per_chunk;
+    int64_t zero_blocks = 0;
+    if (m.slots.all) {
+        c.vec4 = whole_vectors(k.out, k.ld, k.col0, k.ncols);
+        c.zrows = m.slots.zrows;
+        c.gaps = m.gaps;
+        c.n_zero = m.slots.n_zero;
+        c.n_gaps = m.n_gaps;
+        const int64_t stores = (c.n_zero * (c.vec4 ? k.ncols / 4 : k.ncols) + block - 1) / block;
+        zero_blocks = std::min<int64_t>(std::max(stores, c.n_gaps), 4096);
+    }
+    const int64_t grid = c.heavy_blocks + c.light_blocks + zero_blocks;
+    if (grid == 0) return hipSuccess;
+    if (block == 256) hipLaunchKernelGGL(close_kernel<256>, dim3((unsigned)grid), dim3(256), 0, st, c);
+    else hipLaunchKernelGGL(close_kernel<1024>, dim3((unsigned)grid), dim3(1024), 0, st, c);
     return hipGetLastError();
 }
 
@@ -422,11 +496,16 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
     const Shape sh = launch_shape(fn, block, a.nin, v.lpr * v.rpl * eb, cache && !scalar && m.nnz >= kHotMinNnz);
     if (sh.grid <= 0) return hipErrorInvalidDevice;
     set_hot(k, sh.hot_k, a.in_hot, a.nin);
+    // more units than waves: the queue's counters are used, so they are reset first
+    const bool queued = k.n_chunks > (int64_t)launch_grid(sh, k) * (block / 64);
     for (int col0 = 0; col0 < a.rank; col0 += tile) {
         const int ncols = std::min(tile, a.rank - col0);
         // the loss (one launch: the residual forms never tile columns) is reset
         // by the init kernel unless this launch adds to it
-        hipError_t e = launch_init(m, a.out, a.rank, col0, ncols, a.loss_accumulate ? nullptr : k.loss, a.stream);
+        double* const loss = a.loss_accumulate ? nullptr : k.loss;
+        hipError_t e = hipSuccess;
+        if (!m.slots.all) e = launch_init(m, a.out, a.rank, col0, ncols, loss, a.stream);
+        else if (loss || queued) e = launch_init(m, nullptr, 0, 0, 0, loss, a.stream);
         if (e != hipSuccess) return e;
         if (m.n_chunks == 0) continue;
         k.col0 = col0;
@@ -438,7 +517,7 @@ hipError_t launch_mttkrp(const LaunchArgs& a)
         e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(launch_grid(sh, k)), dim3(block), args, sh.dyn,
                             a.stream);
         if (e != hipSuccess) return e;
-        if (k.hcut && (e = launch_close(m, k, a.stream)) != hipSuccess) return e;
+        if (k.cut && (e = launch_close(m, k, a.stream)) != hipSuccess) return e;
     }
     return hipSuccess;
 }

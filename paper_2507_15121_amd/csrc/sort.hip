@@ -705,28 +705,33 @@ __global__ void __launch_bounds__(1024) small_units(const int32_t* keys, int n, 
     }
 }
 
-// ------------------------------------------------------------------ heavy rows
-// One block.  The cuts inside a row are consecutive; its last one is found by
-// bisection.  (Indices out of range may leave the keys unsorted; the call then fails,
-// after this kernel, which stays inside its arrays whatever the keys are.)
-__global__ void __launch_bounds__(1024) heavy_rows(const int32_t* keys, int64_t n, int64_t unit, int units, int4* rows,
-                                                   int2* cut, int32_t* n_rows)
+// ------------------------------------------------------------- rows with slots
+// One block.  The cuts inside a row are consecutive; its last one is found by doubling
+// steps and bisection.  (Indices out of range may leave the keys unsorted; the call then
+// fails, after this kernel, which stays inside its arrays whatever the keys are.)
+__global__ void __launch_bounds__(1024) slot_rows(const int32_t* keys, int64_t n, int64_t unit, int units, int4* light,
+                                                  int4* heavy, int2* cut, int32_t* counts)
 {
-    __shared__ int s_rows[1024], s_slots[1024];
-    const int tid = threadIdx.x, most = (int)heavy_rows_max(units);
+    __shared__ int s_sum[3][1024];   // light rows, heavy rows, slots
+    const int tid = threadIdx.x, least = least_cuts(units), most_heavy = (int)heavy_rows_max(units);
     for (int k = tid; k < units + kHeavyCuts; k += 1024) cut[k] = make_int2(kNoSlot, kNoSlot);
     const int per = (units + 1023) / 1024;
     const int k0 = min(units, tid * per), k1 = min(units, k0 + per);
-    // whether cut k is the first one inside a heavy row
+    // whether cut k is the first one inside a row with slots
     auto first = [&](int k) {
-        if (k < 1 || k + kHeavyCuts - 1 >= units) return false;
+        if (k < 1 || k + least - 1 >= units) return false;
         const int64_t p = (int64_t)k * unit;
         const int32_t row = keys[p];
-        return keys[p - 1] == row && (k == 1 || keys[p - unit - 1] != row) && keys[p + (kHeavyCuts - 1) * unit] == row;
+        return keys[p - 1] == row && (k == 1 || keys[p - unit - 1] != row) && keys[p + (least - 1) * unit] == row;
     };
     auto last = [&](int k) {
         const int32_t row = keys[(int64_t)k * unit];
-        int lo = k + kHeavyCuts - 1, hi = units;
+        int lo = k + least - 1, step = 1;
+        while (lo + step < units && keys[(int64_t)(lo + step) * unit] == row) {
+            lo += step;
+            step *= 2;
+        }
+        int hi = min(lo + step, units);
         while (hi - lo > 1) {
             const int mid = lo + (hi - lo) / 2;
             if (keys[(int64_t)mid * unit] == row) lo = mid;
@@ -734,37 +739,49 @@ __global__ void __launch_bounds__(1024) heavy_rows(const int32_t* keys, int64_t 
         }
         return lo;
     };
-    int nr = 0, ns = 0;
+    int c[3] = {0, 0, 0};
     for (int k = k0; k < k1; ++k)
         if (first(k)) {
-            ++nr;
-            ns += last(k) - k + 2;
+            const int cuts = last(k) - k + 1;
+            ++c[cuts < kHeavyCuts ? 0 : 1];
+            c[2] += cuts + 1;
         }
-    s_rows[tid] = nr;
-    s_slots[tid] = ns;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) s_sum[i][tid] = c[i];
     __syncthreads();
     for (int off = 1; off < 1024; off <<= 1) {
-        const int x = tid >= off ? s_rows[tid - off] : 0, y = tid >= off ? s_slots[tid - off] : 0;
+        int x[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) x[i] = tid >= off ? s_sum[i][tid - off] : 0;
         __syncthreads();
-        s_rows[tid] += x;
-        s_slots[tid] += y;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) s_sum[i][tid] += x[i];
         __syncthreads();
     }
-    int h = s_rows[tid] - nr, slot = s_slots[tid] - ns;
+    int nl = s_sum[0][tid] - c[0], nh = s_sum[1][tid] - c[1], slot = s_sum[2][tid] - c[2];
     for (int k = k0; k < k1; ++k)
         if (first(k)) {
             const int e = last(k);
-            if (h < most) rows[h] = make_int4(keys[(int64_t)k * unit], k - 1, e, slot);
-            ++h;
+            const int4 v = make_int4(keys[(int64_t)k * unit], k - 1, e, slot);
+            if (e - k + 1 < kHeavyCuts) {
+                light[nl++] = v;
+                for (int j = k; j <= e; ++j) cut[j] = make_int2(v.w, v.w - v.y);
+            } else {
+                if (nh < most_heavy) heavy[nh] = v;
+                ++nh;
+            }
             slot += e - k + 2;
         }
     __syncthreads();
-    const int total = min(s_rows[1023], most);
+    const int total = min(s_sum[1][1023], most_heavy);
     for (int r = tid >> 6; r < total; r += 16) {
-        const int4 v = rows[r];
+        const int4 v = heavy[r];
         for (int k = v.y + 1 + (tid & 63); k <= v.z; k += 64) cut[k] = make_int2(v.w, v.w - v.y);
     }
-    if (tid == 0) *n_rows = total;
+    if (tid == 0) {
+        counts[0] = s_sum[0][1023];
+        counts[1] = total;
+    }
 }
 
 int stream_grid(int64_t n, int per_thread)
@@ -875,11 +892,11 @@ hipError_t launch_small_units(const int32_t* keys, int64_t n, int unit, int unit
     return hipGetLastError();
 }
 
-hipError_t launch_heavy_rows(const int32_t* keys, int64_t n, int64_t unit, int n_units, int4* rows, int2* cut,
-                             int32_t* n_rows, hipStream_t st)
+hipError_t launch_slot_rows(const int32_t* keys, int64_t n, int64_t unit, int n_units, int4* light, int4* heavy, int2* cut,
+                            int32_t* counts, hipStream_t st)
 {
     if (n_units < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(heavy_rows, dim3(1), dim3(1024), 0, st, keys, n, unit, n_units, rows, cut, n_rows);
+    hipLaunchKernelGGL(slot_rows, dim3(1), dim3(1024), 0, st, keys, n, unit, n_units, light, heavy, cut, counts);
     return hipGetLastError();
 }
 

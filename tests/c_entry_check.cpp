@@ -166,7 +166,7 @@ hipError_t launch_fill_rows(const int32_t*, int64_t, int64_t, int64_t, const uin
 hipError_t launch_gather_records(int, const void*, const int32_t*, void* const*, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_gram(const float*, int64_t, int, float*, double*, hipStream_t, int64_t) { return hipSuccess; }
 hipError_t launch_gram_noalloc(const float*, int64_t, int, double*, hipStream_t) { return hipSuccess; }
-hipError_t launch_heavy_rows(const int32_t*, int64_t, int64_t, int, int4*, int2*, int32_t*, hipStream_t) { return hipSuccess; }
+hipError_t launch_slot_rows(const int32_t*, int64_t, int64_t, int, int4*, int4*, int2*, int32_t*, hipStream_t) { return hipSuccess; }
 hipError_t launch_hot_tables(const int32_t*, int64_t, unsigned long long*, int32_t*, hipStream_t) { return hipSuccess; }
 hipError_t launch_iota(int32_t*, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_mttkrp(const LaunchArgs&) { return hipSuccess; }

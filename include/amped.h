@@ -67,7 +67,11 @@ typedef struct {
                                  units by the nonzeros.                                */
     int64_t device_byte_cap;  /* 0 = no cap; otherwise creation fails with NOMEM,
                                  before touching the device, if the layouts would
-                                 need more device bytes than this.                     */
+                                 need more device bytes than this.  A handle created
+                                 under a cap takes no more, its build included; what
+                                 faster launches would keep beside the layouts is
+                                 left out where the cap does not hold it.  The CP-ALS
+                                 workspace is not part of the layouts.                 */
     int32_t keep_perm;        /* 1 = keep each mode's permutation (on the device, or
                                  in host memory with host_layout) so
                                  amped_tensor_layout can return it.                    */
@@ -76,7 +80,10 @@ typedef struct {
                                  the device in shards on every call: for tensors whose
                                  layouts do not fit in device memory (out-of-core
                                  shard streaming, Sec. 4.8).  The device then holds
-                                 two shard buffers and the per-mode row lists only.
+                                 two buffers of half a shard's packed nonzeros, one
+                                 shard unpacked, the per-mode row lists and 4 bytes
+                                 per 256 nonzeros and mode (none of these under a cap
+                                 that does not hold them).
                                  Results equal those of a device-resident tensor up
                                  to fp32 summation order.  0 = device-resident.      */
     int64_t shard_nnz;        /* host_layout: nonzeros per streamed shard, rounded up
@@ -186,9 +193,9 @@ amped_status amped_layout_host(int order, const int64_t *dims, int64_t nnz,
  * Errors (synchronous, nothing enqueued): INVALID for a bad mode/rank, a NULL
  * or misaligned pointer; HIP if a launch fails.
  *
- * The most-used rows of each input factor (from the layout's index counts)
- * are read from an on-chip copy made at launch; results are identical either
- * way.  The environment variable AMPED_HOT_MAX, read once per process, caps
+ * In launches of 2^25 nonzeros and more the most-used rows of each input factor
+ * (from the layout's index counts) are read from an on-chip copy made at launch;
+ * results are identical either way.  The environment variable AMPED_HOT_MAX, read once per process, caps
  * the rows kept per factor (0 turns the copy off).  Also applies to
  * amped_mttkrp_bf16.
  */
@@ -310,8 +317,10 @@ amped_status amped_gram_noalloc(const float *A, int64_t rows, int rank, double *
  *            matrices it kept are used instead of being recomputed (INVALID
  *            if there is no such sweep).  0 otherwise.
  * 1 <= rank <= 128.  The tensor keeps a workspace for the rank of its last
- * sweep (max_d dims[d] x rank floats plus small R x R arrays); sweeps on one
- * tensor must not overlap.  With host_layout, the one-time ||X||^2 pass is
+ * sweep (max_d dims[d] x rank floats, R x R arrays, and R x R partial sums: one for
+ * each 256 rows of a mode, at most 1024 of them per mode, 512 above rank 64, or one for
+ * each 8192 rows where that is more, at most 2048); sweeps on one tensor must not
+ * overlap.  With host_layout, the one-time ||X||^2 pass is
  * streamed as well, in shards cut between runs of equal coordinates; a run
  * longer than a shard returns UNSUPPORTED.
  */

@@ -1,6 +1,6 @@
 // C ABI of the sparse MTTKRP library (declared in include/amped.h): argument
-// checks, handle lifetime, the per-mode layout build (host order, device
-// gather) and the kernel launches.
+// checks, handle lifetime, the per-mode layout build (on the device, or packed in
+// host memory) and the kernel launches.
 #include <hip/hip_runtime_api.h>
 #include <omp.h>
 
@@ -964,13 +964,14 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
     }
     // peak device bytes: the N layouts, the kept permutations, and during the
     // build the raw COO plus one permutation; per mode at most one int per row
-    // for the zero-row list and long gaps, and the hot-row tables
+    // for the zero-row list and long gaps, and the hot-row tables.  (What the builds
+    // take now is less; what a cap admits is unchanged, and what goes beyond the layouts
+    // is left out where it does not fit: short_unit_bytes, build_host_layout.)
     const int64_t layout_bytes = (int64_t)order * (order + 1) * 4 * (nnz + 4);
     int64_t row_bytes = 0;
     for (int d = 0; d < order; ++d) row_bytes += 4 * dims[d] + 4 * amped::kHotTableLen;
     // device sort: lexicographic order, key and value ping-pong buffers, 256 counts
-    // per 4096 nonzeros and their sums.  (Most of the buffers now lie in arrays of
-    // modes not yet built; what a cap admits is unchanged.)
+    // per 4096 nonzeros and their sums
     const int64_t sort_counts = (nnz + 4095) / 4096 * 256;
     const int64_t sort_bytes = 16 * nnz + 4 * (sort_counts + (sort_counts + 4095) / 4096 + 64);
     // host-resident layouts: two shard buffers of whole chunks instead (what they are
@@ -1402,7 +1403,6 @@ amped_status amped_cp_loss(amped_tensor_t t, int rank, const float* const* facto
     for (int w = 1; w < t->order; ++w) {
         a.in_factors[w - 1] = factors[w];
         a.in_rows[w - 1] = t->dims[w];
-        a.in_hot[w - 1] = t->mode[w].hot;
     }
     a.loss = loss;
     a.stream = static_cast<hipStream_t>(stream);

@@ -96,7 +96,7 @@ constexpr int64_t kHotMinNnz = AMPED_HOT_MIN_NNZ;
 // takes 2 us or more: up to 2^17 nonzeros a mode takes the one launch unless a row
 // spans more than kSmallSpan units, up to 2^18 only if no row spans any.  Kernels
 // of a mode without and with the one launch: 2000 nonzeros at rank 16 9.3 and 6.0
-// us, 100k 9.1 and 6.6 us (uniform), 20k with heavy rows 9.3 and 9.2 us (and 2.5
+// us, 100k 9.1 and 6.6 us (uniform), 20k with heavy rows 9.3 and 8.1 us (and 2.5
 // us less in the call); 250k with every row split 10.2 and 9.0 us at rank 16, but
 // 19 and 22 us at 128; 500k 15.5 and 15.5 us at rank 32, 10.6 and 14.6 us split.
 #ifndef AMPED_SMALL_NNZ
@@ -233,7 +233,8 @@ hipError_t launch_hot_tables(const int32_t* keys, int64_t n, unsigned long long*
 // a[i] = i for i < n.
 hipError_t launch_iota(int32_t* a, int64_t n, hipStream_t st);
 
-// Gather idx[w][perm[p]] for p in [p0, p1) into dst.
+// Gather src[perm[p]] for p in [p0, p1) into dst (the host check's reference of a
+// layout column; the packed layouts gather as they pack).
 void gather_i32(const int32_t* src, const int32_t* perm, int64_t p0, int64_t p1, int32_t* dst);
 
 // A mode's layout packed for the host link: blocks of kPackBlock nonzeros, each
@@ -359,7 +360,6 @@ struct LossArgs {
     const float* own_factor = nullptr;
     const float* in_factors[kMaxOrder - 1] = {};
     int64_t in_rows[kMaxOrder - 1] = {};
-    const int32_t* in_hot[kMaxOrder - 1] = {};
     double* loss = nullptr;
     bool accumulate = false;                       // add to *loss instead of resetting it
     hipStream_t stream = nullptr;

@@ -1,26 +1,8 @@
-// gfx950 kernels for sparse MTTKRP (Eq. 1, Sec. 2.1), its bfloat16-factor
-// form, the sparse CP loss and the fused residual + MTTKRP gradient.
-//
-// Work decomposition (one GPU's share of the paper's scheme, Sec. 3-4):
-//  * A mode's nonzeros are sorted by output index (Sec. 3.1: all nonzeros of
-//    one output index together) and cut into chunks of CH nonzeros, the
-//    equal-size inter-shard partitions of Sec. 3.1/3.2.
-//  * A persistent grid of wave64s replaces the hardware block scheduler of
-//    Sec. 4.2: each wave takes the next chunk from a device atomic counter
-//    until none is left, so skewed slices spread over all CUs.
-//  * Inside a chunk the wave is G groups of LPR lanes.  Each lane holds RPL
-//    consecutive columns of a factor row (16 bytes), so a group loads a whole
-//    row with one coalesced access.  Group g walks its own contiguous run of
-//    the chunk's nonzeros in order and keeps the running sum of the current
-//    output row in registers (the elementwise computation, EC of Sec. 3,
-//    reduced over consecutive equal output indices instead of one atomic per
-//    nonzero as in Alg. 2).
-//  * A row that starts and ends inside one group's run is written once with a
-//    plain store.  Pieces of rows that cross group boundaries are parked in
-//    LDS and summed at the end of the chunk; only rows that cross a chunk
-//    boundary are added to memory with fp32 atomics (Sec. 3.2 uses atomics
-//    between SMs), after the init kernel has zeroed them.
-//  * Untouched output rows are zeroed once, by the init kernel.
+// The launches of the sparse MTTKRP, its bfloat16-factor form, the fused residual + MTTKRP
+// gradient and the sparse CP loss: which instance, grid and addressing a call takes, and
+// the small kernels before and after it (init, close, scale) and of the layout build
+// (permute).  The work decomposition and the kernel itself are in kernel_impl.h, the
+// one-launch form of small tensors in k_small.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -43,7 +25,7 @@ namespace dev {
 
 // ----------------------------------------------------------------- init kernel
 // Resets the work-queue counters (and the loss) and zeroes the output rows
-// the MTTKRP kernel does not store: rows that several chunks add into,
+// the MTTKRP kernel does not store: rows that several units add into,
 // untouched rows of short runs (both in the zero-row list) and long runs of
 // untouched rows.  vec4: ld, col0 and ncols are multiples of 4 (16-byte stores).
 __global__ void __launch_bounds__(kBlock) init_kernel(float* out, int64_t ld, int col0, int ncols, bool vec4,
@@ -565,7 +547,6 @@ hipError_t launch_cp_loss(const LossArgs& a)
     const int block = mttkrp_block(false);
     const Shape sh = launch_shape(fn, block, a.order - 1, a.rank * 4, false);
     if (sh.grid <= 0) return hipErrorInvalidDevice;
-    set_hot(k, sh.hot_k, a.in_hot, a.order - 1);
 #if AMPED_QUEUE_STATS
     if ((e = qstats_attach(k, launch_grid(sh, k), block, a.stream)) != hipSuccess) return e;
 #endif

@@ -483,9 +483,9 @@ amped_status build_device_layout(amped_tensor_s* t, const int32_t* indices, cons
     const size_t units = small ? (n + small_len - 1) / small_len : 0;
     const size_t small_bytes = small ? (size_t)order * (2 * Arena::step((units + 1) * 4) + Arena::step(units * 8) +
                                                         Arena::step(units * 4)) : 0;
-    // the rows that cross edges of units shorter than a chunk
+    // the rows that cross unit edges
     const int n_units = (int)((nnz + t->unit - 1) / t->unit);
-    const bool slots = t->own_units && nnz > 0 && t->unit < amped::kDefaultChunk;
+    const bool slots = t->own_units && nnz > 0;
     const size_t cuts = (size_t)(n_units + amped::kHeavyCuts), light_max = (size_t)amped::light_rows_max(n_units),
                  heavy_max = (size_t)amped::heavy_rows_max(n_units);
     const size_t slot_floats = (size_t)amped::slots_max(n_units) * amped::kSlotCols;
@@ -966,7 +966,7 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
     // build the raw COO plus one permutation; per mode at most one int per row
     // for the zero-row list and long gaps, and the hot-row tables.  (What the builds
     // take now is less; what a cap admits is unchanged, and what goes beyond the layouts
-    // is left out where it does not fit: short_unit_bytes, build_host_layout.)
+    // is left out where it does not fit: own_unit_bytes, build_host_layout.)
     const int64_t layout_bytes = (int64_t)order * (order + 1) * 4 * (nnz + 4);
     int64_t row_bytes = 0;
     for (int d = 0; d < order; ++d) row_bytes += 4 * dims[d] + 4 * amped::kHotTableLen;
@@ -1004,10 +1004,10 @@ amped_status amped_tensor_create(int order, const int64_t* dims, int64_t nnz, co
     t->n_chunks = (nnz + chunk - 1) / chunk;
     t->unit = chunk;
     t->own_units = !opts || opts->chunk_nnz == 0;
-    // under a cap that does not hold what short units need beside the layouts, the units
-    // are the chunks
+    // under a cap that does not hold what library-sized units take beside the layouts, the
+    // units are the chunks, and rows that cross them take atomics
     if (t->own_units && !host_layout && cap > 0 &&
-        peak + amped::short_unit_bytes(order, nnz, amped::work_unit(nnz)) > cap)
+        peak + amped::own_unit_bytes(order, nnz, amped::work_unit(nnz)) > cap)
         t->own_units = false;
     if (t->own_units)
         t->unit = host_layout ? amped::stream_work_unit(std::min(stage_len, nnz)) : amped::work_unit(nnz);

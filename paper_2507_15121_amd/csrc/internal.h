@@ -28,11 +28,11 @@ constexpr int64_t kMaxChunk = int64_t(1) << 28;
 // more; 2M 103 us (one per wave), 128 us (512); 5M 309, 233, 248 us; 10M 600, 446,
 // 428, 450 us (order 4: 740, 703, 740 us with the last three); 20M 868 us (5120),
 // 809, 830; rank 64 with bfloat16 factors 1002, 934, 955; 50M 2090, -, 2071, 2045;
-// 200M 8694, -, 8756, 8626.  From 64M on the unit is 4096 all the same: a heavy row
-// takes one fp32 atomic per unit, and their rounding then decides the result's error
+// 200M 8694, -, 8756, 8626 (units of 2048).  From 64M on the unit is 4096 all the same:
+// with one fp32 atomic per unit into a heavy row their rounding decided the result's error
 // (40M nonzeros, units of 2048 and 4096: 4.0e-7 and 4.1e-7 of the outputs' norm; 100M
 // 4.7e-7 and 4.4e-7; 200M 5.6e-7 and 4.9e-7; 8192, whose sums in registers are longer,
-// 5.2e-7 to 5.6e-7).
+// 5.2e-7 to 5.6e-7).  Shorter units have not been measured since heavy rows have slots.
 constexpr int64_t kGridWaves = 2048;
 constexpr int64_t kTileNnz = 256;      // a unit is whole tiles of the kernel
 constexpr int64_t kMaxRoundUnit = 2560;
@@ -61,7 +61,7 @@ inline int64_t stream_work_unit(int64_t shard)
     while (u < kDefaultChunk && u * kGridWaves < shard) u *= 2;
     return u;
 }
-// Heavy rows: those with kHeavyCuts or more edges of units shorter than kDefaultChunk
+// Heavy rows: those with kHeavyCuts or more edges of units that the library sizes
 // inside.  One fp32 atomic per unit would make their error grow with the number of
 // units (factors in (0, 1), a row of 199k nonzeros, rank 32: units of 512, 1024, 2048,
 // 4096 2.9e-7, 2.5e-7, 1.4e-7, 1.1e-7 of the row), so in a mode that has such rows the
@@ -73,7 +73,9 @@ inline int64_t stream_work_unit(int64_t shard)
 // the queue, and rows with few edges stay atomics.  All modes of 300k, 1M and 3M nonzeros
 // with Zipf rows at rank 32: atomics only 37, 64 and 139 us; so 43, 72 and 150; with both
 // launches 48, 74 and 152 (a closing launch takes 4 to 6 us, 1.5 more than one that has
-// nothing to add).  10M, ALS sweep: 699 and 720 us; 20M rank 64 bfloat16: 945 and 981.
+// nothing to add).  10M, ALS sweep: 699 and 720 us; 20M rank 64 bfloat16: 945 and 981;
+// 200M, units of 4096: 8437 and 8504, its error 5.3e-7 and 3.7e-7 of the outputs' norm
+// (factors in (-1, 1)).
 //  Streamed layouts have no slots: there a mode with a heavy row takes heavy_units units at
 // a time, whole chunks or a little more.
 constexpr int kHeavyCuts = 8;          // residual_units() is at most this
@@ -218,7 +220,7 @@ hipError_t launch_slot_rows(const int32_t* keys, int64_t n, int64_t unit, int n_
                             int32_t* counts, hipStream_t st);
 // The most device bytes that units sized by the library take beside the layouts: the
 // tables and slots of rows that cross units, the tables and shares of the one-launch MTTKRP.
-inline int64_t short_unit_bytes(int order, int64_t nnz, int64_t unit)
+inline int64_t own_unit_bytes(int order, int64_t nnz, int64_t unit)
 {
     const int64_t n = (nnz + unit - 1) / unit;
     int64_t mode = 8 * (n + kHeavyCuts) + 16 * (light_rows_max(n) + heavy_rows_max(n)) + slots_max(n) * kSlotCols * 4 + 4 * 256;

@@ -24,8 +24,8 @@
 //    plain store.  Pieces of rows that cross group boundaries are parked in
 //    LDS and summed at the end of the unit; only rows that cross a unit's
 //    boundary are added to memory with fp32 atomics (Sec. 3.2 uses atomics
-//    between SMs), after the init kernel has zeroed them.  Where units are
-//    shorter than 4096 the pieces of rows that span many of them, or of all that
+//    between SMs), after the init kernel has zeroed them.  Where the library
+//    sizes the units the pieces of rows that span many of them, or of all that
 //    cross an edge, go to slots instead, which close_kernel adds in fp64.
 //  * Untouched output rows are zeroed once, by the init kernel or close_kernel.
 //  * From 32M nonzeros on, MTTKRP keeps the most-used rows of each input factor

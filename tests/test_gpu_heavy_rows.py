@@ -119,3 +119,26 @@ def test_rows_around_the_least_units(lengths, rank):
             api.cp_grad(t, d, dfac[:3], -2.0, out=got)
             np.testing.assert_array_equal(got.cpu().numpy(), oracle.cp_grad(idx[:3], val, dims[:3], factors[:3], d).astype(np.float32))
         t.close()
+
+
+def test_heavy_row_of_a_large_tensor():
+    """Units of 4096 (from 2^26 nonzeros on): a row of 13.4M nonzeros spans 3280 of them.
+    A unit's sum is 8 groups' of 512 terms each: sqrt(512 / 36) * 2^-23 / sqrt(8 * 3280) =
+    2.8e-9 beside the rounding, and what little a group's sums are biased by."""
+    nnz, rank = (1 << 26) + 100_001, 32
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    dims = (40_000, 30_000, 20_000)
+    idx = torch.stack([torch.randint(d, (nnz,), generator=gen, device="cuda", dtype=torch.int32) for d in dims])
+    idx[0][torch.rand(nnz, generator=gen, device="cuda") < 0.2] = 777
+    val = torch.rand(nnz, generator=gen, device="cuda") + 0.1
+    dev = [torch.rand((d, rank), generator=gen, device="cuda") + 0.1 for d in dims]
+    ref = torch.zeros(rank, dtype=torch.float64, device="cuda")
+    for at in torch.nonzero(idx[0] == 777)[:, 0].split(1 << 20):
+        ref += (val[at].double()[:, None] * dev[1][idx[1, at].long()].double() * dev[2][idx[2, at].long()].double()).sum(0)
+    t = api.Tensor(idx.cpu().numpy(), val.cpu().numpy(), dims)
+    got = api.mttkrp(t, 0, dev)[777]
+    assert torch.equal(got, api.mttkrp(t, 0, dev)[777])
+    assert float((got.double() - ref).norm() / ref.norm()) <= ROUNDED + 3e-8
+    grad = api.cp_grad(t, 0, dev, -2.0)
+    assert torch.equal(grad[777], api.cp_grad(t, 0, dev, -2.0)[777])
+    t.close()

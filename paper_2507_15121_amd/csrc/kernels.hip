@@ -229,13 +229,15 @@ __global__ void __launch_bounds__(kBlock) scale_kernel(float* x, int64_t n, cons
 
 // The output rows whose pieces have slots, each piece a chunk's (per_chunk units) sum, in
 // fp64 and in one order whatever the waves' was; and the untouched rows, where the init
-// kernel is left out.  Blocks: one per heavy row and 32 columns, then one per 16 light rows
-// (a wave each), then those that zero.  cw lanes of 4 columns hold a piece, a wave's or
+// kernel is left out.  Blocks: one per heavy row and 32 columns, then those of the light
+// rows (a wave each), then those that zero.  cw lanes of 4 columns hold a piece, a wave's or
 // block's pieces lie side by side, a heavy row's 8 deep; sums by shuffles, then through
 // LDS.  What bounds it is latency: the row, then one round of loads (a heavy row's 8 BLOCK
-// / cw pieces) of slots that other XCDs have just written.  4.8 us for 23 rows of up to 185
-// pieces at rank 32 (a mode of 5M nonzeros, whose kernel takes 76), 11.4 for 195 rows of up
-// to 1500 at rank 64 (20M, 315); blocks of 1024 threads where a row may have thousands.
+// / cw pieces) of slots that other XCDs have just written.  4.8 us for 23 heavy rows of up
+// to 185 pieces at rank 32 (a mode of 5M nonzeros, whose kernel takes 76), 12 for 195 rows
+// of up to 1500 at rank 64 (20M, 315), 84 for one of 18,900 (1B, 16,200); blocks of 1024
+// threads where a row may have thousands.  With 16, 8 and 4 columns per block the second
+// took 13, 23 and 45 us.
 constexpr int kCloseCols = 32;
 struct CloseParams {
     const int4* heavy;

@@ -28,9 +28,10 @@
  *    Launches are asynchronous; device faults surface at the caller's next
  *    synchronisation.
  *  - A tensor handle is immutable after creation and binds the HIP device that
- *    was current at creation.  It owns a small device work queue per mode, so
- *    calls that use the same handle AND the same mode (or two cp_loss calls)
- *    must be ordered on one stream; calls on different modes may overlap,
+ *    was current at creation.  It owns a small device work queue per mode, and
+ *    memory for the pieces of output rows that several waves share, so calls
+ *    that use the same handle AND the same mode (or two cp_loss calls) must be
+ *    ordered on one stream; calls on different modes may overlap,
  *    except on a handle with host-resident layouts (options.host_layout),
  *    whose calls share its shard buffers and must all be ordered on one
  *    stream.  amped_cp_als_sweep calls on one handle must not overlap.
